@@ -156,7 +156,10 @@ gr_status gr_sssp_noalloc(const gr_graph *g, int32_t src, void *dist_out, void *
 typedef enum {
     GR_LOOP_AUTO = 0,       /* the library's choice: gr_graph_tune's if run, else the
                                single-workgroup loop for graphs of maximum out-degree <= 64
-                               that fit it (GR_LOOP_LDS), the asynchronous loop for other
+                               that fit it (GR_LOOP_LDS), the asynchronous loop over tiles
+                               for graphs that have them (see below) and requests that set
+                               nothing but push, timing or barrier_timeout_us, the
+                               asynchronous loop for other
                                graphs of maximum out-degree <= 64 and n <= 65,536 (the
                                queued loop when the request needs pull or a near-far
                                split), the host-driven loop for graphs of maximum
@@ -175,7 +178,15 @@ typedef enum {
                                4 n entries overflowed), frontier_sum = vertex expansions.
                                The call waits for the stream after each phase.  The
                                environment variable GR_ASYNC_LIST_CAP (entries, >= 1)
-                               lowers the list capacity, to test the overflow path. */
+                               lowers the list capacity, to test the overflow path.
+                               Over tiles (only AUTO picks it; stats report this mode):
+                               graphs of maximum out-degree <= 64 whose vertices cut into
+                               tiles of up to 4,096 with most arcs inside (meshes, road
+                               networks, whatever their vertex order) hold a second copy
+                               of their arcs by tile; one persistent kernel runs a tile
+                               per workgroup in LDS, improvements cross tiles through
+                               inboxes.  Extra workspace: about 64 bytes per tile and 4
+                               per vertex with arcs from other tiles. */
     GR_LOOP_LDS = 5         /* single workgroup (Section III-A's loop with a workgroup
                                barrier per round): one launch of one 1024-thread workgroup
                                copies the distances, row offsets and arcs (a 16-bit head and

@@ -27,6 +27,7 @@
 #include "gr_multi.h"
 #include "gr_noalloc.h"
 #include "gr_sched.h"
+#include "gr_tile.h"
 
 using namespace gr;
 
@@ -180,6 +181,10 @@ struct gr_graph {
     // single-workgroup loop's padded layout; nullptr when it does not fit
     uint32_t *d_ell = nullptr;
     int32_t ell_lg = 0;
+    // tiled layout (bounded-degree graphs that cut into tiles; ntiles = 0
+    // otherwise), and whether AUTO's weighted queries run over it
+    TileSet tiles;
+    bool auto_tiled = false;
     // iterations of the last completed queued-loop query (first chunk size)
     mutable std::atomic<int32_t> last_iters{0};
     double locality = 1.0;  // fraction of arcs with |u - v| < locality_span(n)
@@ -213,6 +218,7 @@ static void graph_free(gr_graph *g) {
     if (g->d_ro) (void)hipFree(g->d_ro);
     if (g->d_adj) (void)hipFree(g->d_adj);
     if (g->d_ell) (void)hipFree(g->d_ell);
+    if (g->tiles.base) (void)hipFree(g->tiles.base);
     if (g->d_pro) (void)hipFree(g->d_pro);
     if (g->d_padj) (void)hipFree(g->d_padj);
     for (int i = 0; i < 2; ++i) {
@@ -346,10 +352,13 @@ static gr_status graph_build(gr_graph *g, int32_t n, int32_t m, const int32_t *r
     BUILD_TRY(launch_pack_arcs(tcol, tw, m, g->d_adj, st), "pack arcs");
     if (wt == GR_W_F32) BUILD_TRY(launch_canon_negzero(g->d_adj, m, st), "canonicalise -0");
     int32_t nonempty = 0;
+    int64_t over4 = 0, over8 = 0;  // arcs past the fourth / eighth of their vertex
     for (int32_t v = 0; v < n; ++v) {
         const int32_t d = g->h_ro[v + 1] - g->h_ro[v];
         g->max_degree = std::max(g->max_degree, d);
         nonempty += d > 0;
+        over4 += std::max(d - 4, 0);
+        over8 += std::max(d - 8, 0);
     }
     // Small rounds by default where they apply (bounded degree): measured
     // faster on grids and road-like graphs, whose many rounds are small.
@@ -449,6 +458,14 @@ static gr_status graph_build(gr_graph *g, int32_t n, int32_t m, const int32_t *r
     {
         gr_status s = build_members(g, d, 0, st, sc);
         if (s != GR_OK) return s;
+    }
+
+    // Tiles: for bounded degrees, unless the single-workgroup loop runs the
+    // whole graph (it needs no inboxes and starts faster).
+    if (g->max_degree <= kTileMaxDegree && g->auto_loop != GR_LOOP_LDS) {
+        BUILD_TRY(tile_build(&g->tiles, n, m, g->d_ro, g->d_adj, (int)wt, over4, over8, st), "tiles");
+        g->auto_tiled = g->tiles.ntiles > 0;
+        g->dev_bytes += g->tiles.bytes;
     }
 
     const bool want_part = !(flags & GR_NO_PARTITION) &&
@@ -1041,6 +1058,81 @@ static gr_status run_lds_batch(const gr_graph *const *graphs, const int32_t *src
     return GR_OK;
 }
 
+// Tiled asynchronous loop: k queries on graphs with tiles (of one slot count),
+// rows[i] receiving query i's distances; one initialisation and one persistent
+// launch for all of them, and one wait.  us (optional): the launches' time.
+struct TileTotals {
+    int64_t arcs = 0, items = 0;
+};
+static gr_status run_tiles(const gr_graph *const *graphs, const int32_t *srcs, int32_t k, uint32_t *const *rows,
+                           int wt, hipStream_t st, int64_t timeout_us, TileTotals *tot, double *us) {
+    DeviceInfo di;
+    gr_status s = device_info(graphs[0]->device, &di);
+    if (s != GR_OK) return s;
+    unsigned long long *hp = pinned_slot();
+    if (!hp) return fail(GR_ERR_OUT_OF_MEMORY, "pinned host buffer");
+    const TileSet *sets[kTileMaxJobs];
+    for (int32_t i = 0; i < k; ++i) sets[i] = &graphs[i]->tiles;
+    void *ws = nullptr;
+    HIP_TRY(hipMallocAsync(&ws, tile_ws_bytes(sets, k), st));
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    const bool timed = us && hipEventCreate(&ev[0]) == hipSuccess && hipEventCreate(&ev[1]) == hipSuccess;
+    const uint64_t spin = (uint64_t)timeout_us * (uint64_t)di.wall_khz / 1000ull;
+    for (int i = 0; i < kTileStatWords; ++i) hp[i] = 0ull;
+    if (timed) (void)hipEventRecord(ev[0], st);
+    hipError_t e = launch_tiles(sets, srcs, rows, k, wt, ws, di.num_cu, spin, hp, st);
+    if (timed) (void)hipEventRecord(ev[1], st);
+    const hipError_t e2 = hipFreeAsync(ws, st);
+    if (e == hipSuccess) e = e2;
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (timed && e == hipSuccess) {
+        float ms = 0.f;
+        (void)hipEventElapsedTime(&ms, ev[0], ev[1]);
+        *us = 1e3 * ms;
+    }
+    for (auto &x : ev)
+        if (x) (void)hipEventDestroy(x);
+    if (e != hipSuccess) return hip_fail(e, "tiled loop");
+    if (hp[0] == 3ull)
+        return fail(GR_ERR_HIP, "tiled loop: a wait exceeded %lld us", (long long)timeout_us);
+    if (hp[0] != 1ull) return fail(GR_ERR_HIP, "tiled loop ended in state %llu", hp[0]);
+    tot->arcs = (int64_t)hp[1];
+    tot->items = (int64_t)hp[2];
+    return GR_OK;
+}
+
+static gr_status run_tiled(const gr_graph *g, int32_t src, uint32_t *dist, hipStream_t st, const RunCfg &rc,
+                           gr_sssp_stats *stats) {
+    TileTotals tot;
+    double us = 0;
+    const int wt = rc.dg->wt == 2 ? 2 : g->plain.wt;
+    gr_status s = run_tiles(&g, &src, 1, &dist, wt, st, rc.barrier_timeout_us, &tot, rc.timing ? &us : nullptr);
+    if (s != GR_OK) return s;
+    if (stats) {
+        gr_sssp_stats local{};
+        local.loop = GR_LOOP_ASYNC;
+        local.layout = GR_LAYOUT_PLAIN;
+        local.relax_filter = GR_RELAX_DIST;
+        local.iterations = 1;  // one worklist phase
+        local.edges_pushed = tot.arcs;
+        local.push_frontier_sum = local.frontier_sum = tot.items;
+        local.push_launches = 1;
+        local.launches = 2;
+        local.push_us = us;
+        *stats = local;
+    }
+    return GR_OK;
+}
+
+// Whether AUTO runs over the graph's tiles: weighted queries with nothing of
+// the round-based schedules asked for.
+static bool wants_tiles(const gr_graph *g, const gr_sssp_opts *o) {
+    if (!g->auto_tiled) return false;
+    return !o || (o->loop == GR_LOOP_AUTO && (o->direction == GR_DIR_AUTO || o->direction == GR_DIR_PUSH) &&
+                  o->alpha_x16 <= 0 && o->max_iters <= 0 && o->layout == GR_LAYOUT_AUTO && o->filter == 0 &&
+                  (o->delta == 0 || o->delta == GR_DELTA_OFF) && o->relax_filter == 0 && o->local_hops == 0);
+}
+
 static gr_status run_async(const gr_graph *g, int32_t src, uint32_t *dist, hipStream_t st, const RunCfg &rc,
                            gr_sssp_stats *stats) {
     DeviceInfo di;
@@ -1136,6 +1228,8 @@ extern "C" gr_status gr_sssp_ex(const gr_graph *g, int32_t src, void *dist_out, 
     RunCfg rc;
     gr_status s = check_opts(g, opts, &rc);
     if (s != GR_OK) return s;
+    if (wants_tiles(g, opts))
+        return run_tiled(g, src, static_cast<uint32_t *>(dist_out), static_cast<hipStream_t>(stream), rc, stats);
     int loop = rc.loop;
     if (loop == GR_LOOP_AUTO) {
         loop = g->auto_loop;
@@ -1298,7 +1392,8 @@ static gr_status run_single_auto(const gr_graph *g, int32_t src, uint32_t *dist,
     if (s != GR_OK) return s;
     const int loop = g->auto_loop;
     gr_sssp_stats one{};
-    if (loop == GR_LOOP_ASYNC) s = run_async(g, src, dist, st, rc, &one);
+    if (wants_tiles(g, nullptr)) s = run_tiled(g, src, dist, st, rc, &one);
+    else if (loop == GR_LOOP_ASYNC) s = run_async(g, src, dist, st, rc, &one);
     else if (loop == GR_LOOP_LDS) s = run_lds(g, src, dist, st, rc, &one);
     else if (loop == GR_LOOP_QUEUED) s = run_queued(g, src, dist, st, rc, &one);
     else if (loop == GR_LOOP_PERSISTENT) s = run_persistent(g, src, dist, st, rc, &one);
@@ -2191,6 +2286,7 @@ struct TuneCfg {
     int32_t relax;
     int32_t async_blocks;  // 0: the default
     int32_t local_hops;
+    bool tiled;  // the asynchronous loop over the graph's tiles (the other fields do not apply)
 };
 
 static void apply_auto(gr_graph *g, const TuneCfg &c) {
@@ -2203,6 +2299,7 @@ static void apply_auto(gr_graph *g, const TuneCfg &c) {
     g->auto_relax = c.relax;
     g->auto_async_blocks = c.async_blocks;
     g->auto_local_hops = c.local_hops;
+    g->auto_tiled = c.tiled && g->tiles.ntiles > 0;
 }
 
 // Near-far split widths to try: multiples of the mean weight of a sample of
@@ -2258,8 +2355,9 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
         if (r.relax_filter != GR_RELAX_BOUND) r.relax_filter = GR_RELAX_DIST;
         if (r.async_blocks < 0 || r.async_blocks > 65536) r.async_blocks = 0;
         if (r.local_hops < 1 || r.local_hops > 64) r.local_hops = kDefaultLocalHops;
+        // (the asynchronous loop with no block count of its own: over the tiles, where the graph has them)
         apply_auto(g, TuneCfg{r.layout, r.loop, r.dense_ratio, r.alpha_x16, r.delta, r.small, r.relax_filter,
-                              r.async_blocks, r.local_hops});
+                              r.async_blocks, r.local_hops, r.loop == GR_LOOP_ASYNC && r.async_blocks == 0});
         r.from_cache = 1;
         if (out) *out = r;
         return GR_OK;
@@ -2281,6 +2379,8 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
         o.relax_filter = c.relax;
         o.local_hops = c.local_hops;
         const int32_t saved = g->auto_dense_ratio, saved_ab = g->auto_async_blocks;
+        const bool saved_tiled = g->auto_tiled;
+        g->auto_tiled = c.tiled;
         g->auto_dense_ratio = c.dense_ratio;
         g->auto_async_blocks = c.async_blocks;
         std::vector<double> t;
@@ -2288,7 +2388,7 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
         for (int32_t rep = 0; rep <= reps && s == GR_OK; ++rep) {
             for (int32_t i = 0; i < nsrcs && s == GR_OK; ++i) {
                 const auto t0 = std::chrono::steady_clock::now();
-                s = gr_sssp_ex(g, srcs[i], dist, st, &o, nullptr);
+                s = gr_sssp_ex(g, srcs[i], dist, st, c.tiled ? nullptr : &o, nullptr);
                 if (s == GR_OK && hipStreamSynchronize(st) != hipSuccess) s = fail(GR_ERR_HIP, "tuning query");
                 const double d = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0)
                                      .count();
@@ -2297,6 +2397,7 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
         }
         g->auto_dense_ratio = saved;
         g->auto_async_blocks = saved_ab;
+        g->auto_tiled = saved_tiled;
         ++trials;
         if (s != GR_OK) return s;
         std::sort(t.begin(), t.end());
@@ -2304,10 +2405,20 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
         return GR_OK;
     };
     TuneCfg best{g->auto_layout, g->auto_loop, g->auto_dense_ratio, g->auto_alpha_x16, g->auto_delta,
-                 g->auto_small ? 1 : 0, g->auto_relax, g->auto_async_blocks, g->auto_local_hops};
+                 g->auto_small ? 1 : 0, g->auto_relax, g->auto_async_blocks, g->auto_local_hops, g->auto_tiled};
     double best_ms = 0;
     status = measure(best, &best_ms);
     const double default_ms = best_ms;
+    if (status == GR_OK && g->tiles.ntiles > 0 && !best.tiled) {
+        TuneCfg c = best;
+        c.tiled = true;
+        double ms = 0;
+        status = measure(c, &ms);
+        if (status == GR_OK && ms < best_ms) {
+            best_ms = ms;
+            best = c;
+        }
+    }
     // greedy: one knob at a time, the others at their best so far
     std::vector<std::pair<int, std::vector<int32_t>>> knobs;
     knobs.push_back({0, g->has_part ? std::vector<int32_t>{GR_LAYOUT_PLAIN, GR_LAYOUT_PARTITIONED}
@@ -2337,6 +2448,11 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
         for (int32_t v : kv.second) {
             if (status != GR_OK) break;
             TuneCfg c = best;
+            if (c.tiled) {
+                if (kv.first != 1) continue;  // only another loop can replace the tiles
+                c.tiled = false;
+                c.loop = -1;
+            }
             if (c.loop == GR_LOOP_ASYNC && kv.first != 1 && kv.first != 7) continue;  // the others do not apply
             if (c.loop == GR_LOOP_LDS && kv.first != 1) continue;
             if (kv.first == 7 && c.loop != GR_LOOP_ASYNC) continue;
@@ -2377,6 +2493,10 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
     if (status != GR_OK) return status;
     apply_auto(g, best);
     r.layout = best.layout;
+    if (best.tiled) {
+        best.loop = GR_LOOP_ASYNC;
+        best.async_blocks = 0;
+    }
     r.loop = best.loop;
     r.dense_ratio = best.dense_ratio;
     r.alpha_x16 = best.alpha_x16;

@@ -1,0 +1,88 @@
+// Tiled asynchronous loop for mesh-like graphs (declarations; see
+// gr_tile.hip for the kernels and gr_tile_build.cpp for the layout).
+//
+// The vertices are cut into tiles of at most kTileVerts that hold most arcs
+// inside; a workgroup runs one tile to its local fixed point with the
+// distances in LDS and the arcs in registers, and tiles trade improvements
+// through inboxes.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstddef>
+#include <cstdint>
+
+namespace gr {
+
+constexpr int kTileThreads = 1024;
+constexpr int kTileVpt = 4;  // vertices per thread
+constexpr int kTileShift = 12;
+constexpr int kTileVerts = 1 << kTileShift;
+static_assert(kTileThreads * kTileVpt == kTileVerts, "a workgroup covers a tile");
+// Arcs that leave a tile (or find no slot inside), at most: each thread keeps
+// two of them in registers.
+constexpr int kTileMaxExt = 2 * kTileThreads;
+
+// A tile's vertices with arcs from other tiles, at most (its inbox words).
+constexpr int kTileMaxBorder = 2 * kTileThreads;
+
+// The tiled layout of a graph (one device allocation, `base`).  A vertex's
+// place is tile << kTileShift | local.  Thread t of a workgroup owns the
+// places tile_place(t, i): each wave a run of 256 consecutive ones.
+__host__ __device__ inline int tile_place(int t, int i) { return (t >> 6) * (64 * kTileVpt) + i * 64 + (t & 63); }
+struct TileSet {
+    void *base = nullptr;
+    size_t bytes = 0;
+    int32_t ntiles = 0;
+    int32_t slots = 0;  // arc slots per vertex: 4 or 8
+    int32_t n = 0;
+    int32_t inbox = 0;  // inbox words of all tiles
+    int32_t *pos = nullptr;      // [n] place of each vertex
+    int32_t *vid = nullptr;      // [ntiles][kTileVerts] vertex at each place, -1 past the end
+    uint32_t *w = nullptr;       // [ntiles][slots][kTileVerts] weight bits
+    uint32_t *head = nullptr;    // [ntiles][slots / 2][kTileVerts] two local heads, as 16-bit byte offsets
+    uint4 *ext = nullptr;        // the other arcs: (local tail, tile or kTileInner | local head, inbox word, weight)
+    int32_t *ext_off = nullptr;  // [ntiles + 1]
+    int32_t *in_off = nullptr;   // [ntiles + 1]
+    int32_t *in_at = nullptr;    // [inbox] local place of each inbox word's vertex
+};
+constexpr uint32_t kTileInner = 0x80000000u;
+
+// Builds the layout of a CSR (device arrays, arcs (head, weight bits)) whose
+// maximum degree is at most kTileMaxDegree.  *out stays empty (ntiles = 0) when
+// the graph does not cut into tiles (see gr_tile_build.cpp); over4 / over8:
+// arcs beyond the fourth / eighth of their vertex.
+constexpr int32_t kTileMaxDegree = 64;
+hipError_t tile_build(TileSet *out, int32_t n, int32_t m, const int32_t *ro, const uint2 *adj, int wt, int64_t over4,
+                      int64_t over8, hipStream_t st);
+
+// One query of a launch.
+struct TileJob {
+    const int32_t *pos;
+    const int32_t *vid;
+    const uint32_t *w;
+    const uint32_t *head;
+    const uint4 *ext;
+    const int32_t *ext_off;
+    const int32_t *in_off;
+    const int32_t *in_at;
+    uint32_t *dist;   // the query's output, n values
+    uint32_t *inbox;  // workspace
+    uint32_t *flags;  // workspace: one word per tile, kTileFlagStride apart
+    int32_t n, ntiles, ninbox, src;
+};
+constexpr int kTileFlagStride = 16;
+constexpr int kTileMaxJobs = 64;
+constexpr int kTileMaxTiles = 1 << 24;  // a queue entry packs (query, tile) in 30 bits
+// Statistics words the kernel writes to stat (pinned host memory): status (1
+// done, 3 a wait timed out), arcs relaxed, vertex expansions.
+constexpr int kTileStatWords = 3;
+
+// Workspace bytes of a launch over these queries' layouts, and the launch:
+// every dist row, in at most `groups` co-resident workgroups per compute unit.
+// wt: 0 uint32, 1 binary32, 2 unit steps; all layouts have `slots` slots.
+size_t tile_ws_bytes(const TileSet *const *sets, int32_t k);
+hipError_t launch_tiles(const TileSet *const *sets, const int32_t *srcs, uint32_t *const *dist, int32_t k, int wt,
+                        void *ws, int num_cu, uint64_t spin_ticks, unsigned long long *stat, hipStream_t st);
+
+}  // namespace gr
