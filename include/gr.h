@@ -181,12 +181,12 @@ typedef enum {
                                lowers the list capacity, to test the overflow path.
                                Over tiles (only AUTO picks it; stats report this mode):
                                graphs of maximum out-degree <= 64 whose vertices cut into
-                               tiles of up to 4,096 with most arcs inside (meshes, road
+                               tiles of up to 3,584 with most arcs inside (meshes, road
                                networks, whatever their vertex order) hold a second copy
                                of their arcs by tile; one persistent kernel runs a tile
                                per workgroup in LDS, improvements cross tiles through
-                               inboxes.  Extra workspace: about 64 bytes per tile and 4
-                               per vertex with arcs from other tiles. */
+                               one word per arc.  Extra workspace: about 64 bytes per
+                               tile and 4 per arc between tiles. */
     GR_LOOP_LDS = 5         /* single workgroup (Section III-A's loop with a workgroup
                                barrier per round): one launch of one 1024-thread workgroup
                                copies the distances, row offsets and arcs (a 16-bit head and
@@ -337,8 +337,10 @@ gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsrcs, int32_t
  * opts as for gr_sssp_ex, except: delta must be 0 / GR_DELTA_OFF, the
  * persistent loop is GR_ERR_INVALID_ARG, and AUTO runs the single-workgroup
  * loop (push only) on graphs that fit one workgroup's LDS unless pull or
- * alternation is asked for, else the host-driven loop on graphs of maximum
- * out-degree > 64 and the queued loop otherwise.
+ * alternation is asked for, else the asynchronous loop over tiles on graphs of
+ * more than 65,536 vertices that have them (see gr_loop_mode; unless the
+ * request names a round-based schedule), else the host-driven loop on graphs of
+ * maximum out-degree > 64 and the queued loop otherwise.
  */
 gr_status gr_bfs(const gr_graph *g, int32_t src, void *depth_out, void *stream);
 gr_status gr_bfs_ex(const gr_graph *g, int32_t src, void *depth_out, void *stream, const gr_sssp_opts *opts,
@@ -373,8 +375,9 @@ typedef struct {
  * vertex (distances) + 16 (masks) + about 28 (frontier marks and two queues).
  * k = 1 runs gr_sssp's schedule.  A graph whose AUTO loop is the single-
  * workgroup loop (GR_LOOP_LDS) runs that loop for every source instead, one
- * workgroup per source in one launch, with no workspace.  The current device
- * must be the graph's.
+ * workgroup per source in one launch, with no workspace; one whose AUTO runs
+ * over tiles runs the sources' tiles in one launch (stats: rounds 1, replays 0).
+ * The current device must be the graph's.
  */
 gr_status gr_sssp_batch(const gr_graph *g, const int32_t *srcs, int32_t k, void *dist_out, void *stream);
 /* gr_sssp_batch with statistics (stats may be NULL). */
@@ -406,7 +409,9 @@ gr_status gr_sssp_batch_ex(const gr_graph *g, const int32_t *srcs, int32_t k, vo
  * graph's AUTO loop is the single-workgroup loop (GR_LOOP_LDS), and all fit
  * one arc layout (row offsets, or arcs padded to the same slot count), each
  * query runs that loop in a workgroup of its own, all in one launch, with no
- * workspace (stats->replays = 0).
+ * workspace (stats->replays = 0).  Queries on graphs whose AUTO runs over tiles
+ * run in launches of their own before the others (rounds 1, or 0 for a source
+ * without arcs).
  */
 gr_status gr_sssp_multi(const gr_graph *const *graphs, const int32_t *srcs, int32_t k, void *const *dist_out,
                         void *stream, gr_multi_stats *stats, int32_t *iterations);
@@ -449,7 +454,12 @@ typedef struct {
  * workgroup loop (GR_LOOP_LDS) and that fit its row-offset layout take no slot: an executor takes up to 64 of
  * them from anywhere in the FIFO (they hold nothing the head waits for) and
  * runs them as one launch, one workgroup per query, on a stream of its own;
- * batch_size is then that launch's query count.  cfg may be NULL. */
+ * batch_size is then that launch's query count.  Queries on graphs whose AUTO
+ * runs over tiles take no slot either: a thread of the server runs all that
+ * wait (up to 64) in one launch beside the executors; their workspace is
+ * outside the budget (about 64 bytes per tile and 4 per arc between tiles,
+ * some 2% of what the budget counts for a query).  cfg may be
+ * NULL. */
 gr_status gr_server_create(gr_server **out, size_t hbm_budget_bytes, const gr_server_config *cfg);
 /* Registers a graph (not copied; it must outlive the server). */
 gr_status gr_server_add_graph(gr_server *s, const gr_graph *g, int32_t *graph_id);
