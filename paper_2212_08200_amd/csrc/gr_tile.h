@@ -1,10 +1,10 @@
 // Tiled asynchronous loop for mesh-like graphs (declarations; see
 // gr_tile.hip for the kernels and gr_tile_build.cpp for the layout).
 //
-// The vertices are cut into tiles of at most kTileVerts that hold most arcs
+// The vertices are cut into tiles of at most kTileFill that hold most arcs
 // inside; a workgroup runs one tile to its local fixed point with the
 // distances in LDS and the arcs in registers, and tiles trade improvements
-// through inboxes.
+// through one mail word per arc between them.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -18,33 +18,36 @@ constexpr int kTileThreads = 1024;
 constexpr int kTileVpt = 4;  // vertices per thread
 constexpr int kTileShift = 12;
 constexpr int kTileVerts = 1 << kTileShift;
-static_assert(kTileThreads * kTileVpt == kTileVerts, "a workgroup covers a tile");
-// Arcs that leave a tile (or find no slot inside), at most: each thread keeps
-// two of them in registers.
-constexpr int kTileMaxExt = 2 * kTileThreads;
-
-// A tile's vertices with arcs from other tiles, at most (its inbox words).
-constexpr int kTileMaxBorder = 2 * kTileThreads;
+static_assert(kTileThreads * kTileVpt == kTileVerts, "a workgroup covers a tile's places");
+// The last two waves carry offers in and out and hold no vertices: the places
+// that the others cover are filled.
+constexpr int kTileWaves = kTileThreads / 64 - 2;
+constexpr int kOutWave = kTileWaves, kInWave = kTileWaves + 1;
+constexpr int kTileFill = kTileWaves * 64 * kTileVpt;
+// Arcs that leave a tile (or find no slot inside), and arcs that enter it from
+// other tiles, at most (held in LDS).
+constexpr int kTileMaxExt = 3072;
 
 // The tiled layout of a graph (one device allocation, `base`).  A vertex's
 // place is tile << kTileShift | local.  Thread t of a workgroup owns the
 // places tile_place(t, i): each wave a run of 256 consecutive ones.
-__host__ __device__ inline int tile_place(int t, int i) { return (t >> 6) * (64 * kTileVpt) + i * 64 + (t & 63); }
+__host__ __device__ inline int tile_place(int t, int i) { return t * kTileVpt + i; }
 struct TileSet {
     void *base = nullptr;
     size_t bytes = 0;
     int32_t ntiles = 0;
     int32_t slots = 0;  // arc slots per vertex: 4 or 8
     int32_t n = 0;
-    int32_t inbox = 0;  // inbox words of all tiles
+    int32_t mail = 0;  // mail words: one per arc of ext
     int32_t *pos = nullptr;      // [n] place of each vertex
     int32_t *vid = nullptr;      // [ntiles][kTileVerts] vertex at each place, -1 past the end
     uint32_t *w = nullptr;       // [ntiles][slots][kTileVerts] weight bits
     uint32_t *head = nullptr;    // [ntiles][slots / 2][kTileVerts] two local heads, as 16-bit byte offsets
-    uint4 *ext = nullptr;        // the other arcs: (local tail, tile or kTileInner | local head, inbox word, weight)
+    uint4 *ext = nullptr;        // the other arcs by tail's tile, sorted by head's: (local tail, head's tile or
+                                 // kTileInner | local head, 0, weight)
     int32_t *ext_off = nullptr;  // [ntiles + 1]
+    uint2 *in = nullptr;         // the arcs of ext that enter each tile: (arc = mail word, local head)
     int32_t *in_off = nullptr;   // [ntiles + 1]
-    int32_t *in_at = nullptr;    // [inbox] local place of each inbox word's vertex
 };
 constexpr uint32_t kTileInner = 0x80000000u;
 
@@ -64,12 +67,12 @@ struct TileJob {
     const uint32_t *head;
     const uint4 *ext;
     const int32_t *ext_off;
+    const uint2 *in;
     const int32_t *in_off;
-    const int32_t *in_at;
     uint32_t *dist;   // the query's output, n values
-    uint32_t *inbox;  // workspace
+    uint32_t *mail;   // workspace: the lowest offer along each arc of ext
     uint32_t *flags;  // workspace: one word per tile, kTileFlagStride apart
-    int32_t n, ntiles, ninbox, src;
+    int32_t n, ntiles, nmail, src;
 };
 constexpr int kTileFlagStride = 16;
 constexpr int kTileMaxJobs = 64;

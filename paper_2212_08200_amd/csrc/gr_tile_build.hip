@@ -1,5 +1,5 @@
 // Builds the tiled layout (gr_tile.h): the vertices of a mesh-like graph cut
-// into tiles of at most kTileVerts with most arcs inside.
+// into tiles of at most kTileFill with most arcs inside.
 //
 // 1. Cells: one seed vertex per run of kCellVerts ids; sweeps over the arcs
 //    give every other vertex the cell of a neighbour (a graph Voronoi diagram
@@ -27,7 +27,7 @@ namespace {
 
 // Vertices per cell: fine cells fill the tiles better, coarse ones keep the
 // host's merge short.
-int32_t cell_verts(int32_t n) { return n > (1 << 17) ? 256 : 64; }
+int32_t cell_verts(int32_t n) { return n > (1 << 15) ? 256 : 128; }
 constexpr int kSweepBatch = 8;
 constexpr int kMaxSweeps = 96;
 constexpr int32_t kMaxPairs = 1 << 20;
@@ -119,17 +119,6 @@ __global__ __launch_bounds__(256) void k_tile_place(int32_t n, const int32_t *la
     pos[v] = p;
 }
 
-__global__ __launch_bounds__(256) void k_tile_mark(int32_t n, const int32_t *ro, const uint2 *adj,
-                                                   const int32_t *pos, uint8_t *border) {
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v >= n) return;
-    const int32_t q = pos[v] >> kTileShift;
-    for (int32_t e = ro[v]; e < ro[v + 1]; ++e) {
-        const uint32_t x = adj[e].x;
-        if (pos[x] >> kTileShift != q) border[x] = 1;
-    }
-}
-
 // One workgroup per tile: its vertices sorted by cell and id (a wave then owns
 // a compact patch, and most waves are idle while a front crosses the tile).
 __global__ __launch_bounds__(kTileThreads) void k_tile_sort(const int32_t *label, int32_t *vid, int32_t *pos) {
@@ -160,51 +149,13 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_sort(const int32_t *label
     }
 }
 
-// One workgroup per tile: its border vertices' inbox words, in order of place.
-// in_at == NULL: only their number.
-__global__ __launch_bounds__(kTileThreads) void k_tile_border(const uint8_t *border, const int32_t *vid,
-                                                              int32_t *nborder, const int32_t *in_off, int32_t *in_at,
-                                                              int32_t *in_word) {
-    __shared__ int sWave[kTileVerts / 64];
-    const int t = threadIdx.x, lane = t & 63;
-    const size_t base = (size_t)blockIdx.x << kTileShift;
-    bool b[kTileVpt];
-    unsigned long long m[kTileVpt];
-#pragma unroll
-    for (int i = 0; i < kTileVpt; ++i) {
-        const int32_t v = vid[base + tile_place(t, i)];
-        b[i] = v >= 0 && border[v] != 0;
-        m[i] = __ballot(b[i]);
-        if (lane == 0) sWave[tile_place(t, i) >> 6] = (int)__popcll(m[i]);
-    }
-    __syncthreads();
-    if (in_at == nullptr) {
-        if (t == 0) {
-            int n = 0;
-            for (int k = 0; k < kTileVerts / 64; ++k) n += sWave[k];
-            nborder[blockIdx.x] = n;
-        }
-        return;
-    }
-#pragma unroll
-    for (int i = 0; i < kTileVpt; ++i) {
-        if (!b[i]) continue;
-        const int p = tile_place(t, i);
-        int at = in_off[blockIdx.x] + (int)__popcll(m[i] & ((1ull << lane) - 1ull));
-        for (int k = 0; k < p >> 6; ++k) at += sWave[k];
-        in_at[at] = p;
-        in_word[vid[base + p]] = at;
-    }
-}
-
 // One workgroup per tile.  FILL 0: the arcs inside (the first `slots` of each
 // vertex) into the columns, and the number of the others; 1: the others.
 template <int FILL>
 __global__ __launch_bounds__(kTileThreads) void k_tile_arcs(int slots, uint32_t inf, const int32_t *ro,
                                                             const uint2 *adj, const int32_t *pos, const int32_t *vid,
-                                                            uint32_t *w, uint16_t *head, int32_t *next,
-                                                            const int32_t *in_word, const int32_t *ext_off,
-                                                            uint4 *ext) {
+                                                            uint32_t *w, uint16_t *head, int32_t *next, int32_t *nin,
+                                                            const int32_t *ext_off, uint4 *ext) {
     __shared__ int sN;
     const int t = threadIdx.x;
     const int32_t tile = blockIdx.x;
@@ -228,10 +179,10 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_arcs(int slots, uint32_t 
                     ++used;
                 } else if (FILL == 0) {
                     ++out;
+                    if (q != tile) atomicAdd(nin + q, 1);
                 } else {
                     const int c = atomicAdd(&sN, 1);
-                    ext[ext_off[tile] + c] = q == tile ? make_uint4((uint32_t)i, kTileInner | l, 0u, a.y)
-                                                       : make_uint4((uint32_t)i, (uint32_t)q, (uint32_t)in_word[a.x], a.y);
+                    ext[ext_off[tile] + c] = make_uint4((uint32_t)i, q == tile ? kTileInner | l : (uint32_t)q, l, a.y);
                 }
             }
         }
@@ -250,7 +201,65 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_arcs(int slots, uint32_t 
     }
 }
 
-// Joins the cells into tiles of at most kTileVerts vertices: a tile grows by
+// Sorts n <= kTileMaxExt keys in LDS (size: a power of two >= n, the keys past
+// n all ones).
+__device__ __forceinline__ void sort_keys(unsigned long long *key, int size) {
+    for (int k = 2; k <= size; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            __syncthreads();
+            for (int i = threadIdx.x; i < size / 2; i += kTileThreads) {
+                const int a = 2 * i - (i & (j - 1)), b = a + j;
+                const unsigned long long x = key[a], y = key[b];
+                if ((x > y) == ((a & k) == 0)) {
+                    key[a] = y;
+                    key[b] = x;
+                }
+            }
+        }
+    __syncthreads();
+}
+
+// One workgroup per tile: its arcs of ext sorted by head's tile (those inside
+// last), so that offers to one tile go out together; then listed with the
+// tiles they enter.
+__global__ __launch_bounds__(kTileThreads) void k_tile_ext_sort(const int32_t *ext_off, uint4 *ext, int32_t *in_cur,
+                                                                uint2 *in) {
+    __shared__ uint4 sE[kTileMaxExt];
+    __shared__ unsigned long long key[4096];
+    static_assert(kTileMaxExt <= 4096, "the list fits the sort");
+    const int t = threadIdx.x;
+    const int32_t e0 = ext_off[blockIdx.x], n = ext_off[blockIdx.x + 1] - e0;
+    int size = 64;
+    while (size < n) size <<= 1;
+    for (int i = t; i < size; i += kTileThreads) {
+        if (i < n) sE[i] = ext[e0 + i];
+        // (head's tile, head, tail): one order, but for parallel arcs
+        key[i] = i < n ? (unsigned long long)sE[i].y << 32 | (unsigned long long)sE[i].z << 19 |
+                             (unsigned long long)(sE[i].x & 127u) << 12 | (unsigned long long)i
+                       : ~0ull;
+    }
+    sort_keys(key, size);
+    for (int i = t; i < n; i += kTileThreads) {
+        const uint4 x = sE[(uint32_t)key[i] & 4095u];
+        ext[e0 + i] = x;
+        if (!(x.y & kTileInner)) in[atomicAdd(in_cur + x.y, 1)] = make_uint2((uint32_t)(e0 + i), x.z);
+    }
+}
+
+// One workgroup per tile: the arcs that enter it, sorted by mail word.
+__global__ __launch_bounds__(kTileThreads) void k_tile_in_sort(const int32_t *in_off, uint2 *in) {
+    __shared__ unsigned long long key[4096];
+    const int t = threadIdx.x;
+    const int32_t e0 = in_off[blockIdx.x], n = in_off[blockIdx.x + 1] - e0;
+    int size = 64;
+    while (size < n) size <<= 1;
+    for (int i = t; i < size; i += kTileThreads)
+        key[i] = i < n ? (unsigned long long)in[e0 + i].x << 32 | in[e0 + i].y : ~0ull;
+    sort_keys(key, size);
+    for (int i = t; i < n; i += kTileThreads) in[e0 + i] = make_uint2((uint32_t)(key[i] >> 32), (uint32_t)key[i]);
+}
+
+// Joins the cells into tiles of at most kTileFill vertices: a tile grows by
 // the neighbouring cell it shares most sampled border arcs with, among those
 // that fit; the next tile starts beside the tiles made so far.  Returns the
 // number of tiles, or -1 when a cell is too large.
@@ -296,7 +305,7 @@ int32_t merge_cells(const std::vector<unsigned int> &size, const std::vector<uin
                     continue;
                 }
                 front[keep++] = x;
-                if (gain[x] > best && have + size[x] <= kTileVerts) {
+                if (gain[x] > best && have + size[x] <= kTileFill) {
                     best = gain[x];
                     add = x;
                 }
@@ -310,7 +319,7 @@ int32_t merge_cells(const std::vector<unsigned int> &size, const std::vector<uin
         fill.push_back(have);
     };
     for (int32_t i = 0; i < c; ++i) {
-        if (size[i] > (unsigned)kTileVerts) return -1;
+        if (size[i] > (unsigned)kTileFill) return -1;
         if (size[i] == 0 || (*tile_of)[i] >= 0) continue;
         starts.push_back(i);
         while (!starts.empty()) {
@@ -329,7 +338,7 @@ int32_t merge_cells(const std::vector<unsigned int> &size, const std::vector<uin
     std::vector<int32_t> links((size_t)nt, 0);
     int32_t spare = -1;
     for (int32_t t = 0; t < nt; ++t) {
-        if (fill[t] * 2 > kTileVerts) continue;
+        if (fill[t] * 2 > kTileFill) continue;
         todo.clear();
         for (const int32_t i : cells[t])
             for (int32_t k = off[i]; k < off[i + 1]; ++k) {
@@ -339,9 +348,9 @@ int32_t merge_cells(const std::vector<unsigned int> &size, const std::vector<uin
             }
         int32_t best = -1;
         for (const int32_t x : todo)
-            if (fill[x] + fill[t] <= kTileVerts && (best < 0 || links[x] > links[best])) best = x;
+            if (fill[x] + fill[t] <= kTileFill && (best < 0 || links[x] > links[best])) best = x;
         for (const int32_t x : todo) links[x] = 0;
-        if (best < 0 && spare >= 0 && spare != t && fill[spare] > 0 && fill[spare] + fill[t] <= kTileVerts) best = spare;
+        if (best < 0 && spare >= 0 && spare != t && fill[spare] > 0 && fill[spare] + fill[t] <= kTileFill) best = spare;
         if (best < 0) {
             spare = t;
             continue;
@@ -395,7 +404,7 @@ hipError_t tile_build(TileSet *out, int32_t n, int32_t m, const int32_t *ro, con
     if (m < 1 || (slots == 8 && over8 * 50 > m)) return hipSuccess;
     const dim3 grid((unsigned)(((int64_t)n + 255) / 256)), blk(256);
     Temp tmp{st, {}};
-    const int32_t s = cell_verts(n), cells = n <= kTileVerts ? 1 : (int32_t)(((int64_t)n + s - 1) / s);
+    const int32_t s = cell_verts(n), cells = n <= kTileFill ? 1 : (int32_t)(((int64_t)n + s - 1) / s);
     int32_t *la = nullptr, *lb = nullptr, *cursor = nullptr;
     unsigned int *cnt = nullptr, *size = nullptr;
     uint2 *pairs = nullptr;
@@ -406,7 +415,7 @@ hipError_t tile_build(TileSet *out, int32_t n, int32_t m, const int32_t *ro, con
     std::vector<unsigned int> hsize((size_t)cells * 2, 0u);
     std::vector<int32_t> tile_of, hcur((size_t)cells * 2, 0);
     int32_t nt = 1;
-    if (n <= kTileVerts) {
+    if (n <= kTileFill) {
         TRY(hipMemsetAsync(la, 0, sizeof(int32_t) * (size_t)n, st));
         hsize[0] = (unsigned)n;
     } else {
@@ -434,9 +443,10 @@ hipError_t tile_build(TileSet *out, int32_t n, int32_t m, const int32_t *ro, con
         TRY(hipMemcpyAsync(hc, cnt, sizeof hc, hipMemcpyDeviceToHost, st));
         TRY(hipMemcpyAsync(hsize.data(), size, sizeof(unsigned int) * hsize.size(), hipMemcpyDeviceToHost, st));
         TRY(hipStreamSynchronize(st));
-        // cells of a mesh lose a tenth to a third of their arcs; a graph
-        // without locality loses nearly all
-        if ((int64_t)hc[0] * 5 > (int64_t)m * 2) return hipSuccess;
+        // cells of a mesh lose a tenth to a third of their arcs; those of a
+        // random graph are trees, which hold half of four arcs per vertex and
+        // less of more
+        if ((int64_t)hc[0] * 20 > (int64_t)m * 9) return hipSuccess;
         std::vector<uint2> hp(std::min<unsigned int>(hc[32], (unsigned)kMaxPairs));
         if (!hp.empty()) {
             TRY(hipMemcpyAsync(hp.data(), pairs, sizeof(uint2) * hp.size(), hipMemcpyDeviceToHost, st));
@@ -457,10 +467,9 @@ hipError_t tile_build(TileSet *out, int32_t n, int32_t m, const int32_t *ro, con
     const size_t b_pos = al256(sizeof(int32_t) * (size_t)n), b_vid = sizeof(int32_t) * places,
                  b_w = sizeof(uint32_t) * places * slots, b_h = b_w / 2,
                  b_off = al256(sizeof(int32_t) * ((size_t)nt + 1));
-    const size_t b_ext = sizeof(uint4) * ((size_t)m / 5 + 1);
-    const size_t b_at = sizeof(int32_t) * (std::min((size_t)m / 5, (size_t)n) + 1);  // a border vertex has an arc of ext
+    const size_t b_ext = sizeof(uint4) * ((size_t)m / 5 + 1), b_in = sizeof(uint2) * ((size_t)m / 5 + 1);
     void *base = nullptr;
-    TRY(hipMalloc(&base, b_pos + b_vid + b_w + b_h + 2 * b_off + b_ext + b_at));
+    TRY(hipMalloc(&base, b_pos + b_vid + b_w + b_h + 2 * b_off + b_ext + b_in));
     struct Guard {
         void *p;
         ~Guard() {
@@ -470,7 +479,7 @@ hipError_t tile_build(TileSet *out, int32_t n, int32_t m, const int32_t *ro, con
     TileSet ts;
     char *p = static_cast<char *>(base);
     ts.base = base;
-    ts.bytes = b_pos + b_vid + b_w + b_h + 2 * b_off + b_ext + b_at;
+    ts.bytes = b_pos + b_vid + b_w + b_h + 2 * b_off + b_ext + b_in;
     ts.n = n;
     ts.ntiles = nt;
     ts.slots = slots;
@@ -488,42 +497,39 @@ hipError_t tile_build(TileSet *out, int32_t n, int32_t m, const int32_t *ro, con
     p += b_off;
     ts.ext = reinterpret_cast<uint4 *>(p);
     p += b_ext;
-    ts.in_at = reinterpret_cast<int32_t *>(p);
-    uint8_t *border = nullptr;
+    ts.in = reinterpret_cast<uint2 *>(p);
     int32_t *nb = nullptr;
-    TRY(tmp.get(&border, n));
-    TRY(tmp.get(&nb, 2 * (size_t)nt));
+    TRY(tmp.get(&nb, 2 * (size_t)nt));  // arcs that leave each tile, and that enter it
     TRY(tmp.get(&cursor, 2 * (size_t)cells));
     TRY(hipMemcpyAsync(cursor, hcur.data(), sizeof(int32_t) * hcur.size(), hipMemcpyHostToDevice, st));
     TRY(hipMemsetAsync(ts.vid, 0xFF, b_vid, st));
-    TRY(hipMemsetAsync(border, 0, n, st));
+    TRY(hipMemsetAsync(nb, 0, sizeof(int32_t) * 2 * (size_t)nt, st));
     hipLaunchKernelGGL(k_tile_place, grid, blk, 0, st, n, la, cursor, ts.vid, ts.pos);
-    hipLaunchKernelGGL(k_tile_mark, grid, blk, 0, st, n, ro, adj, ts.pos, border);
     const dim3 tg((unsigned)nt), tb(kTileThreads);
     const uint32_t inf = wt == 1 ? kInfF32 : kInfU32;
     hipLaunchKernelGGL(k_tile_sort, tg, tb, 0, st, la, ts.vid, ts.pos);
-    hipLaunchKernelGGL(k_tile_border, tg, tb, 0, st, border, ts.vid, nb, nullptr, nullptr, nullptr);
     hipLaunchKernelGGL((k_tile_arcs<0>), tg, tb, 0, st, slots, inf, ro, adj, ts.pos, ts.vid, ts.w,
-                       reinterpret_cast<uint16_t *>(ts.head), nb + nt, nullptr, nullptr, nullptr);
+                       reinterpret_cast<uint16_t *>(ts.head), nb, nb + nt, nullptr, nullptr);
     TRY(hipGetLastError());
     std::vector<int32_t> hn(2 * (size_t)nt), ioff((size_t)nt + 1, 0), eoff((size_t)nt + 1, 0);
     TRY(hipMemcpyAsync(hn.data(), nb, sizeof(int32_t) * hn.size(), hipMemcpyDeviceToHost, st));
     TRY(hipStreamSynchronize(st));
     int64_t ext = 0;
     for (int32_t i = 0; i < nt; ++i) {
-        ioff[i + 1] = ioff[i] + hn[i];
-        ext += hn[(size_t)nt + i];
-        if (hn[(size_t)nt + i] > kTileMaxExt || hn[i] > kTileMaxBorder) return hipSuccess;
+        if (hn[i] > kTileMaxExt || hn[(size_t)nt + i] > kTileMaxExt) return hipSuccess;
+        ext += hn[i];
         if (ext > (int64_t)m / 5) return hipSuccess;
         eoff[i + 1] = (int32_t)ext;
+        ioff[i + 1] = ioff[i] + hn[(size_t)nt + i];
     }
-    ts.inbox = ioff[nt];
+    ts.mail = (int32_t)ext;
     TRY(hipMemcpyAsync(ts.ext_off, eoff.data(), sizeof(int32_t) * eoff.size(), hipMemcpyHostToDevice, st));
     TRY(hipMemcpyAsync(ts.in_off, ioff.data(), sizeof(int32_t) * ioff.size(), hipMemcpyHostToDevice, st));
-    int32_t *in_word = lb;  // the sweeps' second buffer: inbox word of each border vertex
-    hipLaunchKernelGGL(k_tile_border, tg, tb, 0, st, border, ts.vid, nb, ts.in_off, ts.in_at, in_word);
+    TRY(hipMemcpyAsync(nb, ts.in_off, sizeof(int32_t) * (size_t)nt, hipMemcpyDeviceToDevice, st));  // fill cursors
     hipLaunchKernelGGL((k_tile_arcs<1>), tg, tb, 0, st, slots, inf, ro, adj, ts.pos, ts.vid, nullptr, nullptr, nullptr,
-                       in_word, ts.ext_off, ts.ext);
+                       nullptr, ts.ext_off, ts.ext);
+    hipLaunchKernelGGL(k_tile_ext_sort, tg, tb, 0, st, ts.ext_off, ts.ext, nb, ts.in);
+    hipLaunchKernelGGL(k_tile_in_sort, tg, tb, 0, st, ts.in_off, ts.in);
     TRY(hipGetLastError());
     TRY(hipStreamSynchronize(st));
     guard.p = nullptr;

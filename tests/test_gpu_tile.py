@@ -48,8 +48,9 @@ SIX3D = [(0, 0, 1), (0, 1, 0), (1, 0, 0)]
 hub = [(2100, int(x)) for x in np.random.default_rng(1).integers(0, 9000, 40)]
 
 CASES = {
-    "one tile, exactly full": lambda: lattice((64, 64), FOUR, 1, 100, 1, gg.W_F32),
-    "one vertex past a tile": lambda: lattice((1, 4097), FOUR, 1, 100, 2, gg.W_F32),
+    "one tile, exactly full": lambda: lattice((64, 56), FOUR, 1, 100, 1, gg.W_F32),
+    "one vertex past a tile": lambda: lattice((1, 3585), FOUR, 1, 100, 2, gg.W_F32),
+    "a full square of places": lambda: lattice((64, 64), FOUR, 1, 100, 13, gg.W_F32),
     "two tiles, ragged": lambda: lattice((83, 79), FOUR, 1, 100, 3, gg.W_F32),
     "permuted ids": lambda: lattice((300, 211), FOUR, 1, 1000, 4, perm=True),
     "zero weights": lambda: lattice((150, 150), FOUR, 0, 2, 5),
@@ -112,3 +113,64 @@ def test_tiled_tuned():
         gr.gr_sssp(G.handle, 9, d)
         torch.cuda.synchronize()
         np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), oracle.dijkstra(g, 9))
+
+
+def test_tiled_bfs_and_batch():
+    g = lattice((300, 230), EIGHT, 1, 255, 21, perm=True)  # 69,000 vertices: breadth-first search too
+    srcs = [0, 68999, 5, 5, 31000]
+    with gr.Graph.from_csr(g) as G:
+        d = torch.empty(g.n, dtype=torch.int32, device="cuda")
+        st = gr.gr_bfs_ex(G.handle, 7, d)
+        torch.cuda.synchronize()
+        assert st["loop"] == gr.GR_LOOP_ASYNC
+        np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), oracle.bfs(g, 7))
+        rows = torch.full((len(srcs), g.n), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+        st = gr.gr_sssp_batch_ex(G.handle, srcs, rows)
+        torch.cuda.synchronize()
+        assert st["replays"] == 0 and st["rounds"] == 1
+        for s, row in zip(srcs, rows.cpu().numpy().view(np.uint32)):
+            np.testing.assert_array_equal(row, oracle.dijkstra(g, s))
+    g = gg.grid(90, wseed=8)
+    with gr.Graph.from_csr(g) as G:  # the most queries of one launch
+        srcs = gg.pick_sources(g, 5, 64)
+        rows = torch.full((64, g.n), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+        gr.gr_sssp_batch(G.handle, srcs, rows)
+        torch.cuda.synchronize()
+        for s, row in zip(srcs, rows.cpu().numpy().view(np.uint32)):
+            np.testing.assert_array_equal(row, oracle.dijkstra(g, int(s)))
+
+
+def test_tiled_multi_and_server():
+    # both slot counts and weight types over tiles, beside graphs that have none
+    graphs = [gg.grid(110, wseed=3), lattice((100, 90), EIGHT, 1, 9, 4), lattice((95, 101), FOUR, 1, 5, 5, gg.W_F32),
+              gg.rmat(11, 8, gseed=1, pseed=2, wseed=3), gg.grid(30, wseed=6),
+              lattice((2, 5000), FOUR, 1, 70000, 7, extra=[])]
+    Gs = [gr.Graph.from_csr(g) for g in graphs]
+    try:
+        qs = [(i % len(graphs), (977 * i) % graphs[i % len(graphs)].n) for i in range(30)]
+        want = [oracle.dijkstra(graphs[i], s) for i, s in qs]
+        outs = [torch.full((graphs[i].n,), 0x5A5A5A5A, dtype=torch.int32, device="cuda") for i, _ in qs]
+        st = gr.gr_sssp_multi([Gs[i].handle for i, _ in qs], [s for _, s in qs], outs)
+        torch.cuda.synchronize()
+        for (i, s), o, w in zip(qs, outs, want):
+            np.testing.assert_array_equal(o.cpu().numpy().view(np.uint32), w, err_msg=str((i, s)))
+        assert len(st["iterations"]) == len(qs) and max(st["iterations"]) <= st["rounds"]
+        for destroy_first in (False, True):  # queries still queued when the server goes are run first
+            outs = [torch.full((graphs[i].n,), 0x5A5A5A5A, dtype=torch.int32, device="cuda") for i, _ in qs]
+            torch.cuda.synchronize()
+            server = gr.gr_server_create(1 << 30)
+            ids = [gr.gr_server_add_graph(server, G.handle) for G in Gs]
+            tickets = [gr.gr_serve_submit(server, ids[i], s, o) for (i, s), o in zip(qs, outs)]
+            if not destroy_first:
+                for t, (i, s) in zip(tickets, qs):
+                    r = None
+                    while r is None:
+                        r = gr.gr_serve_poll(server, t)
+                    assert r["status"] == gr.GR_OK and r["src"] == s and r["batch_size"] >= 1
+            gr.gr_server_destroy(server)
+            torch.cuda.synchronize()
+            for (i, s), o, w in zip(qs, outs, want):
+                np.testing.assert_array_equal(o.cpu().numpy().view(np.uint32), w, err_msg=str((i, s)))
+    finally:
+        for G in Gs:
+            G.close()
