@@ -17,7 +17,9 @@ Prints ONE JSON line on stdout:
               (queue 4, offsets 8, dist 4, next-queue 4) -- divided by its
               launch time measured with HIP events on the query's stream (in
               a second pass over the same steps, outside the timed region),
-              against the 8 TB/s HBM3E peak.  The kernel is k_step (every
+              against the 8 TB/s HBM3E peak.  The kernel is k_order for the
+              weight-ordered loop (which reads few arcs and adds 20 B per
+              vertex and pull: distance and two lightest arcs), k_step (every
               phase of a round) for the queued loop, k_push (the advance)
               for the host-driven loop.  traffic: HBM bytes per launch from
               the committed rocprofv3 counter summary when it matches the
@@ -193,15 +195,15 @@ def main():
         s, st = run(args.warmup + i)
         edges += reached[s]
         iters += st["iterations"]
-        q_bytes += 12 * st["edges_pushed"] + 20 * st["push_frontier_sum"]
-        relax += st["edges_pushed"]
+        q_bytes += stat_bytes(st, g.n, g.m)
+        relax += relaxations(st, g.m)
         stats_last = st
     torch.cuda.synchronize()
     t_total = time.perf_counter() - t_start
     ms_per_step = 1e3 * t_total / args.steps
     gteps = edges / t_total / 1e9
     log("timed: %.3f ms/step, %.2f GTEPS, %d iterations/step, %.0f M relaxations/step" % (
-        ms_per_step, gteps, iters // args.steps, q_bytes / 12e6 / args.steps))
+        ms_per_step, gteps, iters // args.steps, relax / 1e6 / args.steps))
 
     # Kernel roofline: the same steps again, now with HIP events around every
     # advance launch on the query's stream (outside the timed region: the
@@ -214,7 +216,7 @@ def main():
     launches = 0
     for i in range(args.steps):
         s, st = run(args.warmup + i, timing=1)
-        alg_bytes += 12 * st["edges_pushed"] + 20 * st["push_frontier_sum"]
+        alg_bytes += stat_bytes(st, g.n, g.m)
         if st["loop"] == 3:
             push_us += st["push_us"] + st["filter_us"]
             launches += st["launches"]
@@ -225,7 +227,7 @@ def main():
     roof = None
     if launches and push_us > 0:
         achieved = alg_bytes / (push_us * 1e-6) / 1e9
-        kern = {2: "k_persistent", 3: "k_step", 4: "k_async", 5: "k_lds"}.get(stats_last["loop"], "k_push")
+        kern = kernel_name(stats_last, g.m)
         loop_name = {1: "host", 2: "persistent", 3: "queued", 4: "async", 5: "lds"}.get(stats_last["loop"], "?")
         layout_name = {1: "plain", 2: "partitioned"}.get(stats_last["layout"], "?")
         relax_name = {1: "dist", 2: "bound"}.get(stats_last["relax_filter"], "?")
@@ -365,13 +367,39 @@ def cpu_baseline(g, srcs, deg, inf, seconds):
             "single_thread_gteps": round(one_edges / one_s / 1e9, 5)}
 
 
-def kernel_roofline(stats_list, wall_s, q_bytes):
+def ordered(st, m):
+    """Whether a query ran the weight-ordered loop (queued launches whose pulls
+    read part of the arcs)."""
+    return st["loop"] == 3 and 0 < st["arcs_pulled"] < m * max(st["pull_iterations"], 1)
+
+
+def relaxations(st, m):
+    return st["edges_pushed"] + (st["arcs_pulled"] if ordered(st, m) else 0)
+
+
+def stat_bytes(st, n, m):
+    """Algorithmic bytes of a query: 12 B per arc relaxed and 20 B per frontier
+    vertex; a weight-ordered pull also streams 20 B per vertex (its distance and
+    its two lightest arcs)."""
+    b = 12 * relaxations(st, m) + 20 * st["push_frontier_sum"]
+    return b + (20 * n * st["pull_iterations"] if ordered(st, m) else 0)
+
+
+def kernel_name(st, m):
+    if ordered(st, m):
+        return "k_order"
+    if st["loop"] == 4 and st["launches"] == 2 and st["iterations"] == 1:
+        return "k_tile"  # the asynchronous loop over tiles (its init and itself)
+    return {2: "k_persistent", 3: "k_step", 4: "k_async", 5: "k_lds"}.get(st["loop"], "k_push")
+
+
+def kernel_roofline(stats_list, wall_s, q_bytes, n, m):
     """Kernel roofline from per-query statistics gathered with timing on: the
     algorithmic bytes of the advance rounds (12 B per relaxed edge + 20 B per
     frontier vertex) over the summed launch times of the dominant kernel."""
     push_us, alg, launches, last = 0.0, 0, 0, None
     for st in stats_list:
-        alg += 12 * st["edges_pushed"] + 20 * st["push_frontier_sum"]
+        alg += stat_bytes(st, n, m)
         if st["loop"] == 3:
             push_us += st["push_us"] + st["filter_us"]
             launches += st["launches"]
@@ -382,7 +410,7 @@ def kernel_roofline(stats_list, wall_s, q_bytes):
     if not launches or push_us <= 0:
         return None
     achieved = alg / (push_us * 1e-6) / 1e9
-    kern = {2: "k_persistent", 3: "k_step", 4: "k_async", 5: "k_lds"}.get(last["loop"], "k_push")
+    kern = kernel_name(last, m)
     roof = {"kernel": kern, "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "bytes_per_launch": int(alg / launches),
             "avg_launch_us": round(push_us / launches, 2), "launches": launches,
@@ -416,10 +444,10 @@ def measure_config(name, steps, torch, np, gr, gg, dev):
     stats = [gr.gr_sssp_ex(G.handle, s, dist) for _ in range(steps)]
     torch.cuda.synchronize()
     wall = time.perf_counter() - t1
-    q_bytes = sum(12 * x["edges_pushed"] + 20 * x["push_frontier_sum"] for x in stats)
+    q_bytes = sum(stat_bytes(x, g.n, g.m) for x in stats)
     timed = [gr.gr_sssp_ex(G.handle, s, dist, timing=1) for _ in range(min(steps, 5))]
     torch.cuda.synchronize()
-    roof = kernel_roofline(timed, wall, q_bytes)
+    roof = kernel_roofline(timed, wall, q_bytes, g.n, g.m)
     last = stats[-1]
     batch = None
     if last["loop"] == 5:
@@ -451,8 +479,8 @@ def measure_config(name, steps, torch, np, gr, gg, dev):
             "loop": {1: "host", 2: "persistent", 3: "queued", 4: "async", 5: "lds"}.get(last["loop"], "?"),
             "ms_per_query": round(1e3 * wall / steps, 4), "queries": steps,
             "gteps": round(reached * steps / wall / 1e9, 4),
-            "rounds": last["iterations"], "relaxations": last["edges_pushed"],
-            "relaxation_inflation": round(last["edges_pushed"] / max(reached, 1), 3),
+            "rounds": last["iterations"], "relaxations": relaxations(last, g.m),
+            "relaxation_inflation": round(relaxations(last, g.m) / max(reached, 1), 3),
             "roofline": roof, "batch64": batch, "setup_s": round(gen_s, 1)}
 
 

@@ -159,7 +159,10 @@ typedef enum {
                                that fit it (GR_LOOP_LDS), the asynchronous loop over tiles
                                for graphs that have them (see below) and requests that set
                                nothing but push, timing or barrier_timeout_us, the
-                               asynchronous loop for other
+                               weight-ordered loop (see GR_LOOP_QUEUED) for graphs of
+                               n > 65,536 or maximum out-degree > 64 that have no tiles
+                               and allow pull, and requests that set nothing but timing,
+                               the asynchronous loop for other
                                graphs of maximum out-degree <= 64 and n <= 65,536 (the
                                queued loop when the request needs pull or a near-far
                                split), the host-driven loop for graphs of maximum
@@ -167,7 +170,14 @@ typedef enum {
     GR_LOOP_HOST = 1,       /* one launch per operator, host reads the frontier size */
     GR_LOOP_PERSISTENT = 2, /* one cooperative launch, device-side grid barrier */
     GR_LOOP_QUEUED = 3,     /* launches enqueued ahead in chunks; each reads the frontier
-                               size from device memory; the host checks once per chunk */
+                               size from device memory; the host checks once per chunk.
+                               Weight-ordered (only AUTO picks it; stats report this
+                               mode): the graph holds a copy of its in-arcs sorted by
+                               weight within each row (8 m + 20 n bytes); a round pushes
+                               a small frontier, else pulls, reading a vertex's arcs in
+                               order of weight while they can still improve it.  Extra
+                               workspace: about 5 bytes per vertex.  stats: arcs_pulled
+                               counts the arcs read. */
     GR_LOOP_ASYNC = 4,      /* asynchronous (Section III-A without the per-advance barrier,
                                III-B frontier as a message queue): one persistent kernel
                                drains a device worklist of improved vertices; no rounds.

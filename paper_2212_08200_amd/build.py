@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgr.so")
 SOURCES = ["gr_api.cpp", "gr_kernels.hip", "gr_async.hip", "gr_multi.hip", "gr_noalloc.hip", "gr_lds.hip",
-           "gr_tile.hip", "gr_tile_build.hip"]
+           "gr_tile.hip", "gr_tile_build.hip", "gr_order.hip"]
 ARCH = os.environ.get("GR_OFFLOAD_ARCH", "gfx950")
 
 HIPCC_FLAGS = [

@@ -27,6 +27,7 @@
 #include "gr_lds.h"
 #include "gr_multi.h"
 #include "gr_noalloc.h"
+#include "gr_order.h"
 #include "gr_sched.h"
 #include "gr_tile.h"
 
@@ -80,6 +81,8 @@ extern "C" const char *gr_version(void) { return "gr 0.1 (gfx950)"; }
 
 // ---------------------------------------------------------------------------
 // device properties and the stream-ordered pool
+
+static inline size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct DeviceInfo {
     int num_cu = 0;
@@ -186,6 +189,11 @@ struct gr_graph {
     // otherwise), and whether AUTO's weighted queries run over it
     TileSet tiles;
     bool auto_tiled = false;
+    // in-arcs by weight (the other graphs, unless they fit one workgroup's LDS
+    // or pull is off), and whether AUTO's weighted queries run over them
+    OrderSet order;
+    bool auto_order = false;
+    mutable std::atomic<int32_t> order_rounds{12};  // rounds of the last such query
     // iterations of the last completed queued-loop query (first chunk size)
     mutable std::atomic<int32_t> last_iters{0};
     double locality = 1.0;  // fraction of arcs with |u - v| < locality_span(n)
@@ -220,6 +228,7 @@ static void graph_free(gr_graph *g) {
     if (g->d_adj) (void)hipFree(g->d_adj);
     if (g->d_ell) (void)hipFree(g->d_ell);
     if (g->tiles.base) (void)hipFree(g->tiles.base);
+    if (g->order.base) (void)hipFree(g->order.base);
     if (g->d_pro) (void)hipFree(g->d_pro);
     if (g->d_padj) (void)hipFree(g->d_padj);
     for (int i = 0; i < 2; ++i) {
@@ -467,6 +476,23 @@ static gr_status graph_build(gr_graph *g, int32_t n, int32_t m, const int32_t *r
         BUILD_TRY(tile_build(&g->tiles, n, m, g->d_ro, g->d_adj, (int)wt, over4, over8, st), "tiles");
         g->auto_tiled = g->tiles.ntiles > 0;
         g->dev_bytes += g->tiles.bytes;
+    }
+    // In-arcs by weight: the graphs that have no better loop (small bounded-
+    // degree ones keep the asynchronous loop: uniform graphs of 5,000 and
+    // 30,000 vertices 0.28 and 0.35 ms against 0.33 and 0.40; 300,000: 1.5
+    // queued against 0.97).
+    if (g->auto_loop != GR_LOOP_LDS && g->auto_loop != GR_LOOP_ASYNC && !g->auto_tiled && g->pull && m > 0) {
+        std::vector<int32_t> in;
+        if (g->csc_separate) {
+            in.resize((size_t)n + 1);
+            BUILD_TRY(hipMemcpyAsync(in.data(), g->d_ro_in, sizeof(int32_t) * in.size(), hipMemcpyDeviceToHost, st),
+                      "copy in-offsets");
+            BUILD_TRY(hipStreamSynchronize(st), "copy in-offsets");
+        }
+        BUILD_TRY(order_build(&g->order, n, m, g->d_ro_in, g->d_adj_in, g->csc_separate ? in.data() : g->h_ro.data(),
+                              (int)wt, st), "in-arcs by weight");
+        g->auto_order = true;
+        g->dev_bytes += g->order.bytes;
     }
 
     const bool want_part = !(flags & GR_NO_PARTITION) &&
@@ -1164,6 +1190,119 @@ static gr_status run_tile_group(const gr_graph *const *graphs, const int32_t *sr
 // rounds that the tiled loop, which has none, reports.
 static int32_t tile_rounds(const gr_graph *g, int32_t src) { return g->h_ro[src + 1] > g->h_ro[src] ? 1 : 0; }
 
+// Weight-ordered loop (gr_order.hip): k queries, rows[i] receiving query i's
+// distances; every launch is a round of all of them.  The first chunk of
+// launches is as long as the graphs' last queries, the host then reads the
+// pinned statistics.
+static_assert(kOrderMaxJobs * kOrderStatWords * 8 <= 8192, "the statistics fit the pinned slot");
+static gr_status run_order(const gr_graph *const *graphs, const int32_t *srcs, int32_t k, uint32_t *const *rows,
+                           int wt, hipStream_t st, const unsigned long long **stat_out, int64_t *launches, double *us) {
+    unsigned long long *hp = pinned_slot();
+    if (!hp) return fail(GR_ERR_OUT_OF_MEMORY, "pinned host buffer");
+    OrderJob jobs[kOrderMaxJobs];
+    size_t bytes = al256(sizeof(OrderJob) * kOrderMaxJobs), off[kOrderMaxJobs];
+    int64_t chunk = 1, cap = 1;
+    for (int32_t i = 0; i < k; ++i) {
+        off[i] = bytes;
+        bytes += order_ws_bytes(graphs[i]->plain.n);
+        chunk = std::max<int64_t>(chunk, (int64_t)graphs[i]->order_rounds.load(std::memory_order_relaxed) + 1);
+        cap = std::max<int64_t>(cap, (int64_t)graphs[i]->plain.n + 2);
+    }
+    void *ws = nullptr;
+    HIP_TRY(hipMallocAsync(&ws, bytes, st));
+    for (int32_t i = 0; i < k; ++i) {
+        const gr_graph *g = graphs[i];
+        OrderJob &j = jobs[i];
+        j = OrderJob{};
+        j.ro = g->d_ro;
+        j.adj = g->d_adj;
+        j.ro_in = g->d_ro_in;
+        j.arc = g->order.arc;
+        j.a0 = g->order.a0;
+        j.a1 = g->order.a1;
+        j.w2 = g->order.w2;
+        j.chunk = g->order.chunk;
+        j.nchunks = g->order.nchunks;
+        j.dist = rows[i];
+        j.n = g->plain.n;
+        j.m = g->plain.m;
+        j.src = srcs[i];
+        order_carve(&j, static_cast<char *>(ws) + off[i]);
+    }
+    for (int i = 0; i < k * kOrderStatWords; ++i) hp[i] = 0ull;
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    const bool timed = us && hipEventCreate(&ev[0]) == hipSuccess && hipEventCreate(&ev[1]) == hipSuccess;
+    OrderJob *table = static_cast<OrderJob *>(ws);
+    hipError_t e = order_begin(jobs, k, wt, table, st);
+    if (timed) (void)hipEventRecord(ev[0], st);
+    int64_t done = 0;
+    bool over = false;
+    while (e == hipSuccess) {
+        const int32_t c = (int32_t)std::min<int64_t>(chunk, 64);
+        e = order_rounds(jobs, k, wt, table, done, c, hp, st);
+        done += c;
+        if (timed) (void)hipEventRecord(ev[1], st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        bool all = true;
+        for (int32_t i = 0; i < k; ++i) all = all && hp[i * kOrderStatWords] != 0ull;
+        over = !all && done > cap;
+        if (all || over) break;
+        chunk = done > 64 ? 32 : 4;
+    }
+    if (timed && e == hipSuccess) {
+        float ms = 0.f;
+        (void)hipEventElapsedTime(&ms, ev[0], ev[1]);
+        *us = 1e3 * ms;
+    }
+    for (auto &x : ev)
+        if (x) (void)hipEventDestroy(x);
+    const hipError_t e2 = hipFreeAsync(ws, st);
+    if (e != hipSuccess) return hip_fail(e, "weight-ordered loop");
+    if (e2 != hipSuccess) return hip_fail(e2, "hipFreeAsync");
+    if (over) return fail(GR_ERR_ITER_LIMIT, "a query ran past n + 1 rounds");
+    for (int32_t i = 0; i < k; ++i)
+        graphs[i]->order_rounds.store((int32_t)std::min<unsigned long long>(hp[i * kOrderStatWords + 1], 512),
+                                      std::memory_order_relaxed);
+    *stat_out = hp;
+    *launches = done;
+    return GR_OK;
+}
+
+static gr_status run_ordered(const gr_graph *g, int32_t src, uint32_t *dist, hipStream_t st, const RunCfg &rc,
+                             gr_sssp_stats *stats) {
+    const unsigned long long *x = nullptr;
+    int64_t launches = 0;
+    double us = 0;
+    gr_status s = run_order(&g, &src, 1, &dist, rc.dg->wt == 2 ? 2 : g->plain.wt, st, &x, &launches,
+                            rc.timing ? &us : nullptr);
+    if (s != GR_OK) return s;
+    if (stats) {
+        gr_sssp_stats local{};
+        local.loop = GR_LOOP_QUEUED;
+        local.layout = GR_LAYOUT_PLAIN;
+        local.relax_filter = GR_RELAX_DIST;
+        local.iterations = (int32_t)x[1];
+        local.pull_iterations = (int32_t)x[2];
+        local.frontier_sum = local.push_frontier_sum = (int64_t)x[3];
+        local.edges_pushed = (int64_t)x[4];
+        local.arcs_pulled = (int64_t)x[5];
+        local.push_launches = (int32_t)(x[1] - x[2]);
+        local.launches = (int32_t)std::min<int64_t>(launches + 1, INT32_MAX);
+        local.push_us = us;  // both directions share the kernel
+        *stats = local;
+    }
+    return GR_OK;
+}
+
+// Whether AUTO runs over the in-arcs by weight: as wants_tiles, and the
+// direction left open.
+static bool wants_order(const gr_graph *g, const gr_sssp_opts *o) {
+    if (!g->auto_order) return false;
+    return !o || (o->loop == GR_LOOP_AUTO && o->direction == GR_DIR_AUTO && o->alpha_x16 <= 0 && o->beta <= 0 &&
+                  o->max_iters <= 0 && o->layout == GR_LAYOUT_AUTO && o->filter == 0 &&
+                  (o->delta == 0 || o->delta == GR_DELTA_OFF) && o->relax_filter == 0 && o->local_hops == 0);
+}
+
 // Whether AUTO runs over the graph's tiles: weighted queries with nothing of
 // the round-based schedules asked for.
 static bool wants_tiles(const gr_graph *g, const gr_sssp_opts *o) {
@@ -1270,6 +1409,8 @@ extern "C" gr_status gr_sssp_ex(const gr_graph *g, int32_t src, void *dist_out, 
     if (s != GR_OK) return s;
     if (wants_tiles(g, opts))
         return run_tiled(g, src, static_cast<uint32_t *>(dist_out), static_cast<hipStream_t>(stream), rc, stats);
+    if (wants_order(g, opts))
+        return run_ordered(g, src, static_cast<uint32_t *>(dist_out), static_cast<hipStream_t>(stream), rc, stats);
     int loop = rc.loop;
     if (loop == GR_LOOP_AUTO) {
         loop = g->auto_loop;
@@ -1438,6 +1579,7 @@ static gr_status run_single_auto(const gr_graph *g, int32_t src, uint32_t *dist,
     const int loop = g->auto_loop;
     gr_sssp_stats one{};
     if (wants_tiles(g, nullptr)) s = run_tiled(g, src, dist, st, rc, &one);
+    else if (wants_order(g, nullptr)) s = run_ordered(g, src, dist, st, rc, &one);
     else if (loop == GR_LOOP_ASYNC) s = run_async(g, src, dist, st, rc, &one);
     else if (loop == GR_LOOP_LDS) s = run_lds(g, src, dist, st, rc, &one);
     else if (loop == GR_LOOP_QUEUED) s = run_queued(g, src, dist, st, rc, &one);
@@ -1456,8 +1598,6 @@ static gr_status run_single_auto(const gr_graph *g, int32_t src, uint32_t *dist,
 // ---------------------------------------------------------------------------
 // multi-query sessions (gr_multi.h): one-shot gr_sssp_multi calls and the
 // query server's executors
-
-static inline size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Multi-query rounds whose queue holds fewer than kMqNarrowArcs arcs replay a
 // capture on kMqNarrowGrid blocks per launch.
@@ -2396,7 +2536,9 @@ static std::string graph_signature(const gr_graph *g) {
     return buf;
 }
 
-static bool cache_lookup(const std::string &sig, gr_tune_result *r) {
+// own: the line says that AUTO's own loop won (lines of earlier versions do not
+// have the field: the loop they name runs, as it did).
+static bool cache_lookup(const std::string &sig, gr_tune_result *r, bool *own) {
     const char *path = getenv("GR_TUNE_CACHE");
     if (!path || !*path) return false;
     FILE *f = fopen(path, "r");
@@ -2409,11 +2551,13 @@ static bool cache_lookup(const std::string &sig, gr_tune_result *r) {
         unsigned dl;
         int sm, rf, ab, lh;
         double ms;
+        int ow = 0;
         if (sscanf(line, "{\"sig\": \"%299[^\"]\", \"layout\": %d, \"loop\": %d, \"dense_ratio\": %d, \"alpha_x16\": %d, "
                          "\"delta\": %u, \"small\": %d, \"relax_filter\": %d, \"async_blocks\": %d, "
-                         "\"local_hops\": %d, \"best_ms\": %lf}",
-                   s, &lay, &loop, &dr, &al, &dl, &sm, &rf, &ab, &lh, &ms) == 11 &&
+                         "\"local_hops\": %d, \"best_ms\": %lf, \"own\": %d}",
+                   s, &lay, &loop, &dr, &al, &dl, &sm, &rf, &ab, &lh, &ms, &ow) >= 11 &&
             sig == s) {
+            *own = ow != 0;
             r->layout = lay;
             r->loop = loop;
             r->dense_ratio = dr;
@@ -2431,16 +2575,16 @@ static bool cache_lookup(const std::string &sig, gr_tune_result *r) {
     return found;
 }
 
-static void cache_store(const std::string &sig, const gr_tune_result &r) {
+static void cache_store(const std::string &sig, const gr_tune_result &r, bool own) {
     const char *path = getenv("GR_TUNE_CACHE");
     if (!path || !*path) return;
     FILE *f = fopen(path, "a");
     if (!f) return;
     fprintf(f, "{\"sig\": \"%s\", \"layout\": %d, \"loop\": %d, \"dense_ratio\": %d, \"alpha_x16\": %d, "
                "\"delta\": %u, \"small\": %d, \"relax_filter\": %d, \"async_blocks\": %d, \"local_hops\": %d, "
-               "\"best_ms\": %.6f}\n",
+               "\"best_ms\": %.6f, \"own\": %d}\n",
             sig.c_str(), r.layout, r.loop, r.dense_ratio, r.alpha_x16, r.delta, r.small, r.relax_filter, r.async_blocks,
-            r.local_hops, r.best_ms);
+            r.local_hops, r.best_ms, own ? 1 : 0);
     fclose(f);
 }
 
@@ -2451,8 +2595,14 @@ struct TuneCfg {
     int32_t relax;
     int32_t async_blocks;  // 0: the default
     int32_t local_hops;
-    bool tiled;  // the asynchronous loop over the graph's tiles (the other fields do not apply)
+    bool own;  // AUTO's own loop over tiles or weight-ordered arcs (the other fields do not apply)
 };
+
+static bool has_own(const gr_graph *g) { return g->tiles.ntiles > 0 || g->order.base != nullptr; }
+static void set_own(gr_graph *g, bool own) {
+    g->auto_tiled = own && g->tiles.ntiles > 0;
+    g->auto_order = own && g->order.base != nullptr;
+}
 
 static void apply_auto(gr_graph *g, const TuneCfg &c) {
     g->auto_layout = c.layout;
@@ -2464,7 +2614,7 @@ static void apply_auto(gr_graph *g, const TuneCfg &c) {
     g->auto_relax = c.relax;
     g->auto_async_blocks = c.async_blocks;
     g->auto_local_hops = c.local_hops;
-    g->auto_tiled = c.tiled && g->tiles.ntiles > 0;
+    set_own(g, c.own);
 }
 
 // Near-far split widths to try: multiples of the mean weight of a sample of
@@ -2513,16 +2663,16 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
             return fail(GR_ERR_SOURCE_RANGE, "srcs[%d] = %d outside [0, %d)", i, srcs[i], g->plain.n);
     gr_tune_result r{};
     const std::string sig = graph_signature(g);
-    if (cache_lookup(sig, &r)) {
+    bool own = false;
+    if (cache_lookup(sig, &r, &own)) {
         if (r.layout == GR_LAYOUT_PARTITIONED && !g->has_part) r.layout = GR_LAYOUT_PLAIN;
         if (r.alpha_x16 > 0 && !g->pull) r.alpha_x16 = 0;
         if (r.delta) r.alpha_x16 = 0;
         if (r.relax_filter != GR_RELAX_BOUND) r.relax_filter = GR_RELAX_DIST;
         if (r.async_blocks < 0 || r.async_blocks > 65536) r.async_blocks = 0;
         if (r.local_hops < 1 || r.local_hops > 64) r.local_hops = kDefaultLocalHops;
-        // (the asynchronous loop with no block count of its own: over the tiles, where the graph has them)
         apply_auto(g, TuneCfg{r.layout, r.loop, r.dense_ratio, r.alpha_x16, r.delta, r.small, r.relax_filter,
-                              r.async_blocks, r.local_hops, r.loop == GR_LOOP_ASYNC && r.async_blocks == 0});
+                              r.async_blocks, r.local_hops, own});
         r.from_cache = 1;
         if (out) *out = r;
         return GR_OK;
@@ -2544,8 +2694,8 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
         o.relax_filter = c.relax;
         o.local_hops = c.local_hops;
         const int32_t saved = g->auto_dense_ratio, saved_ab = g->auto_async_blocks;
-        const bool saved_tiled = g->auto_tiled;
-        g->auto_tiled = c.tiled;
+        const bool saved_own = g->auto_tiled || g->auto_order;
+        set_own(g, c.own);
         g->auto_dense_ratio = c.dense_ratio;
         g->auto_async_blocks = c.async_blocks;
         std::vector<double> t;
@@ -2553,7 +2703,7 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
         for (int32_t rep = 0; rep <= reps && s == GR_OK; ++rep) {
             for (int32_t i = 0; i < nsrcs && s == GR_OK; ++i) {
                 const auto t0 = std::chrono::steady_clock::now();
-                s = gr_sssp_ex(g, srcs[i], dist, st, c.tiled ? nullptr : &o, nullptr);
+                s = gr_sssp_ex(g, srcs[i], dist, st, c.own ? nullptr : &o, nullptr);
                 if (s == GR_OK && hipStreamSynchronize(st) != hipSuccess) s = fail(GR_ERR_HIP, "tuning query");
                 const double d = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0)
                                      .count();
@@ -2562,7 +2712,7 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
         }
         g->auto_dense_ratio = saved;
         g->auto_async_blocks = saved_ab;
-        g->auto_tiled = saved_tiled;
+        set_own(g, saved_own);
         ++trials;
         if (s != GR_OK) return s;
         std::sort(t.begin(), t.end());
@@ -2570,13 +2720,14 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
         return GR_OK;
     };
     TuneCfg best{g->auto_layout, g->auto_loop, g->auto_dense_ratio, g->auto_alpha_x16, g->auto_delta,
-                 g->auto_small ? 1 : 0, g->auto_relax, g->auto_async_blocks, g->auto_local_hops, g->auto_tiled};
+                 g->auto_small ? 1 : 0, g->auto_relax, g->auto_async_blocks, g->auto_local_hops,
+                 g->auto_tiled || g->auto_order};
     double best_ms = 0;
     status = measure(best, &best_ms);
     const double default_ms = best_ms;
-    if (status == GR_OK && g->tiles.ntiles > 0 && !best.tiled) {
+    if (status == GR_OK && has_own(g) && !best.own) {
         TuneCfg c = best;
-        c.tiled = true;
+        c.own = true;
         double ms = 0;
         status = measure(c, &ms);
         if (status == GR_OK && ms < best_ms) {
@@ -2613,9 +2764,9 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
         for (int32_t v : kv.second) {
             if (status != GR_OK) break;
             TuneCfg c = best;
-            if (c.tiled) {
-                if (kv.first != 1) continue;  // only another loop can replace the tiles
-                c.tiled = false;
+            if (c.own) {
+                if (kv.first != 1) continue;  // only another loop can replace it
+                c.own = false;
                 c.loop = -1;
             }
             if (c.loop == GR_LOOP_ASYNC && kv.first != 1 && kv.first != 7) continue;  // the others do not apply
@@ -2657,11 +2808,12 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
     (void)hipStreamSynchronize(st);
     if (status != GR_OK) return status;
     apply_auto(g, best);
-    r.layout = best.layout;
-    if (best.tiled) {
-        best.loop = GR_LOOP_ASYNC;
+    if (best.own) {  // as its statistics name it
+        best.loop = g->tiles.ntiles > 0 ? GR_LOOP_ASYNC : GR_LOOP_QUEUED;
+        best.layout = GR_LAYOUT_PLAIN;
         best.async_blocks = 0;
     }
+    r.layout = best.layout;
     r.loop = best.loop;
     r.dense_ratio = best.dense_ratio;
     r.alpha_x16 = best.alpha_x16;
@@ -2673,7 +2825,7 @@ extern "C" gr_status gr_graph_tune(gr_graph *g, const int32_t *srcs, int32_t nsr
     r.best_ms = best_ms;
     r.default_ms = default_ms;
     r.trials = trials;
-    cache_store(sig, r);
+    cache_store(sig, r, best.own);
     if (out) *out = r;
     return GR_OK;
 }

@@ -1,0 +1,635 @@
+// Weight-ordered loop (the paper's push / pull operators, Section III-C, with
+// the pull's arcs ordered by weight).
+//
+// On graphs without locality a push relaxes every arc of the frontier, three
+// to five times over the query (R-MAT 20: 166 M relaxations for 31 M arcs),
+// each a random access and some a memory-side atomic.  Nearly all are lost: the
+// hubs' distances lie within a few light weights of each other, so a vertex is
+// improved through its lightest arcs or not at all.  Here a round pulls: with mu
+// the smallest distance that the round before improved, an arc (u, v, w) can
+// only improve v if mu (+) w < dist[v], so v's arcs are read in order of weight
+// until that fails -- one or two arcs per vertex and round (R-MAT 20: 15 M arcs
+// read in 18 rounds).  (+) is monotone in both operands, so what is not read
+// could not have improved v: mu (+) w <= dist[u] (+) w for every u that the
+// round before improved, and a u improved earlier was read then or was ruled
+// out then.  Of the arcs read, only those whose tail's bit is set need its
+// distance.
+//
+// A pull round reads every vertex's distance and lightest weight (streamed),
+// so small frontiers are pushed instead, from a queue of (vertex, run of 256
+// arcs) entries: a round pushes while its frontier is small (kOrderBias) and
+// the queue held it, and once a round has pulled all later ones do (a pull
+// writes no queue: its frontier exists as a bitmap only).
+//
+// One launch is one round of every query in it; the launches of a query are
+// enqueued ahead, each reads the state that the round before left, and those
+// past the end return at once.  State: three slots of counters rotated over the
+// rounds, each in kOrderRegions regions on 256-byte lines of their own (memory-
+// side atomics to one line are serialised: a block adds to region blockIdx mod
+// kOrderRegions), summed by every block at its start; three bitmaps, rotated
+// likewise (one read, one written, one cleared per round).
+#include "gr_order.h"
+
+#include <algorithm>
+#include <vector>
+
+#include "gr_device.h"
+
+namespace gr {
+
+namespace {
+
+// A first pull reads each vertex's arcs until one comes from the frontier,
+// about m / E of them (E: the frontier's arcs), so n m / E in all, against E
+// for a push: pull when kOrderBias E^2 >= n m.
+#ifndef BIAS
+#define BIAS 4.0
+#endif
+constexpr double kOrderBias = BIAS;
+constexpr int kOrderVerts = 512;     // vertices per block of a pull, two per thread
+constexpr int kPushRun = 256;        // arcs per queue entry
+
+// Counters of a region, as words: frontier vertices, their arcs, the complement
+// of mu (a maximum: a cleared word is neutral), queue entries, flags, and the
+// arcs that the round before read.
+constexpr int kRgF = 0, kRgE = 1, kRgMu = 2, kRgCnt = 3, kRgFlags = 4, kRgRead = 5;
+constexpr unsigned long long kFlagOver = 1ull, kFlagPulled = 2ull;  // the queue overflowed; the round before pulled
+// State words after the slots (block 0 of each launch keeps them).
+constexpr int kStDone = 0, kStPulls = 2, kStF = 3, kStPushed = 4, kStPulledArcs = 5;
+
+template <typename T>
+using gptr = T __attribute__((address_space(1))) *;
+template <typename T>
+__device__ __forceinline__ gptr<T> to_global(T *p) {
+    return (gptr<T>)p;
+}
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+struct OrderArgs {
+    const OrderJob *job;
+    int64_t round;
+    unsigned long long *stat;
+};
+
+__device__ __forceinline__ uint32_t ld_dev(gptr<uint32_t> p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Totals of a slot (every lane of every wave gets them).
+struct Totals {
+    unsigned long long F, E, flags;
+    uint32_t mu;
+};
+__device__ __forceinline__ Totals read_slot(gptr<const unsigned long long> s) {
+    gptr<const unsigned long long> r = s + (threadIdx.x % kOrderRegions) * kOrderRegionWords;
+    unsigned long long F = r[kRgF], E = r[kRgE], o = r[kRgFlags];
+    uint32_t mu = ~(uint32_t)r[kRgMu];
+#pragma unroll
+    for (int k = kOrderRegions / 2; k > 0; k >>= 1) {
+        F += __shfl_xor(F, k, 64);
+        E += __shfl_xor(E, k, 64);
+        o |= __shfl_xor(o, k, 64);
+        mu = min(mu, (uint32_t)__shfl_xor((int)mu, k, 64));
+    }
+    return Totals{F, E, o, mu};
+}
+
+constexpr int kBeginJobs = 16;
+struct BeginArgs {
+    OrderJob job[kBeginJobs];
+    OrderJob *table;
+    uint32_t inf;
+};
+
+__global__ __launch_bounds__(256) void k_order_begin(BeginArgs a) {
+    const OrderJob j = a.job[blockIdx.y];
+    const int32_t t = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+    for (int64_t i = t; i < j.n; i += step) j.dist[i] = i == j.src ? 0u : a.inf;
+    for (int64_t i = t; i < 3 * (int64_t)j.nword; i += step)
+        j.bits[i] = i == (j.src >> 6) ? 1ull << (j.src & 63) : 0ull;
+    const int32_t deg = j.ro[j.src + 1] - j.ro[j.src], runs = (deg + kPushRun - 1) / kPushRun;
+    // round 0's counters (region 0); mu = 0, complemented
+    const bool fits = runs <= j.cap;
+    for (int32_t i = t; i < kOrderCtlWords; i += step)
+        j.ctl[i] = i == kRgF ? (deg > 0 ? 1ull : 0ull)
+                   : i == kRgE ? (unsigned long long)deg
+                   : i == kRgMu ? 0xFFFFFFFFull
+                   : i == kRgCnt ? (unsigned long long)(fits ? runs : 0)
+                   : i == kRgFlags ? (fits ? 0ull : kFlagOver)
+                                  : 0ull;
+    if (fits)
+        for (int32_t i = t; i < runs; i += step) j.queue[i] = make_uint2((uint32_t)j.src, (uint32_t)i);
+    if (t == 0) a.table[blockIdx.y] = j;
+}
+
+// One push pass of a wave over entries [first, ...) of the round's queue.
+template <int WT>
+__device__ __forceinline__ void push_entry(const OrderJob &J, gptr<uint32_t> dist, gptr<unsigned long long> next_bits,
+                                           gptr<u32x2> next_queue, gptr<unsigned long long> region, u32x2 ent,
+                                           uint32_t &lowest) {
+    const int lane = threadIdx.x & 63;
+    gptr<const int32_t> ro = to_global(J.ro);
+    gptr<const u32x2> adj = reinterpret_cast<gptr<const u32x2>>(to_global(J.adj));
+    const int32_t e0 = ro[ent.x] + (int32_t)ent.y * kPushRun, e1 = min(ro[ent.x + 1], e0 + kPushRun);
+    const uint32_t du = ld_dev(dist + ent.x);
+    u32x2 a[kPushRun / 64];
+    uint32_t cur[kPushRun / 64], nd[kPushRun / 64];
+#pragma unroll
+    for (int k = 0; k < kPushRun / 64; ++k) a[k] = adj[min(e0 + k * 64 + lane, e1 - 1)];
+#pragma unroll
+    for (int k = 0; k < kPushRun / 64; ++k) {
+        nd[k] = plus<WT>(du, a[k].y);
+        cur[k] = dist[a[k].x];
+    }
+    uint32_t old[kPushRun / 64];
+    bool win[kPushRun / 64];
+#pragma unroll
+    for (int k = 0; k < kPushRun / 64; ++k) {
+        win[k] = e0 + k * 64 + lane < e1 && nd[k] < cur[k];
+        if (win[k])
+            old[k] = __hip_atomic_fetch_min(dist + a[k].x, nd[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    unsigned long long was[kPushRun / 64];
+#pragma unroll
+    for (int k = 0; k < kPushRun / 64; ++k) {
+        win[k] = win[k] && nd[k] < old[k];
+        if (win[k]) {
+            lowest = min(lowest, nd[k]);
+            was[k] = __hip_atomic_fetch_or(next_bits + (a[k].x >> 6), 1ull << (a[k].x & 63), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    // vertices new on the next frontier: their runs go to the queue
+    uint32_t news = 0, runs = 0;
+    unsigned long long arcs = 0;
+    uint32_t deg[kPushRun / 64];
+#pragma unroll
+    for (int k = 0; k < kPushRun / 64; ++k) {
+        win[k] = win[k] && !(was[k] >> (a[k].x & 63) & 1ull);
+        deg[k] = 0;
+        if (win[k]) {
+            deg[k] = (uint32_t)(ro[a[k].x + 1] - ro[a[k].x]);
+            news += deg[k] > 0u ? 1u : 0u;  // a vertex without out-arcs is on no frontier
+            runs += (deg[k] + kPushRun - 1) / kPushRun;
+            arcs += deg[k];
+        }
+    }
+    if (__ballot(news != 0u) == 0ull) return;
+    uint32_t before = runs, total = news;
+    unsigned long long sum = arcs;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t x = (uint32_t)__shfl_up((int)before, o, 64);
+        if (lane >= o) before += x;
+        total += (uint32_t)__shfl_xor((int)total, o, 64);
+        sum += __shfl_xor(sum, o, 64);
+    }
+    const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)before, 63);
+    unsigned long long base = 0;
+    if (lane == 0) {
+        base = __hip_atomic_fetch_add(region + kRgCnt, (unsigned long long)all, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_AGENT);
+        (void)__hip_atomic_fetch_add(region + kRgF, (unsigned long long)total, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+        (void)__hip_atomic_fetch_add(region + kRgE, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    base = (unsigned long long)__shfl((long long)base, 0, 64);
+    if (base + all > (unsigned long long)J.cap) {  // the next round pulls
+        if (lane == 0)
+            (void)__hip_atomic_fetch_or(region + kRgFlags, kFlagOver, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
+    uint32_t at = (uint32_t)base + before - runs;
+#pragma unroll
+    for (int k = 0; k < kPushRun / 64; ++k)
+        if (win[k])
+            for (uint32_t r = 0; r * kPushRun < deg[k]; ++r) next_queue[at++] = u32x2{a[k].x, r};
+}
+
+// WT: 0 uint32, 1 binary32, 2 unit steps.  Blocks [0, vblocks) of a pull take
+// kOrderVerts vertices each, the others the long rows' chunks.
+template <int WT>
+__global__ __launch_bounds__(256) void k_order(OrderArgs g) {
+    const OrderJob &J = g.job[blockIdx.y];
+    const int t = threadIdx.x, lane = t & 63;
+    gptr<unsigned long long> ctl = to_global(J.ctl);
+    const int32_t n = J.n;
+    const int s0 = (int)(g.round % 3), s1 = (int)((g.round + 1) % 3), s2 = (int)((g.round + 2) % 3);
+    constexpr int slot_words = kOrderRegions * kOrderRegionWords;
+    const Totals T = read_slot(ctl + s0 * slot_words);
+    const bool pull = T.flags != 0ull || kOrderBias * (double)T.E * (double)T.E >= (double)n * (double)J.m;
+    // the slot and the bitmap of the round after next
+    if (blockIdx.x == 0)
+        for (int i = t; i < slot_words; i += 256) ctl[s2 * slot_words + i] = 0ull;
+    gptr<unsigned long long> region = ctl + s1 * slot_words + (blockIdx.x % kOrderRegions) * kOrderRegionWords;
+    if (blockIdx.x == 0 && t == 0) {
+        gptr<unsigned long long> state = ctl + kOrderState;
+        for (int i = 0; i < kOrderRegions; ++i)
+            state[kStPulledArcs] += ctl[s0 * slot_words + i * kOrderRegionWords + kRgRead];
+        if (T.F == 0ull) {
+            if (state[kStDone] == 0ull) {
+                state[kStDone] = 1ull;
+                unsigned long long *st = g.stat + (size_t)blockIdx.y * kOrderStatWords;
+                const unsigned long long v[kOrderStatWords] = {1ull, (unsigned long long)g.round, state[kStPulls],
+                                                               state[kStF], state[kStPushed], state[kStPulledArcs]};
+#pragma unroll
+                for (int i = kOrderStatWords - 1; i >= 0; --i)
+                    __hip_atomic_store(st + i, v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+        } else {
+            state[kStF] += T.F;
+            if (pull) {
+                (void)__hip_atomic_fetch_or(region + kRgFlags, kFlagPulled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                state[kStPulls] += 1ull;
+            } else {
+                state[kStPushed] += T.E;
+            }
+        }
+    }
+    if (T.F == 0ull) return;
+    gptr<unsigned long long> bits = reinterpret_cast<gptr<unsigned long long>>(to_global(J.bits));
+    gptr<unsigned long long> next_bits = bits + (size_t)s1 * J.nword;
+    gptr<uint32_t> dist = to_global(J.dist);
+    for (int32_t i = blockIdx.x * 256 + t; i < J.nword; i += gridDim.x * 256) bits[(size_t)s2 * J.nword + i] = 0ull;
+    __shared__ uint32_t sLow, sCnt, sArcs, sRead;
+    if (t == 0) {
+        sLow = 0xFFFFFFFFu;
+        sCnt = sArcs = sRead = 0u;
+    }
+    uint32_t lowest = 0xFFFFFFFFu, nread = 0, nnew = 0;
+    const int32_t vblocks = (n + kOrderVerts - 1) / kOrderVerts;
+    if (!pull) {
+        gptr<u32x2> queue = reinterpret_cast<gptr<u32x2>>(to_global(J.queue));
+        gptr<const u32x2> from = queue + (size_t)(g.round & 1) * kOrderRegions * J.cap;
+        gptr<u32x2> to = queue + ((size_t)((g.round + 1) & 1) * kOrderRegions + blockIdx.x % kOrderRegions) * J.cap;
+        // entry i of the regions' lists laid end to end
+        uint32_t mine = lane < kOrderRegions ? (uint32_t)ctl[s0 * slot_words + lane * kOrderRegionWords + kRgCnt] : 0u;
+        uint32_t upto = mine;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t x = (uint32_t)__shfl_up((int)upto, o, 64);
+            if (lane >= o) upto += x;
+        }
+        const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+        const uint32_t waves = gridDim.x * 4u;
+        for (uint32_t i = blockIdx.x * 4u + (uint32_t)(t >> 6); i < all; i += waves) {
+            const int rg = (int)__popcll(__ballot(upto <= i));
+            const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)upto, rg);
+            const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)mine, rg);
+            const u32x2 ent = from[(size_t)rg * J.cap + (i - (end - cnt))];
+            push_entry<WT>(J, dist, next_bits, to, region, ent, lowest);
+        }
+        __syncthreads();
+    } else {
+        gptr<const uint32_t> on = reinterpret_cast<gptr<const uint32_t>>(bits + (size_t)s0 * J.nword);
+        gptr<const u32x2> arc = reinterpret_cast<gptr<const u32x2>>(to_global(J.arc));
+        const uint32_t mu = T.mu;
+        const auto step = [](uint32_t d, uint32_t w) { return plus<WT>(d, w); };
+        __shared__ uint32_t sList[kOrderVerts], sBest[kOrderVerts];
+        __shared__ unsigned long long sNew[kOrderVerts / 64];
+        for (int32_t vb = blockIdx.x; vb < vblocks; vb += gridDim.x) {
+            if (t == 0) sCnt = 0u;
+            __syncthreads();
+            // the two lightest arcs: every load of a vertex is issued at once,
+            // then the tails' bits, then their distances
+            constexpr int V = kOrderVerts / 256;
+            uint32_t b[V], best[V], on0[V], on1[V];
+            u32x2 a0[V], a1[V];
+            bool in0[V], in1[V], row[V];
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                const int32_t v = min(vb * kOrderVerts + k * 256 + t, n - 1);
+                b[k] = dist[v];
+                a0[k] = reinterpret_cast<gptr<const u32x2>>(to_global(J.a0))[v];
+                a1[k] = reinterpret_cast<gptr<const u32x2>>(to_global(J.a1))[v];
+            }
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                const bool ok = vb * kOrderVerts + k * 256 + t < n;
+                // (absent arcs: weight INF, and no tail)
+                in0[k] = ok && a0[k].x != kOrderNone && step(mu, a0[k].y) < b[k];
+                in1[k] = in0[k] && a1[k].x != kOrderNone && step(mu, a1[k].y) < b[k];
+                if (in0[k]) on0[k] = on[a0[k].x >> 5];
+                if (in1[k]) on1[k] = on[a1[k].x >> 5];
+            }
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                nread += (in0[k] ? 1u : 0u) + (in1[k] ? 1u : 0u);
+                best[k] = b[k];
+                row[k] = in1[k];
+                in0[k] = in0[k] && (on0[k] >> (a0[k].x & 31u) & 1u) != 0u;
+                in1[k] = in1[k] && (on1[k] >> (a1[k].x & 31u) & 1u) != 0u;
+                if (in0[k]) on0[k] = dist[a0[k].x];
+                if (in1[k]) on1[k] = dist[a1[k].x];
+            }
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                if (in0[k]) best[k] = min(best[k], step(on0[k], a0[k].y));
+                if (in1[k]) best[k] = min(best[k], step(on1[k], a1[k].y));
+                // the others, below, for the vertices they may still improve
+                row[k] = row[k] && step(mu, a1[k].y) < best[k];
+                const int i = k * 256 + t;
+                const int32_t v = vb * kOrderVerts + i;
+                if (row[k]) row[k] = step(mu, to_global(J.w2)[v]) < best[k];
+                const unsigned long long m = __ballot(row[k]);
+                if (m != 0ull) {
+                    uint32_t at = 0;
+                    if (lane == 0) at = atomicAdd(&sCnt, (uint32_t)__popcll(m));
+                    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+                    if (row[k]) {
+                        sList[at] = (uint32_t)i;
+                        sBest[at] = best[k];
+                    }
+                }
+                const bool won = !row[k] && best[k] < b[k];
+                if (won) {
+                    dist[v] = best[k];
+                    lowest = min(lowest, best[k]);
+                }
+                const unsigned long long x = __ballot(won);
+                if (lane == 0) sNew[i >> 6] = x;
+            }
+            __syncthreads();
+            // eight lanes per vertex: a line of eight arcs at a time
+            const uint32_t cnt = sCnt;
+            gptr<const int32_t> ro = to_global(J.ro_in);
+            for (uint32_t k = (uint32_t)t >> 3; k < cnt; k += 32u) {
+                const uint32_t i = sList[k];
+                const int32_t v = vb * kOrderVerts + (int32_t)i;
+                uint32_t low = sBest[k];
+                const int32_t e0 = ro[v] + 2, e1 = ro[v + 1];
+                for (int32_t e = e0; e < e1; e += 8) {
+                    const int32_t my = e + (t & 7);
+                    const u32x2 a = arc[min(my, e1 - 1)];
+                    const bool in = my < e1 && step(mu, a.y) < low;
+                    uint32_t c = low;
+                    if (in) {
+                        ++nread;
+                        if (on[a.x >> 5] >> (a.x & 31u) & 1u) c = min(c, step(dist[a.x], a.y));
+                    }
+#pragma unroll
+                    for (int o = 1; o < 8; o <<= 1) c = min(c, (uint32_t)__shfl_xor((int)c, o, 8));
+                    low = c;
+                    // the last of the eight still counts: the next eight may
+                    if (!(__ballot(in && step(mu, a.y) < low) >> ((lane & 56) + 7) & 1ull)) break;
+                }
+                // (the block read dist[v] before, and only it writes it)
+                if ((t & 7) == 0 && low < dist[v]) {
+                    dist[v] = low;
+                    lowest = min(lowest, low);
+                    (void)atomicOr(&sNew[i >> 6], 1ull << (i & 63));
+                }
+            }
+            __syncthreads();
+            if (t < kOrderVerts / 64 && sNew[t] != 0ull) {
+                nnew += (uint32_t)__popcll(sNew[t]);
+                (void)__hip_atomic_fetch_or(next_bits + vb * (kOrderVerts / 64) + t, sNew[t], __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __syncthreads();
+        }
+        // long rows: 16 lanes per chunk, 16 arcs at a time
+        const int32_t cfirst = ((int32_t)gridDim.x > vblocks ? (int32_t)blockIdx.x - vblocks : (int32_t)blockIdx.x);
+        const int32_t cstep = ((int32_t)gridDim.x > vblocks ? (int32_t)gridDim.x - vblocks : (int32_t)gridDim.x) * 16;
+        for (int32_t c = cfirst * 16 + (t >> 4); cfirst >= 0 && c < J.nchunks; c += cstep) {
+            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+            const u32x4 ch = reinterpret_cast<gptr<const u32x4>>(to_global(J.chunk))[c];
+            const uint32_t b0 = ld_dev(dist + ch.x);
+            uint32_t low = b0;
+            if (!(step(mu, ch.w) < low)) continue;  // its lightest arc
+            for (int32_t e = (int32_t)ch.y; e < (int32_t)ch.z; e += 16) {
+                const int32_t my = e + (t & 15);
+                const u32x2 a = arc[min(my, (int32_t)ch.z - 1)];
+                const bool in = my < (int32_t)ch.z && step(mu, a.y) < low;
+                uint32_t c1 = low;
+                if (in) {
+                    ++nread;
+                    if (on[a.x >> 5] >> (a.x & 31u) & 1u) c1 = min(c1, step(dist[a.x], a.y));
+                }
+#pragma unroll
+                for (int o = 1; o < 16; o <<= 1) c1 = min(c1, (uint32_t)__shfl_xor((int)c1, o, 16));
+                low = c1;
+                if (!(__ballot(in && step(mu, a.y) < low) >> ((lane & 48) + 15) & 1ull)) break;
+            }
+            if ((t & 15) == 0 && low < b0 &&
+                low < __hip_atomic_fetch_min(dist + ch.x, low, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                lowest = min(lowest, low);
+                ++nnew;
+                (void)__hip_atomic_fetch_or(next_bits + (ch.x >> 6), 1ull << (ch.x & 63u), __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+    if (lowest != 0xFFFFFFFFu) atomicMin(&sLow, lowest);
+    if (nnew) atomicAdd(&sArcs, nnew);
+    if (nread) atomicAdd(&sRead, nread);
+    __syncthreads();
+    if (t == 0) {
+        if (sLow != 0xFFFFFFFFu)
+            (void)__hip_atomic_fetch_max(region + kRgMu, (unsigned long long)(uint32_t)~sLow, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+        if (sArcs)
+            (void)__hip_atomic_fetch_add(region + kRgF, (unsigned long long)sArcs, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+        if (sRead)
+            (void)__hip_atomic_fetch_add(region + kRgRead, (unsigned long long)sRead, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// ---- layout ------------------------------------------------------------------
+
+// Rows of up to 64 arcs: a wave each, sorted across its lanes.
+__device__ __forceinline__ unsigned long long wave_sort(unsigned long long key) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 2; k <= 64; k <<= 1)
+#pragma unroll
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            const unsigned long long other = __shfl_xor(key, j, 64);
+            const bool keep_low = ((lane & j) == 0) == ((lane & k) == 0);
+            key = (key < other) == keep_low ? key : other;
+        }
+    return key;
+}
+
+__device__ __forceinline__ uint2 key_arc(unsigned long long k) { return make_uint2((uint32_t)k, (uint32_t)(k >> 32)); }
+
+__device__ __forceinline__ void order_lightest(int32_t v, int32_t deg, unsigned long long k0, unsigned long long k1,
+                                               unsigned long long k2, uint32_t inf, uint2 *a0, uint2 *a1, uint32_t *w2) {
+    const bool own = deg <= kOrderChunk;  // long rows go by chunks
+    a0[v] = own && deg > 0 ? key_arc(k0) : make_uint2(kOrderNone, inf);
+    a1[v] = own && deg > 1 ? key_arc(k1) : make_uint2(kOrderNone, inf);
+    w2[v] = own && deg > 2 ? (uint32_t)(k2 >> 32) : inf;
+}
+
+__global__ __launch_bounds__(256) void k_order_short(int32_t n, const int32_t *ro, const uint2 *adj, uint2 *arc,
+                                                     uint32_t inf, uint2 *a0, uint2 *a1, uint32_t *w2) {
+    const int lane = threadIdx.x & 63;
+    for (int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); v < n; v += (int64_t)gridDim.x * 4) {
+        const int32_t e0 = ro[v], deg = ro[v + 1] - e0;
+        if (deg > 64) continue;
+        unsigned long long key = ~0ull;
+        if (lane < deg) {
+            const uint2 a = adj[e0 + lane];
+            key = (unsigned long long)a.y << 32 | a.x;
+        }
+        if (deg > 1) key = wave_sort(key);
+        if (lane < deg) arc[e0 + lane] = key_arc(key);
+        const unsigned long long k0 = __shfl(key, 0, 64), k1 = __shfl(key, 1, 64), k2 = __shfl(key, 2, 64);
+        if (lane == 0) order_lightest((int32_t)v, deg, k0, k1, k2, inf, a0, a1, w2);
+    }
+}
+
+// Longer rows: a block per run of up to kOrderChunk arcs, sorted in LDS.  runs:
+// (vertex, first arc, its entry in chunk or kOrderNone).
+__global__ __launch_bounds__(256) void k_order_long(const uint4 *runs, const int32_t *ro, const uint2 *adj, uint2 *arc,
+                                                    uint32_t inf, uint2 *a0, uint2 *a1, uint32_t *w2, uint4 *chunk) {
+    __shared__ unsigned long long key[kOrderChunk];
+    const int t = threadIdx.x;
+    const uint4 r = runs[blockIdx.x];
+    const int32_t v = (int32_t)r.x, e0 = (int32_t)r.y, deg = ro[v + 1] - ro[v], n = min(ro[v + 1] - e0, kOrderChunk);
+    int size = 128;
+    while (size < n) size <<= 1;
+    for (int i = t; i < size; i += 256) {
+        unsigned long long k = ~0ull;
+        if (i < n) {
+            const uint2 a = adj[e0 + i];
+            k = (unsigned long long)a.y << 32 | a.x;
+        }
+        key[i] = k;
+    }
+    for (int k = 2; k <= size; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            __syncthreads();
+            for (int i = t; i < size / 2; i += 256) {
+                const int a = 2 * i - (i & (j - 1)), b = a + j;
+                const unsigned long long x = key[a], y = key[b];
+                if ((x > y) == ((a & k) == 0)) {
+                    key[a] = y;
+                    key[b] = x;
+                }
+            }
+        }
+    __syncthreads();
+    for (int i = t; i < n; i += 256) arc[e0 + i] = key_arc(key[i]);
+    if (t == 0 && e0 == ro[v]) order_lightest(v, deg, key[0], key[1], key[2], inf, a0, a1, w2);
+    if (t == 0 && r.z != kOrderNone) chunk[r.z] = make_uint4(r.x, r.y, (uint32_t)(e0 + n), (uint32_t)(key[0] >> 32));
+}
+
+inline size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
+inline int32_t bit_words(int32_t n) { return (int32_t)(((int64_t)n + kOrderVerts - 1) / kOrderVerts * (kOrderVerts / 64)); }
+inline int32_t queue_cap(int32_t n) { return std::clamp(n / 64, 1024, 65536); }
+
+}  // namespace
+
+hipError_t order_build(OrderSet *out, int32_t n, int32_t m, const int32_t *ro_in, const uint2 *adj_in,
+                       const int32_t *h_ro_in, int wt, hipStream_t st) {
+    *out = OrderSet{};
+    std::vector<uint4> runs;
+    uint32_t nchunks = 0;
+    for (int32_t v = 0; v < n; ++v) {
+        const int32_t d = h_ro_in[v + 1] - h_ro_in[v];
+        if (d <= 64) continue;
+        for (int32_t e = h_ro_in[v]; e < h_ro_in[v + 1]; e += kOrderChunk) {
+            runs.push_back(make_uint4((uint32_t)v, (uint32_t)e, d > kOrderChunk ? nchunks++ : kOrderNone, 0u));
+            if (h_ro_in[v + 1] - e <= kOrderChunk) break;  // (e + kOrderChunk may pass 2^31)
+        }
+    }
+    const size_t bn = al256(sizeof(uint32_t) * (size_t)n), bm = al256(sizeof(uint2) * (size_t)std::max(m, 1)),
+                 bc = al256(sizeof(uint4) * std::max<size_t>(nchunks, 1)), b2 = al256(sizeof(uint2) * (size_t)n);
+    OrderSet s;
+    s.bytes = bm + bn + 2 * b2 + bc;
+    hipError_t e = hipMalloc(&s.base, s.bytes);
+    if (e != hipSuccess) return e;
+    char *p = static_cast<char *>(s.base);
+    s.arc = reinterpret_cast<uint2 *>(p);
+    p += bm;
+    s.a0 = reinterpret_cast<uint2 *>(p);
+    p += b2;
+    s.a1 = reinterpret_cast<uint2 *>(p);
+    p += b2;
+    s.w2 = reinterpret_cast<uint32_t *>(p);
+    p += bn;
+    s.chunk = reinterpret_cast<uint4 *>(p);
+    s.nchunks = (int32_t)nchunks;
+    void *d_runs = nullptr;
+    const uint32_t inf = wt == 1 ? kInfF32 : kInfU32;
+    if (!runs.empty()) e = hipMallocAsync(&d_runs, sizeof(uint4) * runs.size(), st);
+    if (e == hipSuccess && !runs.empty())
+        e = hipMemcpyAsync(d_runs, runs.data(), sizeof(uint4) * runs.size(), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) {
+        const unsigned blocks = (unsigned)std::min<int64_t>(((int64_t)n + 3) / 4, 8192);
+        hipLaunchKernelGGL(k_order_short, dim3(blocks), dim3(256), 0, st, n, ro_in, adj_in, s.arc, inf, s.a0, s.a1, s.w2);
+        if (!runs.empty())
+            hipLaunchKernelGGL(k_order_long, dim3((unsigned)runs.size()), dim3(256), 0, st,
+                               static_cast<const uint4 *>(d_runs), ro_in, adj_in, s.arc, inf, s.a0, s.a1, s.w2, s.chunk);
+        e = hipGetLastError();
+    }
+    if (d_runs) (void)hipFreeAsync(d_runs, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) {
+        (void)hipFree(s.base);
+        return e;
+    }
+    *out = s;
+    return hipSuccess;
+}
+
+size_t order_ws_bytes(int32_t n) {
+    return al256(kOrderCtlWords * 8) + al256(3 * (size_t)bit_words(n) * 8) +
+           al256(2 * (size_t)kOrderRegions * (size_t)queue_cap(n) * sizeof(uint2));
+}
+
+void order_carve(OrderJob *j, void *ws) {
+    char *p = static_cast<char *>(ws);
+    j->ctl = reinterpret_cast<unsigned long long *>(p);
+    p += al256(kOrderCtlWords * 8);
+    j->nword = bit_words(j->n);
+    j->bits = reinterpret_cast<uint64_t *>(p);
+    p += al256(3 * (size_t)j->nword * 8);
+    j->cap = queue_cap(j->n);
+    j->queue = reinterpret_cast<uint2 *>(p);
+}
+
+hipError_t order_begin(const OrderJob *jobs, int32_t k, int wt, OrderJob *table, hipStream_t st) {
+    if (k < 1 || k > kOrderMaxJobs || wt < 0 || wt > 2) return hipErrorInvalidValue;
+    for (int32_t b = 0; b < k; b += kBeginJobs) {
+        BeginArgs a{};
+        const int32_t c = std::min(kBeginJobs, k - b);
+        int32_t big = 1;
+        for (int32_t i = 0; i < c; ++i) {
+            const OrderJob &j = jobs[b + i];
+            if (j.n < 1 || j.src < 0 || j.src >= j.n || !j.dist || !j.arc || !j.ctl) return hipErrorInvalidValue;
+            a.job[i] = j;
+            big = std::max(big, j.n);
+        }
+        a.table = table + b;
+        a.inf = wt == 1 ? kInfF32 : kInfU32;
+        const int32_t blocks = (int32_t)std::min<int64_t>(((int64_t)big + 1023) / 1024, 1024);
+        hipLaunchKernelGGL(k_order_begin, dim3((unsigned)blocks, (unsigned)c), dim3(256), 0, st, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t order_rounds(const OrderJob *jobs, int32_t k, int wt, const OrderJob *table, int64_t first, int32_t rounds,
+                        unsigned long long *stat, hipStream_t st) {
+    // blocks for the vertices, and for the long rows (16 chunks each)
+    int64_t blocks = 64;
+    for (int32_t i = 0; i < k; ++i)
+        blocks = std::max<int64_t>(blocks, std::min<int64_t>(((int64_t)jobs[i].n + kOrderVerts - 1) / kOrderVerts, 8192) +
+                                               std::min<int64_t>(((int64_t)jobs[i].nchunks + 15) / 16, 1024));
+    const dim3 grid((unsigned)blocks, (unsigned)k), blk(256);
+    OrderArgs a{table, 0, stat};
+    for (int32_t r = 0; r < rounds; ++r) {
+        a.round = first + r;
+        if (wt == 0) hipLaunchKernelGGL((k_order<0>), grid, blk, 0, st, a);
+        else if (wt == 1) hipLaunchKernelGGL((k_order<1>), grid, blk, 0, st, a);
+        else hipLaunchKernelGGL((k_order<2>), grid, blk, 0, st, a);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace gr
