@@ -360,7 +360,9 @@ gr_status gr_bfs_ex(const gr_graph *g, int32_t src, void *depth_out, void *strea
 typedef struct {
     int32_t rounds;             /* rounds in which some query's frontier was not empty */
     int32_t replays;            /* replays of the captured chunk of rounds (one host wait each); 0 when
-                                   none runs (k = 1, or the single-workgroup loop) */
+                                   none runs (k = 1, or the single-workgroup loop); the weight-ordered
+                                   loop and calls whose queries take several loops count chunks of 8
+                                   rounds */
     int64_t edges_pushed;       /* arcs expanded (a batched arc serves every source active at its tail) */
     int64_t frontier_sum;       /* frontier entries expanded */
     int64_t source_relaxations; /* (arc, query) relaxations: for gr_sssp_batch_ex the (arc, active source)
@@ -420,8 +422,8 @@ gr_status gr_sssp_batch_ex(const gr_graph *g, const int32_t *srcs, int32_t k, vo
  * one arc layout (row offsets, or arcs padded to the same slot count), each
  * query runs that loop in a workgroup of its own, all in one launch, with no
  * workspace (stats->replays = 0).  Queries on graphs whose AUTO runs over tiles
- * run in launches of their own before the others (rounds 1, or 0 for a source
- * without arcs).
+ * (rounds 1, or 0 for a source without arcs) or weight-ordered arcs run in
+ * launches of their own, each kind together, before the others.
  */
 gr_status gr_sssp_multi(const gr_graph *const *graphs, const int32_t *srcs, int32_t k, void *const *dist_out,
                         void *stream, gr_multi_stats *stats, int32_t *iterations);
@@ -465,10 +467,11 @@ typedef struct {
  * them from anywhere in the FIFO (they hold nothing the head waits for) and
  * runs them as one launch, one workgroup per query, on a stream of its own;
  * batch_size is then that launch's query count.  Queries on graphs whose AUTO
- * runs over tiles take no slot either: a thread of the server runs all that
- * wait (up to 64) in one launch beside the executors; their workspace is
- * outside the budget (about 64 bytes per tile and 4 per arc between tiles,
- * some 2% of what the budget counts for a query).  cfg may be
+ * runs over tiles or weight-ordered arcs take no slot either: a thread of the
+ * server runs all that wait (up to 64) together, beside the executors; their
+ * workspace is outside the budget (over tiles about 64 bytes per tile and 4
+ * per arc between tiles, over weight-ordered arcs about 5 per vertex; the
+ * budget counts 28 bytes per vertex for a query).  cfg may be
  * NULL. */
 gr_status gr_server_create(gr_server **out, size_t hbm_budget_bytes, const gr_server_config *cfg);
 /* Registers a graph (not copied; it must outlive the server). */

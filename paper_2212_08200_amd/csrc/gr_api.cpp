@@ -1091,7 +1091,7 @@ static gr_status run_lds_batch(const gr_graph *const *graphs, const int32_t *src
 // rows[i] receiving query i's distances; one initialisation and one persistent
 // launch for all of them, and one wait.  us (optional): the launches' time.
 struct TileTotals {
-    int64_t arcs = 0, items = 0;
+    int64_t arcs = 0, items = 0, launches = 0;
 };
 static gr_status run_tiles(const gr_graph *const *graphs, const int32_t *srcs, int32_t k, uint32_t *const *rows,
                            int wt, hipStream_t st, int64_t timeout_us, TileTotals *tot, double *us) {
@@ -1152,43 +1152,6 @@ static gr_status run_tiled(const gr_graph *g, int32_t src, uint32_t *dist, hipSt
     }
     return GR_OK;
 }
-
-// The queries among graphs[0..k) that run over tiles (those whose AUTO does;
-// with `all`, those whose graph has them), as groups that share a launch (one
-// weight type, one slot count).
-static std::vector<std::vector<int32_t>> tile_groups(const gr_graph *const *graphs, int32_t k, bool all) {
-    std::vector<std::vector<int32_t>> out;
-    for (int32_t i = 0; i < k; ++i) {
-        const gr_graph *g = graphs[i];
-        if (!(all ? g->tiles.ntiles > 0 : g->auto_tiled)) continue;
-        size_t j = 0;
-        while (j < out.size() && (graphs[out[j][0]]->plain.wt != g->plain.wt ||
-                                  graphs[out[j][0]]->tiles.slots != g->tiles.slots))
-            ++j;
-        if (j == out.size()) out.emplace_back();
-        out[j].push_back(i);
-    }
-    return out;
-}
-
-// One launch over such a group (weighted queries).
-static gr_status run_tile_group(const gr_graph *const *graphs, const int32_t *srcs, uint32_t *const *rows,
-                                const std::vector<int32_t> &idx, hipStream_t st, TileTotals *tot) {
-    const gr_graph *gs[kTileMaxJobs];
-    int32_t ss[kTileMaxJobs];
-    uint32_t *rs[kTileMaxJobs];
-    const int32_t k = (int32_t)idx.size();
-    for (int32_t j = 0; j < k; ++j) {
-        gs[j] = graphs[idx[j]];
-        ss[j] = srcs[idx[j]];
-        rs[j] = rows[idx[j]];
-    }
-    return run_tiles(gs, ss, k, rs, gs[0]->plain.wt, st, kBarrierTimeoutUs, tot, nullptr);
-}
-
-// Whether a query's frontier was ever non-empty (its source has arcs): the
-// rounds that the tiled loop, which has none, reports.
-static int32_t tile_rounds(const gr_graph *g, int32_t src) { return g->h_ro[src + 1] > g->h_ro[src] ? 1 : 0; }
 
 // Weight-ordered loop (gr_order.hip): k queries, rows[i] receiving query i's
 // distances; every launch is a round of all of them.  The first chunk of
@@ -1290,6 +1253,61 @@ static gr_status run_ordered(const gr_graph *g, int32_t src, uint32_t *dist, hip
         local.launches = (int32_t)std::min<int64_t>(launches + 1, INT32_MAX);
         local.push_us = us;  // both directions share the kernel
         *stats = local;
+    }
+    return GR_OK;
+}
+
+static bool has_own(const gr_graph *g) { return g->tiles.ntiles > 0 || g->order.base != nullptr; }
+
+// Whether a query's frontier was ever non-empty (its source has arcs): also the
+// rounds that the tiled loop, which has none, reports.
+static int32_t source_rounds(const gr_graph *g, int32_t src) { return g->h_ro[src + 1] > g->h_ro[src] ? 1 : 0; }
+
+// The queries among graphs[0..k) whose AUTO runs over tiles or weight-ordered
+// arcs (with `all`, those whose graph has them), as groups that share their
+// launches (one weight type, and one slot count of the tiles).
+static std::vector<std::vector<int32_t>> own_groups(const gr_graph *const *graphs, int32_t k, bool all) {
+    std::vector<std::vector<int32_t>> out;
+    for (int32_t i = 0; i < k; ++i) {
+        const gr_graph *g = graphs[i];
+        if (!(all ? has_own(g) : g->auto_tiled || g->auto_order)) continue;
+        size_t j = 0;
+        while (j < out.size() && (graphs[out[j][0]]->plain.wt != g->plain.wt ||
+                                  graphs[out[j][0]]->tiles.slots != g->tiles.slots))
+            ++j;
+        if (j == out.size()) out.emplace_back();
+        out[j].push_back(i);
+    }
+    return out;
+}
+
+// Such a group (weighted queries); rounds receives each query's.
+static gr_status run_own_group(const gr_graph *const *graphs, const int32_t *srcs, uint32_t *const *rows,
+                               const std::vector<int32_t> &idx, hipStream_t st, TileTotals *tot,
+                               std::vector<int32_t> *rounds) {
+    const gr_graph *gs[kTileMaxJobs];
+    int32_t ss[kTileMaxJobs];
+    uint32_t *rs[kTileMaxJobs];
+    const int32_t k = (int32_t)idx.size();
+    rounds->assign((size_t)k, 0);
+    for (int32_t j = 0; j < k; ++j) {
+        gs[j] = graphs[idx[j]];
+        ss[j] = srcs[idx[j]];
+        rs[j] = rows[idx[j]];
+    }
+    if (gs[0]->tiles.ntiles > 0) {
+        for (int32_t j = 0; j < k; ++j) (*rounds)[j] = source_rounds(gs[j], ss[j]);
+        return run_tiles(gs, ss, k, rs, gs[0]->plain.wt, st, kBarrierTimeoutUs, tot, nullptr);
+    }
+    const unsigned long long *x = nullptr;
+    int64_t launches = 0;
+    const gr_status s = run_order(gs, ss, k, rs, gs[0]->plain.wt, st, &x, &launches, nullptr);
+    if (s != GR_OK) return s;
+    tot->launches = launches;
+    for (int32_t j = 0; j < k; ++j, x += kOrderStatWords) {
+        (*rounds)[j] = (int32_t)std::min<unsigned long long>(x[1], INT32_MAX);
+        tot->items += (int64_t)x[3];
+        tot->arcs += (int64_t)(x[4] + x[5]);
     }
     return GR_OK;
 }
@@ -1859,23 +1877,24 @@ extern "C" gr_status gr_sssp_multi(const gr_graph *const *graphs, const int32_t 
         for (int32_t i = 0; i < k; ++i) rows[i] = static_cast<uint32_t *>(dist_out[i]);
         return run_lds_batch(graphs, srcs, k, rows.data(), st, stats, iterations);
     }
-    // queries on graphs with tiles run over them, one launch per kind of
-    // layout; the others follow through the session
-    const auto tiled = tile_groups(graphs, k, false);
-    if (!tiled.empty()) {
+    // queries on graphs with tiles or weight-ordered arcs run over them, the
+    // queries of one kind together; the others follow through the session
+    const auto groups = own_groups(graphs, k, false);
+    if (!groups.empty()) {
         std::vector<uint32_t *> rows((size_t)k);
         for (int32_t i = 0; i < k; ++i) rows[i] = static_cast<uint32_t *>(dist_out[i]);
         gr_multi_stats sum{};
-        for (const auto &idx : tiled) {
+        for (const auto &idx : groups) {
             TileTotals tot;
-            gr_status s = run_tile_group(graphs, srcs, rows.data(), idx, st, &tot);
+            std::vector<int32_t> rounds;
+            gr_status s = run_own_group(graphs, srcs, rows.data(), idx, st, &tot, &rounds);
             if (s != GR_OK) return s;
             sum.edges_pushed += tot.arcs;
             sum.frontier_sum += tot.items;
-            for (const int32_t i : idx) {
-                const int32_t r = tile_rounds(graphs[i], srcs[i]);
-                sum.rounds = std::max(sum.rounds, r);
-                if (iterations) iterations[i] = r;
+            sum.replays += (int32_t)((tot.launches + kMqRoundsPerReplay - 1) / kMqRoundsPerReplay);
+            for (size_t j = 0; j < idx.size(); ++j) {
+                sum.rounds = std::max(sum.rounds, rounds[j]);
+                if (iterations) iterations[idx[j]] = rounds[j];
             }
         }
         sum.source_relaxations = sum.edges_pushed;
@@ -1883,7 +1902,7 @@ extern "C" gr_status gr_sssp_multi(const gr_graph *const *graphs, const int32_t 
         std::vector<int32_t> rs, at;
         std::vector<void *> rd;
         for (int32_t i = 0; i < k; ++i)
-            if (!graphs[i]->auto_tiled) {
+            if (!graphs[i]->auto_tiled && !graphs[i]->auto_order) {
                 rg.push_back(graphs[i]);
                 rs.push_back(srcs[i]);
                 rd.push_back(dist_out[i]);
@@ -1896,13 +1915,17 @@ extern "C" gr_status gr_sssp_multi(const gr_graph *const *graphs, const int32_t 
                 gr_sssp_multi(rg.data(), rs.data(), (int32_t)rg.size(), rd.data(), stream, &rest, it.data());
             if (s != GR_OK) return s;
             sum.rounds = std::max(sum.rounds, rest.rounds);
-            sum.replays = rest.replays;
+            sum.replays += rest.replays;
             sum.edges_pushed += rest.edges_pushed;
             sum.frontier_sum += rest.frontier_sum;
             sum.source_relaxations += rest.source_relaxations;
             if (iterations)
-                for (size_t j = 0; j < at.size(); ++j) iterations[at[j]] = it[j];
+                for (size_t j = 0; j < at.size(); ++j)  // (a source without arcs has no frontier in any loop)
+                    iterations[at[j]] = source_rounds(rg[j], rs[j]) ? it[j] : 0;
         }
+        // several loops in one call: as many chunks of rounds as the longest ran
+        if (groups.size() + (rg.empty() ? 0 : 1) > 1)
+            sum.replays = std::max(sum.replays, (sum.rounds + kMqRoundsPerReplay - 1) / kMqRoundsPerReplay);
         if (stats) *stats = sum;
         return GR_OK;
     }
@@ -2062,7 +2085,7 @@ extern "C" gr_status gr_sssp_batch_ex(const gr_graph *g, const int32_t *srcs, in
         s = run_tiles(gs.data(), srcs, k, rows.data(), g->plain.wt, st, kBarrierTimeoutUs, &tot, nullptr);
         if (s == GR_OK && stats) {
             *stats = gr_multi_stats{};
-            for (int32_t i = 0; i < k; ++i) stats->rounds = std::max(stats->rounds, tile_rounds(g, srcs[i]));
+            for (int32_t i = 0; i < k; ++i) stats->rounds = std::max(stats->rounds, source_rounds(g, srcs[i]));
             stats->edges_pushed = stats->source_relaxations = tot.arcs;
             stats->frontier_sum = tot.items;
         }
@@ -2104,8 +2127,8 @@ struct gr_server {
     size_t in_flight = 0;
     bool stopping = false;
     std::vector<std::thread> workers;
-    std::deque<SchedQuery> tiled;  // queries on graphs that run over tiles
-    std::thread tile_worker;
+    std::deque<SchedQuery> own;  // queries on graphs that run over tiles or weight-ordered arcs
+    std::thread own_worker;
 };
 
 static QuerySize query_size(const gr_graph *g) {
@@ -2368,16 +2391,16 @@ static void server_worker(gr_server *s, int exec_id) {
     (void)exec_id;
 }
 
-// Queries on graphs that run over tiles: one thread takes all that wait (up to
-// kTileMaxJobs) and runs them together, while the executors' sessions go on.
-// Those that arrive meanwhile make the next launch.
-static void server_tile_worker(gr_server *s) {
+// Queries on graphs that run over tiles or weight-ordered arcs: one thread takes
+// all that wait (up to kTileMaxJobs) and runs them together, while the
+// executors' sessions go on.  Those that arrive meanwhile are the next ones.
+static void server_own_worker(gr_server *s) {
     (void)hipSetDevice(s->device);
     hipStream_t st = nullptr;  // created with the first query
     std::unique_lock<std::mutex> lk(s->mu);
     for (;;) {
-        s->cv.wait(lk, [&] { return s->stopping || !s->tiled.empty(); });
-        if (s->tiled.empty()) break;
+        s->cv.wait(lk, [&] { return s->stopping || !s->own.empty(); });
+        if (s->own.empty()) break;
         if (!st) {  // (without a stream of their own the queries run on the null stream)
             lk.unlock();
             if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) st = nullptr;
@@ -2388,9 +2411,9 @@ static void server_tile_worker(gr_server *s) {
         std::vector<int32_t> ss;
         std::vector<uint32_t *> rows;
         const int64_t t_start = now_ns();
-        while (!s->tiled.empty() && (int)qs.size() < kTileMaxJobs) {
-            const SchedQuery q = s->tiled.front();
-            s->tiled.pop_front();
+        while (!s->own.empty() && (int)qs.size() < kTileMaxJobs) {
+            const SchedQuery q = s->own.front();
+            s->own.pop_front();
             qs.push_back(q);
             gs.push_back(s->graphs[q.graph]);
             ss.push_back(q.src);
@@ -2400,18 +2423,19 @@ static void server_tile_worker(gr_server *s) {
             t.res.t_start_ns = t_start;
         }
         lk.unlock();
-        for (const auto &idx : tile_groups(gs.data(), (int32_t)gs.size(), true)) {
+        for (const auto &idx : own_groups(gs.data(), (int32_t)gs.size(), true)) {
             TileTotals tot;
-            const gr_status ds = run_tile_group(gs.data(), ss.data(), rows.data(), idx, st, &tot);
+            std::vector<int32_t> rounds;
+            const gr_status ds = run_own_group(gs.data(), ss.data(), rows.data(), idx, st, &tot, &rounds);
             const int64_t t_done = now_ns();
             lk.lock();
-            for (const int32_t b : idx) {
-                Ticket &t = s->tickets[qs[b].ticket];
+            for (size_t j = 0; j < idx.size(); ++j) {
+                Ticket &t = s->tickets[qs[idx[j]].ticket];
                 t.state = kDone;
                 t.res.status = ds;
                 t.res.t_done_ns = t_done;
                 t.res.batch_size = (int32_t)idx.size();
-                t.res.iterations = ds == GR_OK ? tile_rounds(gs[b], ss[b]) : 0;
+                t.res.iterations = ds == GR_OK ? rounds[j] : 0;
             }
             lk.unlock();
         }
@@ -2449,7 +2473,7 @@ extern "C" gr_status gr_server_create(gr_server **out, size_t hbm_budget_bytes, 
     gr_server *raw = s.get();
     s->policy.reset(new SlotPolicy(hbm_budget_bytes, [raw](int32_t gid) { return query_size(raw->graphs[gid]); }));
     for (int i = 0; i < c.num_streams; ++i) s->workers.emplace_back(server_worker, raw, i);
-    s->tile_worker = std::thread(server_tile_worker, raw);
+    s->own_worker = std::thread(server_own_worker, raw);
     *out = s.release();
     return GR_OK;
 }
@@ -2486,9 +2510,10 @@ extern "C" gr_status gr_serve_submit(gr_server *s, int32_t graph_id, int32_t src
     // queries on graphs that run the single-workgroup loop by default are
     // run outside the executors' sessions
     // (those whose graph fits the row-offset layout, which any mix of them shares);
-    // those on graphs that run over tiles have a queue and a thread of their own
+    // those on graphs that run over tiles or weight-ordered arcs have a queue
+    // and a thread of their own
     const SchedQuery q{id, graph_id, src, dist_out, t, g->auto_loop == GR_LOOP_LDS && g->lds_fit};
-    if (g->auto_tiled) s->tiled.push_back(q);
+    if (g->auto_tiled || g->auto_order) s->own.push_back(q);
     else s->policy->push(q);
     s->cv.notify_all();
     *ticket = id;
@@ -2513,7 +2538,7 @@ extern "C" gr_status gr_server_destroy(gr_server *s) {
         s->stopping = true;
     }
     s->cv.notify_all();
-    s->tile_worker.join();
+    s->own_worker.join();
     for (std::thread &t : s->workers) t.join();
     delete s;
     return GR_OK;
@@ -2598,7 +2623,6 @@ struct TuneCfg {
     bool own;  // AUTO's own loop over tiles or weight-ordered arcs (the other fields do not apply)
 };
 
-static bool has_own(const gr_graph *g) { return g->tiles.ntiles > 0 || g->order.base != nullptr; }
 static void set_own(gr_graph *g, bool own) {
     g->auto_tiled = own && g->tiles.ntiles > 0;
     g->auto_order = own && g->order.base != nullptr;

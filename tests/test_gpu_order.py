@@ -106,3 +106,40 @@ def test_ordered_tuned(tmp_path, monkeypatch):
             np.testing.assert_array_equal(got, want)
             stats.append((st["loop"], st["layout"], st["arcs_pulled"] > 0))
     assert stats[0] == stats[1]
+
+
+def test_ordered_multi_and_server():
+    graphs = [gg.rmat(14, 16, gseed=31, pseed=32, wseed=33), gg.rmat(13, 8, gseed=34, pseed=35, wseed=36, wtype=gg.W_F32),
+              gg.uniform(70000, 300000, 37, 38), gg.grid(190, 39),
+              gg.from_arcs(300, [(i, i + 1, 1) for i in range(299)])]  # (the last two run other loops)
+    Gs = [gr.Graph.from_csr(g) for g in graphs]
+    qs = [(i % len(graphs), int(s)) for i, g in enumerate(graphs) for s in list(gg.pick_sources(g, 3, 3)) + [g.n - 1]]
+    want = [oracle.dijkstra(graphs[i], s) for i, s in qs]
+
+    def rows():
+        return [torch.full((graphs[i].n,), 0x5A5A5A5A, dtype=torch.int32, device="cuda") for i, _ in qs]
+
+    try:
+        outs = rows()
+        st = gr.gr_sssp_multi([Gs[i].handle for i, _ in qs], [s for _, s in qs], outs)
+        torch.cuda.synchronize()
+        for (i, s), o, w, it in zip(qs, outs, want, st["iterations"]):
+            np.testing.assert_array_equal(o.cpu().numpy().view(np.uint32), w, err_msg=graphs[i].name)
+            assert (it > 0) == bool(graphs[i].ro[s + 1] > graphs[i].ro[s])
+        for destroy_first in (False, True):
+            outs = rows()
+            torch.cuda.synchronize()
+            server = gr.gr_server_create(1 << 30)
+            ids = [gr.gr_server_add_graph(server, G.handle) for G in Gs]
+            tickets = [gr.gr_serve_submit(server, ids[i], s, o) for (i, s), o in zip(qs, outs)]
+            if not destroy_first:
+                for t in tickets:
+                    while gr.gr_serve_poll(server, t) is None:
+                        pass
+            gr.gr_server_destroy(server)
+            torch.cuda.synchronize()
+            for o, w in zip(outs, want):
+                np.testing.assert_array_equal(o.cpu().numpy().view(np.uint32), w)
+    finally:
+        for G in Gs:
+            G.close()
