@@ -389,6 +389,11 @@ typedef struct {
  * workgroup loop (GR_LOOP_LDS) runs that loop for every source instead, one
  * workgroup per source in one launch, with no workspace; one whose AUTO runs
  * over tiles runs the sources' tiles in one launch (stats: rounds 1, replays 0).
+ * One whose AUTO runs over weight-ordered arcs runs fewer than 8 sources as
+ * queries of one launch sequence; 8 or more take a lane each and the rounds of
+ * that loop (workspace: 280 bytes per vertex and at most 17 MB; in stats,
+ * edges_pushed counts the arcs read, source_relaxations the arcs of every
+ * vertex times the sources that improved it).
  * The current device must be the graph's.
  */
 gr_status gr_sssp_batch(const gr_graph *g, const int32_t *srcs, int32_t k, void *dist_out, void *stream);

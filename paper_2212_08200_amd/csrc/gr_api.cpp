@@ -481,7 +481,9 @@ static gr_status graph_build(gr_graph *g, int32_t n, int32_t m, const int32_t *r
     // degree ones keep the asynchronous loop: uniform graphs of 5,000 and
     // 30,000 vertices 0.28 and 0.35 ms against 0.33 and 0.40; 300,000: 1.5
     // queued against 0.97).
-    if (g->auto_loop != GR_LOOP_LDS && g->auto_loop != GR_LOOP_ASYNC && !g->auto_tiled && g->pull && m > 0) {
+    // (The loop's 32-bit arc indices step past a row's end.)
+    if (g->auto_loop != GR_LOOP_LDS && g->auto_loop != GR_LOOP_ASYNC && !g->auto_tiled && g->pull && m > 0 &&
+        m < INT32_MAX - 64) {
         std::vector<int32_t> in;
         if (g->csc_separate) {
             in.resize((size_t)n + 1);
@@ -1153,11 +1155,26 @@ static gr_status run_tiled(const gr_graph *g, int32_t src, uint32_t *dist, hipSt
     return GR_OK;
 }
 
+static_assert(kOrderMaxJobs * kOrderStatWords * 8 <= 8192, "the statistics fit the pinned slot");
+static void order_job(OrderJob *j, const gr_graph *g) {
+    *j = OrderJob{};
+    j->ro = g->d_ro;
+    j->adj = g->d_adj;
+    j->ro_in = g->d_ro_in;
+    j->arc = g->order.arc;
+    j->a0 = g->order.a0;
+    j->a1 = g->order.a1;
+    j->w2 = g->order.w2;
+    j->chunk = g->order.chunk;
+    j->nchunks = g->order.nchunks;
+    j->n = g->plain.n;
+    j->m = g->plain.m;
+}
+
 // Weight-ordered loop (gr_order.hip): k queries, rows[i] receiving query i's
 // distances; every launch is a round of all of them.  The first chunk of
 // launches is as long as the graphs' last queries, the host then reads the
 // pinned statistics.
-static_assert(kOrderMaxJobs * kOrderStatWords * 8 <= 8192, "the statistics fit the pinned slot");
 static gr_status run_order(const gr_graph *const *graphs, const int32_t *srcs, int32_t k, uint32_t *const *rows,
                            int wt, hipStream_t st, const unsigned long long **stat_out, int64_t *launches, double *us) {
     unsigned long long *hp = pinned_slot();
@@ -1174,21 +1191,9 @@ static gr_status run_order(const gr_graph *const *graphs, const int32_t *srcs, i
     void *ws = nullptr;
     HIP_TRY(hipMallocAsync(&ws, bytes, st));
     for (int32_t i = 0; i < k; ++i) {
-        const gr_graph *g = graphs[i];
         OrderJob &j = jobs[i];
-        j = OrderJob{};
-        j.ro = g->d_ro;
-        j.adj = g->d_adj;
-        j.ro_in = g->d_ro_in;
-        j.arc = g->order.arc;
-        j.a0 = g->order.a0;
-        j.a1 = g->order.a1;
-        j.w2 = g->order.w2;
-        j.chunk = g->order.chunk;
-        j.nchunks = g->order.nchunks;
+        order_job(&j, graphs[i]);
         j.dist = rows[i];
-        j.n = g->plain.n;
-        j.m = g->plain.m;
         j.src = srcs[i];
         order_carve(&j, static_cast<char *>(ws) + off[i]);
     }
@@ -2061,6 +2066,62 @@ static gr_status run_batch_dev(const gr_graph *g, const int32_t *srcs, int32_t k
     return status;
 }
 
+// The same over weight-ordered arcs: rounds enqueued as run_order's.
+static gr_status run_batch_order(const gr_graph *g, const int32_t *srcs, int32_t k, uint32_t *const *out_rows,
+                                 hipStream_t st, gr_multi_stats *stats) {
+    DeviceInfo di;
+    gr_status s = device_info(g->device, &di);
+    if (s != GR_OK) return s;
+    unsigned long long *hp = pinned_slot();
+    if (!hp) return fail(GR_ERR_OUT_OF_MEMORY, "pinned host buffer");
+    OrderBatch b{};
+    order_job(&b.g, g);
+    void *ws = nullptr;
+    HIP_TRY(hipMallocAsync(&ws, order_batch_bytes(g->plain.n), st));
+    order_batch_carve(&b, ws);
+    b.k = k;
+    for (int i = 0; i < kOrderBatchStatWords; ++i) hp[i] = 0ull;
+    const int64_t cap = (int64_t)g->plain.n + 2;
+    int64_t chunk = (int64_t)g->order_rounds.load(std::memory_order_relaxed) + 1, done = 0;
+    hipError_t e = order_batch_begin(b, srcs, g->plain.wt, st);
+    bool over = false;
+    while (e == hipSuccess) {
+        const int32_t c = (int32_t)std::min<int64_t>(chunk, 64);
+        e = order_batch_rounds(b, g->plain.wt, done, c, di.num_cu, hp, st);
+        done += c;
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        over = hp[0] == 0ull && done > cap;
+        if (hp[0] != 0ull || over) break;
+        chunk = done > 64 ? 32 : 4;
+    }
+    if (e == hipSuccess && !over) {
+        MqOutRows rows{};
+        for (int32_t i = 0; i < k; ++i) rows.row[i] = out_rows[i];
+        e = mq_batch_output(b.D, g->plain.n, k, rows, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+    }
+    const hipError_t e2 = hipFreeAsync(ws, st);
+    if (e != hipSuccess) return hip_fail(e, "batched weight-ordered loop");
+    if (e2 != hipSuccess) return hip_fail(e2, "hipFreeAsync");
+    if (over) return fail(GR_ERR_ITER_LIMIT, "the batch ran past n + 1 rounds");
+    g->order_rounds.store((int32_t)std::min<unsigned long long>(hp[1], 512), std::memory_order_relaxed);
+    if (stats) {
+        stats->rounds = (int32_t)hp[1];
+        stats->replays = (int32_t)((done + kMqRoundsPerReplay - 1) / kMqRoundsPerReplay);
+        stats->edges_pushed = (int64_t)hp[4];
+        stats->frontier_sum = (int64_t)hp[3];
+        stats->source_relaxations = (int64_t)hp[5];
+    }
+    return GR_OK;
+}
+
+// Batches over weight-ordered arcs: from this many sources on a source per
+// lane, below it a query each, whose time grows with their number (2 / 8 / 32
+// sources as lanes against queries: 313 / 365 / 516 and 280 / 360 / 645 us on
+// R-MAT 15, 627 / 714 / 1136 and 311 / 705 / 2226 on 18, 1424 / 1522 / 1882 and
+// 698 / 2026 / 8045 on 20).
+constexpr int32_t kOrderLanesMin = 8;
+
 extern "C" gr_status gr_sssp_batch_ex(const gr_graph *g, const int32_t *srcs, int32_t k, void *dist_out,
                                       void *stream, gr_multi_stats *stats) {
     if (!g) return fail(GR_ERR_INVALID_ARG, "graph is NULL");
@@ -2088,6 +2149,24 @@ extern "C" gr_status gr_sssp_batch_ex(const gr_graph *g, const int32_t *srcs, in
             for (int32_t i = 0; i < k; ++i) stats->rounds = std::max(stats->rounds, source_rounds(g, srcs[i]));
             stats->edges_pushed = stats->source_relaxations = tot.arcs;
             stats->frontier_sum = tot.items;
+        }
+        return s;
+    }
+    if (wants_order(g, nullptr)) {
+        if (k >= kOrderLanesMin) return run_batch_order(g, srcs, k, rows.data(), st, stats);
+        std::vector<const gr_graph *> gs((size_t)k, g);
+        const unsigned long long *x = nullptr;
+        int64_t launches = 0;
+        s = run_order(gs.data(), srcs, k, rows.data(), g->plain.wt, st, &x, &launches, nullptr);
+        if (s == GR_OK && stats) {
+            *stats = gr_multi_stats{};
+            stats->replays = (int32_t)((launches + kMqRoundsPerReplay - 1) / kMqRoundsPerReplay);
+            for (int32_t i = 0; i < k; ++i, x += kOrderStatWords) {
+                stats->rounds = std::max(stats->rounds, (int32_t)x[1]);
+                stats->frontier_sum += (int64_t)x[3];
+                stats->edges_pushed += (int64_t)(x[4] + x[5]);
+            }
+            stats->source_relaxations = stats->edges_pushed;
         }
         return s;
     }

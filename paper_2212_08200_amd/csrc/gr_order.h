@@ -53,6 +53,23 @@ constexpr int kOrderMaxJobs = 64;
 // else 1; rounds; pull rounds; frontier vertices; arcs pushed; arcs pulled.
 constexpr int kOrderStatWords = 6;
 
+// Batched queries on one graph: up to kBatchLanes sources, one per wave lane,
+// with the distances vertex-major (64 words per vertex).
+struct OrderBatch {
+    OrderJob g;               // the graph (dist, bits and src unused)
+    uint32_t *D;              // workspace: n x 64
+    int32_t k;
+    unsigned long long *mask;  // workspace: 3 x n, the sources whose frontier holds a vertex, by round mod 3
+    uint32_t *mu;             // workspace: 3 x kOrderRegions x 64 complements of each source's mu
+};
+constexpr int kOrderBatchStatWords = 6;  // 0 / 1, rounds, pull rounds, frontier vertices, arcs read, (arc, source) pairs decided
+
+size_t order_batch_bytes(int32_t n);
+void order_batch_carve(OrderBatch *b, void *ws);
+hipError_t order_batch_begin(const OrderBatch &b, const int32_t *srcs, int wt, hipStream_t st);
+hipError_t order_batch_rounds(const OrderBatch &b, int wt, int64_t first, int32_t rounds, int num_cu,
+                              unsigned long long *stat, hipStream_t st);
+
 size_t order_ws_bytes(int32_t n);
 // Fills j's workspace pointers from ws.
 void order_carve(OrderJob *j, void *ws);

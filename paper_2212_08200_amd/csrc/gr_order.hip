@@ -436,6 +436,377 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
     }
 }
 
+// ---- batched queries -----------------------------------------------------------
+
+// The same rounds for up to 64 sources of one graph, a source per lane and the
+// distances vertex-major, so that an arc costs one 256-byte row: a pull reads a
+// vertex's arcs while they can still improve any of its lanes.  Bound by those
+// rows (L2 and memory) and by the instructions per arc, hence scalar loads of
+// the graph, a saturating add and one comparison per arc, and rows read through
+// a scalar base.  A pull doesn't ask whether a tail is on the frontier: the
+// row's newer distances help the lanes along, 17 M arcs read instead of 38 M.
+// 64 sources on a scale-20 R-MAT graph of 32 M arcs: 2.00 ms, of which 0.16
+// transposes the output (the queue-driven push rounds of the session kernels
+// took 11.4 ms); 0.55 ms at scale 15 (1.41).
+struct OrderBatchArgs {
+    OrderBatch b;
+    int64_t round;
+    unsigned long long *stat;
+};
+constexpr int kRgPairs = 6;   // region: (arc, source) pairs of the frontier
+constexpr int kStPairs = 6;   // state: their total
+constexpr int kBatchVerts = 4;   // vertices in flight per wave
+constexpr int kBatchArcs = 4;   // arcs of a row in flight (2000 us for the 64 queries below, 2066 with 8)
+constexpr int kBatchRun = 64;   // arcs per queue entry
+
+struct BatchBeginArgs {
+    OrderBatch b;
+    int32_t src[kBatchLanes];
+};
+
+// (lanes without a source hold 0: nothing improves them)
+__global__ __launch_bounds__(256) void k_order_batch_clear(OrderBatch b, uint32_t inf) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;  // (a multiple of 16)
+    const int l = (int)(t % (kBatchLanes / 4)) * 4;
+    const int k = b.k;
+    const u32x4 x = u32x4{l < k ? inf : 0u, l + 1 < k ? inf : 0u, l + 2 < k ? inf : 0u, l + 3 < k ? inf : 0u};
+    for (int64_t i = t; i < (int64_t)b.g.n * (kBatchLanes / 4); i += step) reinterpret_cast<u32x4 *>(b.D)[i] = x;
+    for (int64_t i = t; i < 3 * (int64_t)b.g.n; i += step) b.mask[i] = 0ull;
+    for (int64_t i = t; i < 3 * kOrderRegions * 64; i += step) b.mu[i] = 0u;
+    for (int64_t i = t; i < kOrderCtlWords; i += step) b.g.ctl[i] = 0ull;
+}
+
+// One wave, a source per lane (repeated sources share an entry).
+__global__ __launch_bounds__(64) void k_order_batch_begin(BatchBeginArgs a) {
+    const int lane = threadIdx.x;
+    unsigned long long *ctl = a.b.g.ctl;
+    const bool mine = lane < a.b.k;
+    const int32_t s = a.src[mine ? lane : 0];
+    const int32_t deg = a.b.g.ro[s + 1] - a.b.g.ro[s];
+    bool first = mine && deg > 0;
+    for (int j = 0; j < a.b.k; ++j) first = first && !(j < lane && a.src[j] == s);
+    const uint32_t runs = first ? (uint32_t)((deg + kBatchRun - 1) / kBatchRun) : 0u;
+    uint32_t upto = runs;
+    unsigned long long E = first ? (unsigned long long)deg : 0ull, pairs = mine ? (unsigned long long)deg : 0ull;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t x = (uint32_t)__shfl_up((int)upto, o, 64);
+        if (lane >= o) upto += x;
+        E += __shfl_xor(E, o, 64);
+        pairs += __shfl_xor(pairs, o, 64);
+    }
+    const uint32_t all = (uint32_t)__shfl((int)upto, 63, 64);
+    const int F = (int)__popcll(__ballot(first));
+    const bool fits = all <= (uint32_t)a.b.g.cap;
+    if (mine) {
+        a.b.D[(size_t)s * kBatchLanes + lane] = 0u;
+        atomicOr(a.b.mask + s, 1ull << lane);
+        a.b.mu[lane] = 0xFFFFFFFFu;
+    }
+    if (fits)
+        for (uint32_t i0 = 0; i0 < all; i0 += 64) {
+            const uint32_t i = i0 + lane;
+            int j = 0;  // the source whose run i is
+            for (int k = 0; k + 1 < a.b.k; ++k) j += (uint32_t)__shfl((int)upto, k, 64) <= i ? 1 : 0;
+            const uint32_t before = (uint32_t)__shfl((int)(upto - runs), j, 64);
+            if (i < all) a.b.g.queue[i] = make_uint2((uint32_t)a.src[j], i - before);
+        }
+    if (lane == 0) {
+        ctl[kRgF] = (unsigned long long)F;
+        ctl[kRgE] = E;
+        ctl[kRgCnt] = fits ? all : 0ull;
+        ctl[kRgFlags] = fits ? 0ull : kFlagOver;
+        ctl[kRgPairs] = pairs;
+    }
+}
+
+template <typename T>
+using cptr = const T __attribute__((address_space(4))) *;  // read-only: uniform loads are scalar ones
+template <typename T>
+__device__ __forceinline__ cptr<T> to_constant(const T *p) {
+    return (cptr<T>)p;
+}
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t arcs_vec __attribute__((ext_vector_type(2 * kBatchArcs), aligned(8)));
+
+// d (+) w in one or two instructions (INF, the largest value, stays).
+template <int WT>
+__device__ __forceinline__ uint32_t plus_sat(uint32_t d, uint32_t w) {
+    if constexpr (WT == 0) return __builtin_elementwise_add_sat(d, w);
+    else return __float_as_uint(fminf(__uint_as_float(d) + __uint_as_float(w), __uint_as_float(kInfF32)));
+}
+// mu (+) w < best, for room = room_of(mu, best): one comparison for uint32.
+template <int WT>
+__device__ __forceinline__ uint32_t room_of(uint32_t mu, uint32_t best) {
+    if constexpr (WT == 0) return __builtin_elementwise_sub_sat(best, mu);
+    else return best;
+}
+template <int WT>
+__device__ __forceinline__ bool in_room(uint32_t mu, uint32_t w, uint32_t room) {
+    if constexpr (WT == 0) return w < room;
+    else return __uint_as_float(mu) + __uint_as_float(w) < __uint_as_float(room);
+}
+
+template <int WT>
+__global__ __launch_bounds__(256, 8) void k_order_batch(OrderBatchArgs g) {
+    const OrderJob &J = g.b.g;
+    const int t = threadIdx.x, lane = t & 63;
+    gptr<unsigned long long> ctl = to_global(J.ctl);
+    const int32_t n = J.n;
+    const int s0 = (int)(g.round % 3), s1 = (int)((g.round + 1) % 3), s2 = (int)((g.round + 2) % 3);
+    constexpr int slot_words = kOrderRegions * kOrderRegionWords;
+    const Totals T = read_slot(ctl + s0 * slot_words);
+    const bool pull = T.flags != 0ull || kOrderBias * (double)T.E * (double)T.E >= (double)n * (double)J.m;
+    gptr<uint32_t> mus = to_global(g.b.mu);
+    if (blockIdx.x == 0) {
+        for (int i = t; i < slot_words; i += 256) ctl[s2 * slot_words + i] = 0ull;
+        for (int i = t; i < kOrderRegions * 64; i += 256) mus[s2 * kOrderRegions * 64 + i] = 0u;
+    }
+    const int rg = (int)(blockIdx.x % kOrderRegions);
+    gptr<unsigned long long> region = ctl + s1 * slot_words + rg * kOrderRegionWords;
+    if (blockIdx.x == 0 && t == 0) {
+        gptr<unsigned long long> state = ctl + kOrderState;
+        for (int i = 0; i < kOrderRegions; ++i) {
+            state[kStPulledArcs] += ctl[s0 * slot_words + i * kOrderRegionWords + kRgRead];
+            state[kStPairs] += ctl[s0 * slot_words + i * kOrderRegionWords + kRgPairs];
+        }
+        if (T.F == 0ull) {
+            if (state[kStDone] == 0ull) {
+                state[kStDone] = 1ull;
+                const unsigned long long v[kOrderBatchStatWords] = {1ull, (unsigned long long)g.round, state[kStPulls],
+                                                                    state[kStF], state[kStPushed] + state[kStPulledArcs],
+                                                                    state[kStPairs]};
+#pragma unroll
+                for (int i = kOrderBatchStatWords - 1; i >= 0; --i)
+                    __hip_atomic_store(g.stat + i, v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+        } else {
+            state[kStF] += T.F;
+            if (pull) {
+                (void)__hip_atomic_fetch_or(region + kRgFlags, kFlagPulled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                state[kStPulls] += 1ull;
+            } else {
+                state[kStPushed] += T.E;
+            }
+        }
+    }
+    if (T.F == 0ull) return;
+    gptr<unsigned long long> mask = to_global(g.b.mask);
+    gptr<const unsigned long long> on = mask + (size_t)s0 * n;
+    gptr<unsigned long long> next = mask + (size_t)s1 * n;
+    gptr<uint32_t> D = to_global(g.b.D);
+    gptr<const int32_t> ro = to_global(J.ro);
+    __shared__ uint32_t sLow[kBatchLanes];
+    __shared__ uint32_t sNew, sRead;
+    __shared__ unsigned long long sPairs;
+    if (t < kBatchLanes) sLow[t] = 0u;
+    if (t == 0) {
+        sNew = sRead = 0u;
+        sPairs = 0ull;
+    }
+    __syncthreads();
+    uint32_t low = 0u;             // complement of this lane's smallest improvement
+    uint32_t nnew = 0, nread = 0;  // by wave, uniform
+    unsigned long long pairs = 0;
+    const auto row = [&](uint32_t v) { return D + (size_t)v * kBatchLanes + lane; };
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4u + (uint32_t)(t >> 6)));
+    const uint32_t waves = gridDim.x * 4u;
+    if (!pull) {
+        for (int64_t i = (int64_t)blockIdx.x * 256 + t; i < n; i += (int64_t)gridDim.x * 256)
+            mask[(size_t)s2 * n + i] = 0ull;
+        gptr<u32x2> queue = reinterpret_cast<gptr<u32x2>>(to_global(J.queue));
+        gptr<const u32x2> from = queue + (size_t)(g.round & 1) * kOrderRegions * J.cap;
+        gptr<u32x2> to = queue + ((size_t)((g.round + 1) & 1) * kOrderRegions + rg) * J.cap;
+        gptr<const u32x2> adj = reinterpret_cast<gptr<const u32x2>>(to_global(J.adj));
+        uint32_t mine = lane < kOrderRegions ? (uint32_t)ctl[s0 * slot_words + lane * kOrderRegionWords + kRgCnt] : 0u;
+        uint32_t upto = mine;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t x = (uint32_t)__shfl_up((int)upto, o, 64);
+            if (lane >= o) upto += x;
+        }
+        const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+        for (uint32_t i = wave; i < all; i += waves) {
+            const int q = (int)__popcll(__ballot(upto <= i));
+            const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)upto, q);
+            const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)mine, q);
+            u32x2 ent = from[(size_t)q * J.cap + (i - (end - cnt))];
+            ent.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)ent.x);
+            ent.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)ent.y);
+            // (a lane whose frontier has no such vertex: INF improves nothing)
+            const uint32_t du = on[ent.x] >> lane & 1ull
+                                    ? __hip_atomic_load(row(ent.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                    : (WT == 1 ? kInfF32 : kInfU32);
+            const int32_t e0 = ro[ent.x] + (int32_t)ent.y * kBatchRun, e1 = min(ro[ent.x + 1], e0 + kBatchRun);
+            const u32x2 a = adj[min(e0 + lane, e1 - 1)];
+            const int deg1 = __builtin_amdgcn_readfirstlane(e1 - e0);
+            unsigned long long won = 0ull;  // the lanes that this lane's arc improved
+            for (int j = 0; j < deg1; j += kBatchArcs) {
+                uint32_t nd[kBatchArcs], cur[kBatchArcs];
+#pragma unroll
+                for (int k = 0; k < kBatchArcs; ++k) {
+                    const int at = min(j + k, deg1 - 1);
+                    nd[k] = plus_sat<WT>(du, (uint32_t)__builtin_amdgcn_readlane((int)a.y, at));
+                    cur[k] = *row((uint32_t)__builtin_amdgcn_readlane((int)a.x, at));
+                }
+#pragma unroll
+                for (int k = 0; k < kBatchArcs; ++k) {
+                    // (another wave may be lower by now: then the vertex is on the frontier with its value)
+                    const bool win = nd[k] < cur[k];
+                    const unsigned long long b = __ballot(win);
+                    if (b == 0ull) continue;
+                    const int at = min(j + k, deg1 - 1);
+                    if (win) {
+                        (void)__hip_atomic_fetch_min(row((uint32_t)__builtin_amdgcn_readlane((int)a.x, at)), nd[k],
+                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        low = max(low, ~nd[k]);
+                    }
+                    if (lane == at) won |= b;
+                }
+            }
+            // (the lane holding the arc marks its head)
+            uint32_t runs = 0, deg = 0;
+            if (won != 0ull) {
+                const unsigned long long was =
+                    __hip_atomic_fetch_or(next + a.x, won, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                deg = (uint32_t)(ro[a.x + 1] - ro[a.x]);
+                pairs += (unsigned long long)__popcll(won & ~was) * deg;
+                if (was == 0ull) runs = (deg + kBatchRun - 1) / kBatchRun;
+            }
+            const unsigned long long fresh = __ballot(runs != 0u);
+            if (fresh == 0ull) continue;
+            uint32_t before = runs;
+            unsigned long long sum = runs ? deg : 0u;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t x = (uint32_t)__shfl_up((int)before, o, 64);
+                if (lane >= o) before += x;
+                sum += __shfl_xor(sum, o, 64);
+            }
+            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)before, 63);
+            unsigned long long base = 0;
+            if (lane == 0) {
+                base = __hip_atomic_fetch_add(region + kRgCnt, (unsigned long long)total, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+                (void)__hip_atomic_fetch_add(region + kRgE, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            nnew += (uint32_t)__popcll(fresh);
+            base = (unsigned long long)__shfl((long long)base, 0, 64);
+            if (base + total > (unsigned long long)J.cap) {  // the next round pulls
+                if (lane == 0)
+                    (void)__hip_atomic_fetch_or(region + kRgFlags, kFlagOver, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                continue;
+            }
+            const uint32_t at = (uint32_t)base + before - runs;
+            for (uint32_t r = 0; r < runs; ++r) to[at + r] = u32x2{a.x, r};
+        }
+    } else {
+        cptr<int32_t> ri = to_constant(J.ro_in), rc = to_constant(J.ro);
+        cptr<uint2> arc = to_constant(J.arc);
+        uint32_t mu = 0u;
+#pragma unroll
+        for (int i = 0; i < kOrderRegions; ++i) mu = max(mu, mus[(s0 * kOrderRegions + i) * 64 + lane]);
+        // (INF for a lane whose frontier is empty: its arcs are all ruled out)
+        mu = min(~mu, WT == 1 ? kInfF32 : kInfU32);
+        // the arcs [e, e1) of a row, in order of weight, against the lanes' best
+        const auto walk = [&](int32_t e, int32_t e1, uint32_t &best) {
+            for (; e < e1; e += kBatchArcs) {
+                const arcs_vec a = *(cptr<arcs_vec>)(arc + e);  // (past the last row: the table after the arcs)
+                const uint32_t room = room_of<WT>(mu, best);
+                uint32_t d[kBatchArcs];
+                bool in[kBatchArcs];
+#pragma unroll
+                for (int k = 0; k < kBatchArcs; ++k) {
+                    in[k] = e + k < e1 && __ballot(in_room<WT>(mu, a[2 * k + 1], room)) != 0ull;
+                    if (in[k]) d[k] = *row(a[2 * k]);
+                }
+#pragma unroll
+                for (int k = 0; k < kBatchArcs; ++k)
+                    if (in[k]) {
+                        best = min(best, plus_sat<WT>(d[k], a[2 * k + 1]));
+                        ++nread;
+                    }
+                if (!in[kBatchArcs - 1]) return;  // out for every lane: so are those after it
+            }
+        };
+        for (uint32_t v0 = wave * kBatchVerts; v0 < (uint32_t)n; v0 += waves * kBatchVerts) {
+            const u32x8 a0 = *(cptr<u32x8>)(to_constant(J.a0) + v0), a1 = *(cptr<u32x8>)(to_constant(J.a1) + v0);
+            const u32x4 w2 = *(cptr<u32x4>)(to_constant(J.w2) + v0);
+            uint32_t b[kBatchVerts], best[kBatchVerts], d0[kBatchVerts], d1[kBatchVerts];
+            bool has[kBatchVerts], in0[kBatchVerts], in1[kBatchVerts];
+#pragma unroll
+            for (int k = 0; k < kBatchVerts; ++k) {
+                has[k] = v0 + k < (uint32_t)n && a0[2 * k] != kOrderNone;
+                if (has[k]) b[k] = *row(v0 + k);
+            }
+#pragma unroll
+            for (int k = 0; k < kBatchVerts; ++k) {
+                in0[k] = in1[k] = false;
+                if (has[k]) {
+                    const uint32_t room = room_of<WT>(mu, b[k]);
+                    in0[k] = __ballot(in_room<WT>(mu, a0[2 * k + 1], room)) != 0ull;
+                    in1[k] = in0[k] && a1[2 * k] != kOrderNone && __ballot(in_room<WT>(mu, a1[2 * k + 1], room)) != 0ull;
+                }
+                if (in0[k]) d0[k] = *row(a0[2 * k]);
+                if (in1[k]) d1[k] = *row(a1[2 * k]);
+            }
+#pragma unroll
+            for (int k = 0; k < kBatchVerts; ++k) {
+                if (!in0[k]) continue;
+                ++nread;
+                best[k] = min(b[k], plus_sat<WT>(d0[k], a0[2 * k + 1]));
+                if (in1[k]) {
+                    ++nread;
+                    best[k] = min(best[k], plus_sat<WT>(d1[k], a1[2 * k + 1]));
+                    if (__ballot(in_room<WT>(mu, w2[k], room_of<WT>(mu, best[k]))) != 0ull)
+                        walk(ri[v0 + k] + 2, ri[v0 + k + 1], best[k]);
+                }
+                const bool won = best[k] < b[k];
+                const unsigned long long w = __ballot(won);
+                if (w == 0ull) continue;
+                if (won) {
+                    *row(v0 + k) = best[k];
+                    low = max(low, ~best[k]);
+                }
+                const unsigned long long x = (unsigned long long)__popcll(w) * (uint32_t)(rc[v0 + k + 1] - rc[v0 + k]);
+                pairs += lane == 0 ? x : 0ull;
+                ++nnew;
+            }
+        }
+        // long rows: a wave per chunk
+        for (uint32_t c = wave; c < (uint32_t)J.nchunks; c += waves) {
+            const u32x4 ch = *(cptr<u32x4>)(to_constant(J.chunk) + c);
+            const uint32_t b = __hip_atomic_load(row(ch.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            uint32_t best = b;
+            walk((int32_t)ch.y, (int32_t)ch.z, best);
+            bool won = best < b;
+            if (won)
+                won = best < __hip_atomic_fetch_min(row(ch.x), best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long w = __ballot(won);
+            if (w == 0ull) continue;
+            if (won) low = max(low, ~best);
+            const unsigned long long x = (unsigned long long)__popcll(w) * (uint32_t)(rc[ch.x + 1] - rc[ch.x]);
+            pairs += lane == 0 ? x : 0ull;
+            ++nnew;
+        }
+    }
+    if (low != 0u) atomicMax(&sLow[lane], low);
+    if (lane == 0 && nnew) atomicAdd(&sNew, nnew);
+    if (lane == 0 && nread) atomicAdd(&sRead, nread);
+    if (pairs) atomicAdd(&sPairs, pairs);
+    __syncthreads();
+    if (t < kBatchLanes && sLow[t] != 0u)
+        (void)__hip_atomic_fetch_max(mus + (s1 * kOrderRegions + rg) * 64 + t, sLow[t], __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+    if (t == 0) {
+        if (sNew) (void)__hip_atomic_fetch_add(region + kRgF, (unsigned long long)sNew, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (sRead) (void)__hip_atomic_fetch_add(region + kRgRead, (unsigned long long)sRead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (sPairs) (void)__hip_atomic_fetch_add(region + kRgPairs, sPairs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 // ---- layout ------------------------------------------------------------------
 
 // Rows of up to 64 arcs: a wave each, sorted across its lanes.
@@ -627,6 +998,56 @@ hipError_t order_rounds(const OrderJob *jobs, int32_t k, int wt, const OrderJob 
         if (wt == 0) hipLaunchKernelGGL((k_order<0>), grid, blk, 0, st, a);
         else if (wt == 1) hipLaunchKernelGGL((k_order<1>), grid, blk, 0, st, a);
         else hipLaunchKernelGGL((k_order<2>), grid, blk, 0, st, a);
+    }
+    return hipGetLastError();
+}
+
+size_t order_batch_bytes(int32_t n) {
+    return al256(kOrderCtlWords * 8) + al256(3 * kOrderRegions * 64 * 4) + al256((size_t)n * kBatchLanes * 4) +
+           al256(3 * (size_t)n * 8) + al256(2 * (size_t)kOrderRegions * (size_t)queue_cap(n) * sizeof(uint2));
+}
+
+void order_batch_carve(OrderBatch *b, void *ws) {
+    char *p = static_cast<char *>(ws);
+    const size_t n = (size_t)b->g.n;
+    b->g.ctl = reinterpret_cast<unsigned long long *>(p);
+    p += al256(kOrderCtlWords * 8);
+    b->mu = reinterpret_cast<uint32_t *>(p);
+    p += al256(3 * kOrderRegions * 64 * 4);
+    b->D = reinterpret_cast<uint32_t *>(p);
+    p += al256(n * kBatchLanes * 4);
+    b->mask = reinterpret_cast<unsigned long long *>(p);
+    p += al256(3 * n * 8);
+    b->g.cap = queue_cap(b->g.n);
+    b->g.queue = reinterpret_cast<uint2 *>(p);
+}
+
+hipError_t order_batch_begin(const OrderBatch &b, const int32_t *srcs, int wt, hipStream_t st) {
+    const int32_t k = b.k;
+    if (k < 1 || k > kBatchLanes || wt < 0 || wt > 1 || b.g.n < 1 || !b.g.arc || !b.D) return hipErrorInvalidValue;
+    BatchBeginArgs a{};
+    a.b = b;
+    for (int32_t i = 0; i < k; ++i) {
+        if (srcs[i] < 0 || srcs[i] >= b.g.n) return hipErrorInvalidValue;
+        a.src[i] = srcs[i];
+    }
+    const unsigned blocks = (unsigned)std::min<int64_t>(((int64_t)b.g.n + 15) / 16, 4096);
+    hipLaunchKernelGGL(k_order_batch_clear, dim3(blocks), dim3(256), 0, st, b, wt == 1 ? kInfF32 : kInfU32);
+    hipLaunchKernelGGL(k_order_batch_begin, dim3(1), dim3(64), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t order_batch_rounds(const OrderBatch &b, int wt, int64_t first, int32_t rounds, int num_cu,
+                              unsigned long long *stat, hipStream_t st) {
+    // one block per 16 vertices, or four times the blocks that the chip holds
+    // (rows differ in length: 2061 us for 64 sources of a scale-20 R-MAT graph,
+    // 2182 with just what it holds, 2330 with eight times as many)
+    const int64_t blocks = std::min<int64_t>(((int64_t)b.g.n + 4 * kBatchVerts - 1) / (4 * kBatchVerts), (int64_t)num_cu * 32);
+    OrderBatchArgs a{b, 0, stat};
+    for (int32_t r = 0; r < rounds; ++r) {
+        a.round = first + r;
+        if (wt == 0) hipLaunchKernelGGL((k_order_batch<0>), dim3((unsigned)blocks), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((k_order_batch<1>), dim3((unsigned)blocks), dim3(256), 0, st, a);
     }
     return hipGetLastError();
 }

@@ -143,3 +143,24 @@ def test_ordered_multi_and_server():
     finally:
         for G in Gs:
             G.close()
+
+
+@pytest.mark.parametrize("k", [2, 17, 64])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_ordered_batch(name, k):
+    g = CASES[name]()
+    # repeated sources, and one without arcs where the graph has it
+    srcs = np.asarray(([0, g.n - 1] + [int(x) for x in gg.pick_sources(g, 3, 29)] * 3)[:k], np.int32)
+    print("ordered batch %s n=%d m=%d k=%d" % (name, g.n, g.m, k), file=sys.stderr, flush=True)
+    want = {int(s): oracle.dijkstra(g, int(s)) for s in set(srcs.tolist())}
+    with gr.Graph.from_csr(g) as G:
+        d = torch.empty(k, g.n, dtype=torch.int32, device="cuda")
+        for rep in range(2):
+            d.fill_(0x5A5A5A5A)
+            st = gr.gr_sssp_batch_ex(G.handle, srcs, d)
+            torch.cuda.synchronize()
+            got = d.cpu().numpy().view(np.uint32)
+            for i, s in enumerate(srcs):
+                np.testing.assert_array_equal(got[i], want[int(s)], err_msg="row %d, source %d" % (i, s))
+        arcs = int(np.diff(g.ro)[srcs].sum())  # (sources without arcs alone: no rounds)
+        assert st["replays"] >= 1 and (st["rounds"] > 0) == (arcs > 0) and st["source_relaxations"] >= min(arcs, st["rounds"])
