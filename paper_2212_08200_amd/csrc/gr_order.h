@@ -39,7 +39,7 @@ struct OrderJob {
     const uint32_t *w2;
     const uint4 *chunk;
     uint32_t *dist;         // the query's output, n values
-    uint64_t *bits;         // workspace: 3 frontier bitmaps of nword words, by round mod 3
+    uint64_t *bits;         // workspace: 2 bitmaps of nword words, of what a push put on the next frontier
     uint2 *queue;           // workspace: 2 x kOrderRegions x cap frontier entries, by round parity
     unsigned long long *ctl;  // workspace: kOrderCtlWords
     int32_t n, m, nchunks, src, nword, cap;

@@ -9,25 +9,34 @@
 // the smallest distance that the round before improved, an arc (u, v, w) can
 // only improve v if mu (+) w < dist[v], so v's arcs are read in order of weight
 // until that fails -- one or two arcs per vertex and round (R-MAT 20: 15 M arcs
-// read in 18 rounds).  (+) is monotone in both operands, so what is not read
+// read in 19 rounds).  (+) is monotone in both operands, so what is not read
 // could not have improved v: mu (+) w <= dist[u] (+) w for every u that the
 // round before improved, and a u improved earlier was read then or was ruled
-// out then.  Of the arcs read, only those whose tail's bit is set need its
-// distance.
+// out then.  Whether a tail is on the frontier is not asked: a pull keeps no
+// bitmap, and a distance lowered earlier in the same round counts at once
+// (against testing the tails' bits first, R-MAT 22: 929-1253 -> 817-1082 us,
+// 31-48 -> 25-42 M arcs; 20: 621-724 -> 583-669; uniform of 200,000 vertices:
+// 537-566 -> 475-501; 15: 203-232 -> 193-219).
+//
+// Bound by the chain of dependent loads in a round (its counters, a vertex, its
+// tails, its row, the tails again: 17-20 us at 200,000 to 1 M vertices, 6 us at
+// 32 K) and, in the first pulls, by their random 64-byte sectors.  Measured
+// against the push-only rounds: R-MAT 15, 432 -> 193 us; 20 (binary32), 1925 ->
+// 620; 22, 3421 -> 890.
 //
 // A pull round reads every vertex's distance and lightest weight (streamed),
 // so small frontiers are pushed instead, from a queue of (vertex, run of 256
 // arcs) entries: a round pushes while its frontier is small (kOrderBias) and
 // the queue held it, and once a round has pulled all later ones do (a pull
-// writes no queue: its frontier exists as a bitmap only).
+// writes no queue).
 //
 // One launch is one round of every query in it; the launches of a query are
 // enqueued ahead, each reads the state that the round before left, and those
 // past the end return at once.  State: three slots of counters rotated over the
 // rounds, each in kOrderRegions regions on 256-byte lines of their own (memory-
 // side atomics to one line are serialised: a block adds to region blockIdx mod
-// kOrderRegions), summed by every block at its start; three bitmaps, rotated
-// likewise (one read, one written, one cleared per round).
+// kOrderRegions), summed by every block at its start; two bitmaps of what a
+// push put on the next frontier (one written, one cleared).
 #include "gr_order.h"
 
 #include <algorithm>
@@ -104,8 +113,7 @@ __global__ __launch_bounds__(256) void k_order_begin(BeginArgs a) {
     const OrderJob j = a.job[blockIdx.y];
     const int32_t t = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
     for (int64_t i = t; i < j.n; i += step) j.dist[i] = i == j.src ? 0u : a.inf;
-    for (int64_t i = t; i < 3 * (int64_t)j.nword; i += step)
-        j.bits[i] = i == (j.src >> 6) ? 1ull << (j.src & 63) : 0ull;
+    for (int64_t i = t; i < 2 * (int64_t)j.nword; i += step) j.bits[i] = 0ull;
     const int32_t deg = j.ro[j.src + 1] - j.ro[j.src], runs = (deg + kPushRun - 1) / kPushRun;
     // round 0's counters (region 0); mu = 0, complemented
     const bool fits = runs <= j.cap;
@@ -217,7 +225,7 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
     constexpr int slot_words = kOrderRegions * kOrderRegionWords;
     const Totals T = read_slot(ctl + s0 * slot_words);
     const bool pull = T.flags != 0ull || kOrderBias * (double)T.E * (double)T.E >= (double)n * (double)J.m;
-    // the slot and the bitmap of the round after next
+    // the slot of the round after next
     if (blockIdx.x == 0)
         for (int i = t; i < slot_words; i += 256) ctl[s2 * slot_words + i] = 0ull;
     gptr<unsigned long long> region = ctl + s1 * slot_words + (blockIdx.x % kOrderRegions) * kOrderRegionWords;
@@ -246,10 +254,7 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
         }
     }
     if (T.F == 0ull) return;
-    gptr<unsigned long long> bits = reinterpret_cast<gptr<unsigned long long>>(to_global(J.bits));
-    gptr<unsigned long long> next_bits = bits + (size_t)s1 * J.nword;
     gptr<uint32_t> dist = to_global(J.dist);
-    for (int32_t i = blockIdx.x * 256 + t; i < J.nword; i += gridDim.x * 256) bits[(size_t)s2 * J.nword + i] = 0ull;
     __shared__ uint32_t sLow, sCnt, sArcs, sRead;
     if (t == 0) {
         sLow = 0xFFFFFFFFu;
@@ -258,6 +263,10 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
     uint32_t lowest = 0xFFFFFFFFu, nread = 0, nnew = 0;
     const int32_t vblocks = (n + kOrderVerts - 1) / kOrderVerts;
     if (!pull) {
+        gptr<unsigned long long> bits = reinterpret_cast<gptr<unsigned long long>>(to_global(J.bits));
+        gptr<unsigned long long> next_bits = bits + (size_t)((g.round + 1) & 1) * J.nword;
+        for (int32_t i = blockIdx.x * 256 + t; i < J.nword; i += gridDim.x * 256)
+            bits[(size_t)(g.round & 1) * J.nword + i] = 0ull;
         gptr<u32x2> queue = reinterpret_cast<gptr<u32x2>>(to_global(J.queue));
         gptr<const u32x2> from = queue + (size_t)(g.round & 1) * kOrderRegions * J.cap;
         gptr<u32x2> to = queue + ((size_t)((g.round + 1) & 1) * kOrderRegions + blockIdx.x % kOrderRegions) * J.cap;
@@ -280,21 +289,19 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
         }
         __syncthreads();
     } else {
-        gptr<const uint32_t> on = reinterpret_cast<gptr<const uint32_t>>(bits + (size_t)s0 * J.nword);
         gptr<const u32x2> arc = reinterpret_cast<gptr<const u32x2>>(to_global(J.arc));
         const uint32_t mu = T.mu;
         const auto step = [](uint32_t d, uint32_t w) { return plus<WT>(d, w); };
-        __shared__ uint32_t sList[kOrderVerts], sBest[kOrderVerts];
-        __shared__ unsigned long long sNew[kOrderVerts / 64];
+        __shared__ uint32_t sList[kOrderVerts], sWas[kOrderVerts], sBest[kOrderVerts];
         for (int32_t vb = blockIdx.x; vb < vblocks; vb += gridDim.x) {
             if (t == 0) sCnt = 0u;
             __syncthreads();
             // the two lightest arcs: every load of a vertex is issued at once,
-            // then the tails' bits, then their distances
+            // then the tails' distances
             constexpr int V = kOrderVerts / 256;
-            uint32_t b[V], best[V], on0[V], on1[V];
+            uint32_t b[V], best[V], d0[V], d1[V];
             u32x2 a0[V], a1[V];
-            bool in0[V], in1[V], row[V];
+            bool in0[V], in1[V];
 #pragma unroll
             for (int k = 0; k < V; ++k) {
                 const int32_t v = min(vb * kOrderVerts + k * 256 + t, n - 1);
@@ -308,53 +315,43 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
                 // (absent arcs: weight INF, and no tail)
                 in0[k] = ok && a0[k].x != kOrderNone && step(mu, a0[k].y) < b[k];
                 in1[k] = in0[k] && a1[k].x != kOrderNone && step(mu, a1[k].y) < b[k];
-                if (in0[k]) on0[k] = on[a0[k].x >> 5];
-                if (in1[k]) on1[k] = on[a1[k].x >> 5];
+                if (in0[k]) d0[k] = dist[a0[k].x];
+                if (in1[k]) d1[k] = dist[a1[k].x];
             }
 #pragma unroll
             for (int k = 0; k < V; ++k) {
                 nread += (in0[k] ? 1u : 0u) + (in1[k] ? 1u : 0u);
                 best[k] = b[k];
-                row[k] = in1[k];
-                in0[k] = in0[k] && (on0[k] >> (a0[k].x & 31u) & 1u) != 0u;
-                in1[k] = in1[k] && (on1[k] >> (a1[k].x & 31u) & 1u) != 0u;
-                if (in0[k]) on0[k] = dist[a0[k].x];
-                if (in1[k]) on1[k] = dist[a1[k].x];
-            }
-#pragma unroll
-            for (int k = 0; k < V; ++k) {
-                if (in0[k]) best[k] = min(best[k], step(on0[k], a0[k].y));
-                if (in1[k]) best[k] = min(best[k], step(on1[k], a1[k].y));
+                if (in0[k]) best[k] = min(best[k], step(d0[k], a0[k].y));
+                if (in1[k]) best[k] = min(best[k], step(d1[k], a1[k].y));
                 // the others, below, for the vertices they may still improve
-                row[k] = row[k] && step(mu, a1[k].y) < best[k];
+                bool row = in1[k] && step(mu, a1[k].y) < best[k];
                 const int i = k * 256 + t;
                 const int32_t v = vb * kOrderVerts + i;
-                if (row[k]) row[k] = step(mu, to_global(J.w2)[v]) < best[k];
-                const unsigned long long m = __ballot(row[k]);
+                if (row) row = step(mu, to_global(J.w2)[v]) < best[k];
+                const unsigned long long m = __ballot(row);
                 if (m != 0ull) {
                     uint32_t at = 0;
                     if (lane == 0) at = atomicAdd(&sCnt, (uint32_t)__popcll(m));
                     at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-                    if (row[k]) {
+                    if (row) {
                         sList[at] = (uint32_t)i;
+                        sWas[at] = b[k];
                         sBest[at] = best[k];
                     }
                 }
-                const bool won = !row[k] && best[k] < b[k];
-                if (won) {
+                if (!row && best[k] < b[k]) {
                     dist[v] = best[k];
                     lowest = min(lowest, best[k]);
+                    ++nnew;
                 }
-                const unsigned long long x = __ballot(won);
-                if (lane == 0) sNew[i >> 6] = x;
             }
             __syncthreads();
             // eight lanes per vertex: a line of eight arcs at a time
             const uint32_t cnt = sCnt;
             gptr<const int32_t> ro = to_global(J.ro_in);
             for (uint32_t k = (uint32_t)t >> 3; k < cnt; k += 32u) {
-                const uint32_t i = sList[k];
-                const int32_t v = vb * kOrderVerts + (int32_t)i;
+                const int32_t v = vb * kOrderVerts + (int32_t)sList[k];
                 uint32_t low = sBest[k];
                 const int32_t e0 = ro[v] + 2, e1 = ro[v + 1];
                 for (int32_t e = e0; e < e1; e += 8) {
@@ -364,7 +361,7 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
                     uint32_t c = low;
                     if (in) {
                         ++nread;
-                        if (on[a.x >> 5] >> (a.x & 31u) & 1u) c = min(c, step(dist[a.x], a.y));
+                        c = min(c, step(dist[a.x], a.y));
                     }
 #pragma unroll
                     for (int o = 1; o < 8; o <<= 1) c = min(c, (uint32_t)__shfl_xor((int)c, o, 8));
@@ -372,18 +369,12 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
                     // the last of the eight still counts: the next eight may
                     if (!(__ballot(in && step(mu, a.y) < low) >> ((lane & 56) + 7) & 1ull)) break;
                 }
-                // (the block read dist[v] before, and only it writes it)
-                if ((t & 7) == 0 && low < dist[v]) {
+                // (only this block writes dist[v])
+                if ((t & 7) == 0 && low < sWas[k]) {
                     dist[v] = low;
                     lowest = min(lowest, low);
-                    (void)atomicOr(&sNew[i >> 6], 1ull << (i & 63));
+                    ++nnew;
                 }
-            }
-            __syncthreads();
-            if (t < kOrderVerts / 64 && sNew[t] != 0ull) {
-                nnew += (uint32_t)__popcll(sNew[t]);
-                (void)__hip_atomic_fetch_or(next_bits + vb * (kOrderVerts / 64) + t, sNew[t], __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_AGENT);
             }
             __syncthreads();
         }
@@ -403,7 +394,7 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
                 uint32_t c1 = low;
                 if (in) {
                     ++nread;
-                    if (on[a.x >> 5] >> (a.x & 31u) & 1u) c1 = min(c1, step(dist[a.x], a.y));
+                    c1 = min(c1, step(dist[a.x], a.y));
                 }
 #pragma unroll
                 for (int o = 1; o < 16; o <<= 1) c1 = min(c1, (uint32_t)__shfl_xor((int)c1, o, 16));
@@ -414,8 +405,6 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
                 low < __hip_atomic_fetch_min(dist + ch.x, low, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
                 lowest = min(lowest, low);
                 ++nnew;
-                (void)__hip_atomic_fetch_or(next_bits + (ch.x >> 6), 1ull << (ch.x & 63u), __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_AGENT);
             }
         }
     }
@@ -947,7 +936,7 @@ hipError_t order_build(OrderSet *out, int32_t n, int32_t m, const int32_t *ro_in
 }
 
 size_t order_ws_bytes(int32_t n) {
-    return al256(kOrderCtlWords * 8) + al256(3 * (size_t)bit_words(n) * 8) +
+    return al256(kOrderCtlWords * 8) + al256(2 * (size_t)bit_words(n) * 8) +
            al256(2 * (size_t)kOrderRegions * (size_t)queue_cap(n) * sizeof(uint2));
 }
 
@@ -957,7 +946,7 @@ void order_carve(OrderJob *j, void *ws) {
     p += al256(kOrderCtlWords * 8);
     j->nword = bit_words(j->n);
     j->bits = reinterpret_cast<uint64_t *>(p);
-    p += al256(3 * (size_t)j->nword * 8);
+    p += al256(2 * (size_t)j->nword * 8);
     j->cap = queue_cap(j->n);
     j->queue = reinterpret_cast<uint2 *>(p);
 }
