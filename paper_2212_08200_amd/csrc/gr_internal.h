@@ -183,6 +183,9 @@ hipError_t launch_filter(const DevGraph &g, const Frontier &f, int64_t iter, uin
                          const uint32_t *dist, bool use_far, uint32_t threshold, hipStream_t st);
 // Device address of the counter slot filled by the filter of iteration `iter`.
 unsigned long long *counters_after(const Frontier &f, int64_t iter);
+// Copies a counter slot to `to` (pinned host memory, the slot's layout), then
+// stores tag in to[kSlotWords].
+hipError_t launch_report(const unsigned long long *slot, unsigned long long *to, unsigned long long tag, hipStream_t st);
 
 // Device-driven loop (cooperative launch).
 struct PersistentCfg {

@@ -1958,6 +1958,21 @@ static inline bool offsets32(const DevGraph &g) {
 
 static inline int slot_of(int64_t i) { return (int)(((i % kCtlSlots) + kCtlSlots) % kCtlSlots); }
 
+// One wave, for the host-driven loop: it waits for the words of one round.
+static __global__ __launch_bounds__(64) void k_report(const unsigned long long *slot, unsigned long long *to,
+                                                      unsigned long long tag) {
+    const int t = threadIdx.x;
+    if (t < kSlotWords / kCtrStride)
+        __hip_atomic_store(to + t * kCtrStride, slot[t * kCtrStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+    if (t == 0) __hip_atomic_store(to + kSlotWords, tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+hipError_t launch_report(const unsigned long long *slot, unsigned long long *to, unsigned long long tag, hipStream_t st) {
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, st, slot, to, tag);
+    return hipGetLastError();
+}
+
 unsigned long long *counters_after(const Frontier &f, int64_t iter) { return f.ctl + slot_of(iter + 1) * kSlotWords; }
 
 void read_counts(const unsigned long long *h, FrontierCounts *c) {

@@ -240,8 +240,9 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
                 const unsigned long long v[kOrderStatWords] = {1ull, (unsigned long long)g.round, state[kStPulls],
                                                                state[kStF], state[kStPushed], state[kStPulledArcs]};
 #pragma unroll
-                for (int i = kOrderStatWords - 1; i >= 0; --i)
+                for (int i = 1; i < kOrderStatWords; ++i)
                     __hip_atomic_store(st + i, v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                __hip_atomic_store(st, v[0], __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);  // (the host polls it)
             }
         } else {
             state[kStF] += T.F;
@@ -568,8 +569,9 @@ __global__ __launch_bounds__(256, 8) void k_order_batch(OrderBatchArgs g) {
                                                                     state[kStF], state[kStPushed] + state[kStPulledArcs],
                                                                     state[kStPairs]};
 #pragma unroll
-                for (int i = kOrderBatchStatWords - 1; i >= 0; --i)
+                for (int i = 1; i < kOrderBatchStatWords; ++i)
                     __hip_atomic_store(g.stat + i, v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                __hip_atomic_store(g.stat, v[0], __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);  // (the host polls it)
             }
         } else {
             state[kStF] += T.F;
