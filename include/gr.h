@@ -139,10 +139,13 @@ gr_status gr_sssp(const gr_graph *g, int32_t src, void *dist_out, void *stream);
  *     frontier queue); a graph whose workspace exceeds the array returns
  *     GR_ERR_NO_CAPACITY before anything is enqueued.  Graphs of up to about
  *     five to seven million vertices fit.
- *   - Schedule: the queued (device-driven) loop over the plain CSR layout,
- *     without a near-far split; the direction, filter and relaxation-filter
- *     defaults are the graph's.  The call waits for `stream` once per chunk
- *     of launches and returns when the query has finished.
+ *   - Schedule: gr_sssp's when that is the single-workgroup loop, the loop
+ *     over tiles or the weight-ordered loop and the array holds its workspace
+ *     (64 bytes per tile and 4 per arc between tiles; at most 17 MB); else the
+ *     queued (device-driven) loop over the plain CSR layout, without a
+ *     near-far split; the direction, filter and relaxation-filter defaults are
+ *     the graph's.  The call waits for `stream` once per chunk of launches and
+ *     returns when the query has finished.
  *   - The current device must be the graph's device (GR_ERR_INVALID_ARG).
  *   - Every call on one GPU shares that GPU's array, which keeps the last
  *     call's contents (each call clears what it reads first).  Calls that

@@ -1539,6 +1539,65 @@ static gr_status run_queued_fixed(const gr_graph *g, int32_t src, uint32_t *dist
     return GR_OK;
 }
 
+// The graph's own loop (single-workgroup, tiles, weight-ordered arcs) for a
+// caller that cannot allocate: workspace and statistics in the fixed array ws,
+// read back with copies.  False in *ran when the graph has none, or the array
+// is too small for it.
+static gr_status run_own_fixed(const gr_graph *g, int32_t src, uint32_t *dist, hipStream_t st, const RunCfg &rc,
+                               void *ws, bool *ran) {
+    const DevGraph &dg = g->plain;
+    constexpr size_t kStat = 4096, kRoom = kNoAllocScratchBytes - kStat;
+    unsigned long long *stat = reinterpret_cast<unsigned long long *>(static_cast<char *>(ws) + kRoom);
+    unsigned long long h[4] = {};
+    const auto read = [&](const unsigned long long *from, int words) {
+        hipError_t e = hipMemcpyAsync(h, from, sizeof(unsigned long long) * words, hipMemcpyDeviceToHost, st);
+        return e == hipSuccess ? hipStreamSynchronize(st) : e;
+    };
+    *ran = true;
+    if (g->auto_loop == GR_LOOP_LDS) {
+        const LdsJob job{dg.ro, dg.adj, g->d_ell, dist, dg.n, dg.m, src, g->ell_lg};
+        HIP_TRY(launch_lds(&job, 1, GR_W_U32, (int64_t)dg.n + 1, stat, st));
+        HIP_TRY(read(stat, 2));
+        return h[1] == 1ull ? GR_OK : fail(GR_ERR_HIP, "single-workgroup loop ended in state %llu", h[1]);
+    }
+    const TileSet *set = &g->tiles;
+    if (wants_tiles(g, nullptr) && tile_ws_bytes(&set, 1) <= kRoom) {
+        DeviceInfo di;
+        gr_status s = device_info(g->device, &di);
+        if (s != GR_OK) return s;
+        const uint64_t spin = (uint64_t)rc.barrier_timeout_us * (uint64_t)di.wall_khz / 1000ull;
+        HIP_TRY(launch_tiles(&set, &src, &dist, 1, dg.wt, ws, di.num_cu, spin, stat, st));
+        HIP_TRY(read(stat, 1));
+        if (h[0] == 3ull)
+            return fail(GR_ERR_HIP, "tiled loop: a wait exceeded %lld us", (long long)rc.barrier_timeout_us);
+        return h[0] == 1ull ? GR_OK : fail(GR_ERR_HIP, "tiled loop ended in state %llu", h[0]);
+    }
+    const size_t table = al256(sizeof(OrderJob) * kOrderMaxJobs);
+    if (wants_order(g, nullptr) && table + order_ws_bytes(dg.n) <= kRoom) {
+        OrderJob j;
+        order_job(&j, g);
+        j.dist = dist;
+        j.src = src;
+        order_carve(&j, static_cast<char *>(ws) + table);
+        OrderJob *t = static_cast<OrderJob *>(ws);
+        HIP_TRY(order_begin(&j, 1, dg.wt, t, st));
+        int64_t done = 0, chunk = (int64_t)g->order_rounds.load(std::memory_order_relaxed) + 1;
+        while (h[0] == 0ull) {
+            if (done > (int64_t)dg.n + 2) return fail(GR_ERR_ITER_LIMIT, "the query ran past n + 1 rounds");
+            const int32_t c = (int32_t)std::min<int64_t>(chunk, 64);
+            HIP_TRY(order_rounds(&j, 1, dg.wt, t, done, c, stat, st));
+            done += c;
+            HIP_TRY(read(j.ctl + kOrderState, 1));  // (its first word: whether a launch found the end)
+            chunk = done > 64 ? 32 : 4;
+        }
+        HIP_TRY(read(stat, 2));
+        g->order_rounds.store((int32_t)std::min<unsigned long long>(h[1], 512), std::memory_order_relaxed);
+        return GR_OK;
+    }
+    *ran = false;
+    return GR_OK;
+}
+
 extern "C" gr_status gr_sssp_noalloc(const gr_graph *g, int32_t src, void *dist_out, void *stream) {
     if (!g) return fail(GR_ERR_INVALID_ARG, "graph is NULL");
     if (!dist_out) return fail(GR_ERR_INVALID_ARG, "dist_out is NULL");
@@ -1560,6 +1619,9 @@ extern "C" gr_status gr_sssp_noalloc(const gr_graph *g, int32_t src, void *dist_
                     kNoAllocScratchBytes);
     void *ws = nullptr;
     HIP_TRY(noalloc_scratch(&ws));
+    bool ran = false;
+    s = run_own_fixed(g, src, static_cast<uint32_t *>(dist_out), static_cast<hipStream_t>(stream), rc, ws, &ran);
+    if (ran || s != GR_OK) return s;
     return run_queued_fixed(g, src, static_cast<uint32_t *>(dist_out), static_cast<hipStream_t>(stream), rc, ws);
 }
 
