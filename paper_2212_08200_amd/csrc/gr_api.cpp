@@ -1182,7 +1182,7 @@ static gr_status run_tiled(const gr_graph *g, int32_t src, uint32_t *dist, hipSt
     return GR_OK;
 }
 
-static_assert(kOrderMaxJobs * kOrderStatWords * 8 <= 8192, "the statistics fit the pinned slot");
+static_assert(kOrderMaxJobs * kOrderStatWords * 8 <= 4096, "the statistics fit the pinned slot, and the fixed array's end");
 static void order_job(OrderJob *j, const gr_graph *g) {
     *j = OrderJob{};
     j->ro = g->d_ro;
@@ -1237,15 +1237,20 @@ static gr_status run_order(const gr_graph *const *graphs, const int32_t *srcs, i
         e = order_rounds(jobs, k, wt, table, done, c, hp, st);
         done += c;
         if (timed) (void)hipEventRecord(ev[1], st);
-        const auto finished = [&] {
-            for (int32_t i = 0; i < k; ++i)
-                if (pinned_load(hp + i * kOrderStatWords) == 0ull) return false;
+        // whether every query ended (or, with the chunk's mark, got past it)
+        const auto settled = [&](unsigned long long mark) {
+            for (int32_t i = 0; i < k; ++i) {
+                const unsigned long long x = pinned_load(hp + i * kOrderStatWords);
+                if (x != 1ull && x != mark) return false;
+            }
             return true;
         };
         // (every distance was stored by the launches before the one that finds
         // its frontier empty; the launches left in the stream do nothing)
-        if (e == hipSuccess) e = timed ? hipStreamSynchronize(st) : wait_pinned(st, finished);
-        const bool all = finished();
+        if (e == hipSuccess)
+            e = timed ? hipStreamSynchronize(st)
+                      : wait_pinned(st, [&] { return settled(2ull * (unsigned long long)done); });
+        const bool all = settled(1ull);
         over = !all && done > cap;
         if (all || over) break;
         chunk = done > 64 ? 32 : 4;
@@ -2184,8 +2189,12 @@ static gr_status run_batch_order(const gr_graph *g, const int32_t *srcs, int32_t
         const int32_t c = (int32_t)std::min<int64_t>(chunk, 64);
         e = order_batch_rounds(b, g->plain.wt, done, c, di.num_cu, hp, st);
         done += c;
-        if (e == hipSuccess) e = wait_pinned(st, [&] { return pinned_load(hp) != 0ull; });
-        const bool all = pinned_load(hp) != 0ull;
+        if (e == hipSuccess)
+            e = wait_pinned(st, [&] {
+                const unsigned long long x = pinned_load(hp);
+                return x == 1ull || x == 2ull * (unsigned long long)done;
+            });
+        const bool all = pinned_load(hp) == 1ull;
         over = !all && done > cap;
         if (all || over) break;
         chunk = done > 64 ? 32 : 4;

@@ -49,8 +49,8 @@ constexpr int kOrderRegionWords = 32;  // a region's counters fill a 256-byte li
 constexpr int kOrderState = 3 * kOrderRegions * kOrderRegionWords;
 constexpr int kOrderCtlWords = kOrderState + 32;
 constexpr int kOrderMaxJobs = 64;
-// Statistics words per query in stat (pinned host memory): 0 while running,
-// else 1; rounds; pull rounds; frontier vertices; arcs pushed; arcs pulled.
+// Statistics words per query in stat (pinned host memory): 1 at the end, else 0
+// until the last launch of a call of order_rounds stores 2 (first + rounds); rounds; pull rounds; frontier vertices; arcs pushed; arcs pulled.
 constexpr int kOrderStatWords = 6;
 
 // Batched queries on one graph: up to kBatchLanes sources, one per wave lane,
@@ -62,7 +62,7 @@ struct OrderBatch {
     unsigned long long *mask;  // workspace: 3 x n, the sources whose frontier holds a vertex, by round mod 3
     uint32_t *mu;             // workspace: 3 x kOrderRegions x 64 complements of each source's mu
 };
-constexpr int kOrderBatchStatWords = 6;  // 0 / 1, rounds, pull rounds, frontier vertices, arcs read, (arc, source) pairs decided
+constexpr int kOrderBatchStatWords = 6;  // as above, rounds, pull rounds, frontier vertices, arcs read, (arc, source) pairs decided
 
 size_t order_batch_bytes(int32_t n);
 void order_batch_carve(OrderBatch *b, void *ws);

@@ -77,6 +77,7 @@ struct OrderArgs {
     const OrderJob *job;
     int64_t round;
     unsigned long long *stat;
+    unsigned long long tag;  // stored if the query goes on, and not 0
 };
 
 __device__ __forceinline__ uint32_t ld_dev(gptr<uint32_t> p) {
@@ -245,6 +246,9 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
                 __hip_atomic_store(st, v[0], __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);  // (the host polls it)
             }
         } else {
+            if (g.tag != 0ull)
+                __hip_atomic_store(g.stat + (size_t)blockIdx.y * kOrderStatWords, g.tag, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_SYSTEM);
             state[kStF] += T.F;
             if (pull) {
                 (void)__hip_atomic_fetch_or(region + kRgFlags, kFlagPulled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -442,6 +446,7 @@ struct OrderBatchArgs {
     OrderBatch b;
     int64_t round;
     unsigned long long *stat;
+    unsigned long long tag;  // as in OrderArgs
 };
 constexpr int kRgPairs = 6;   // region: (arc, source) pairs of the frontier
 constexpr int kStPairs = 6;   // state: their total
@@ -574,6 +579,7 @@ __global__ __launch_bounds__(256, 8) void k_order_batch(OrderBatchArgs g) {
                 __hip_atomic_store(g.stat, v[0], __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);  // (the host polls it)
             }
         } else {
+            if (g.tag != 0ull) __hip_atomic_store(g.stat, g.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             state[kStF] += T.F;
             if (pull) {
                 (void)__hip_atomic_fetch_or(region + kRgFlags, kFlagPulled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -983,9 +989,10 @@ hipError_t order_rounds(const OrderJob *jobs, int32_t k, int wt, const OrderJob 
         blocks = std::max<int64_t>(blocks, std::min<int64_t>(((int64_t)jobs[i].n + kOrderVerts - 1) / kOrderVerts, 8192) +
                                                std::min<int64_t>(((int64_t)jobs[i].nchunks + 15) / 16, 1024));
     const dim3 grid((unsigned)blocks, (unsigned)k), blk(256);
-    OrderArgs a{table, 0, stat};
+    OrderArgs a{table, 0, stat, 0};
     for (int32_t r = 0; r < rounds; ++r) {
         a.round = first + r;
+        a.tag = r + 1 == rounds ? 2ull * (unsigned long long)(first + rounds) : 0ull;
         if (wt == 0) hipLaunchKernelGGL((k_order<0>), grid, blk, 0, st, a);
         else if (wt == 1) hipLaunchKernelGGL((k_order<1>), grid, blk, 0, st, a);
         else hipLaunchKernelGGL((k_order<2>), grid, blk, 0, st, a);
@@ -1034,9 +1041,10 @@ hipError_t order_batch_rounds(const OrderBatch &b, int wt, int64_t first, int32_
     // (rows differ in length: 2061 us for 64 sources of a scale-20 R-MAT graph,
     // 2182 with just what it holds, 2330 with eight times as many)
     const int64_t blocks = std::min<int64_t>(((int64_t)b.g.n + 4 * kBatchVerts - 1) / (4 * kBatchVerts), (int64_t)num_cu * 32);
-    OrderBatchArgs a{b, 0, stat};
+    OrderBatchArgs a{b, 0, stat, 0};
     for (int32_t r = 0; r < rounds; ++r) {
         a.round = first + r;
+        a.tag = r + 1 == rounds ? 2ull * (unsigned long long)(first + rounds) : 0ull;
         if (wt == 0) hipLaunchKernelGGL((k_order_batch<0>), dim3((unsigned)blocks), dim3(256), 0, st, a);
         else hipLaunchKernelGGL((k_order_batch<1>), dim3((unsigned)blocks), dim3(256), 0, st, a);
     }
