@@ -15,11 +15,11 @@
 // arc (u, v, w), new = dist[u] + w, offered to v with an LDS atomic min.
 // Each vertex's LDS word holds its distance shifted left by one and a free
 // bit (set: not on the next list).  Expanding u sets u's free bit with an
-// atomic or, whose result is the distance the group uses; an offer writes
+// atomic or, behind which the group reads the distance it uses; an offer writes
 // new << 1 (free bit clear), and the offer that took v's word from free to
 // queued appends v to list r + 1.  One word per vertex: an improvement that
 // lands after u's atomic or finds u free and queues it again, and one that
-// lands before is read by it.  dist[u] is thus read when u is expanded, so
+// lands before is read.  dist[u] is thus read when u is expanded, so
 // an improvement found earlier in the same round is used (as the other
 // loops read dist[u] when staging their frontier).  One workgroup barrier
 // ends each round (with row offsets, a second one precedes the hubs' arcs);
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kLdsThreads) void k_lds(LdsArgs a) {
     __syncthreads();
     uint32_t arcs = 0, expanded = 0;
     constexpr int32_t lg = LG;
-    const int slot = t & ((1 << lg) - 1), lead = (t & 63) - slot;
+    const int slot = t & ((1 << lg) - 1);
     int64_t r = 0;
     // one arc of the row-offset layout relaxed with its tail's distance du
     const auto relax_csr = [&](int32_t e, uint32_t du, int32_t ln, int kn) {
@@ -152,8 +152,7 @@ __global__ __launch_bounds__(kLdsThreads) void k_lds(LdsArgs a) {
             if constexpr (!ELL) sHubCnt[hb ^ 1] = 0;  // last read in round r - 1
         }
         // G = 2^lg lanes of one wave expand a vertex together: the group's
-        // first lane frees u and reads dist[u] in one atomic, the distance is
-        // broadcast across the group, and lane s of the group takes the arcs
+        // first lane frees u, all of them read dist[u], and lane s takes the arcs
         // e0 + s, e0 + s + G, ...
         for (int32_t i = t; i < (cnt << lg); i += kLdsThreads) {
             const uint32_t u = i == t ? u_first : sL[lc + (i >> lg)];
@@ -165,11 +164,20 @@ __global__ __launch_bounds__(kLdsThreads) void k_lds(LdsArgs a) {
                 e0 = sRo[u];
                 e1 = sRo[u + 1];
             }
-            uint32_t du = 0u;
-            if (slot == 0) du = __hip_atomic_fetch_or(&sW[u], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> 1;
-            // broadcast from the group's first lane (a DPP move within quads
-            // measured no faster than this permute for groups of 2 and 4)
-            if constexpr (LG > 0) du = (uint32_t)__builtin_amdgcn_ds_bpermute(lead << 2, (int)du);
+            // The group's first lane frees u, then every lane reads its word: a
+            // wave's LDS operations are performed in order, so an offer that
+            // the read misses finds u free.  (Broadcasting the atomic's result
+            // across the group took a permute more per round: grid 64^2 75 -> 73
+            // us, 81^2 91 -> 89.  A lane alone has no use for the second trip.)
+            uint32_t du;
+            if constexpr (LG > 0) {
+                if (slot == 0)
+                    (void)__hip_atomic_fetch_or(&sW[u], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                asm volatile("" ::: "memory");
+                du = __hip_atomic_load(&sW[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> 1;
+            } else {
+                du = __hip_atomic_fetch_or(&sW[u], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> 1;
+            }
             if constexpr (ELL) {
                 // slots fill from the first: slot 0 holds an arc iff u has one
                 expanded += slot == 0 && xe != kLdsNoArc ? 1u : 0u;
