@@ -503,12 +503,13 @@ static gr_status graph_build(gr_graph *g, int32_t n, int32_t m, const int32_t *r
     g->d_ro_in = g->d_ro;
     g->d_adj_in = g->d_adj;
     if (!(flags & GR_NO_PULL)) {
-        unsigned int not_sym = 0;
+        unsigned long long not_sym[2] = {0ull, 0ull};
         BUILD_TRY(hipMemsetAsync(flag, 0, 64, st), "memset");
-        BUILD_TRY(launch_symmetry_check(n, g->d_ro, g->d_adj, flag, st), "symmetry check");
-        BUILD_TRY(hipMemcpyAsync(&not_sym, flag, sizeof not_sym, hipMemcpyDeviceToHost, st), "symmetry check");
+        BUILD_TRY(launch_symmetry_check(n, g->d_ro, g->d_adj, reinterpret_cast<unsigned long long *>(flag), st),
+                  "symmetry check");
+        BUILD_TRY(hipMemcpyAsync(not_sym, flag, sizeof not_sym, hipMemcpyDeviceToHost, st), "symmetry check");
         BUILD_TRY(hipStreamSynchronize(st), "symmetry check");
-        if (not_sym) {
+        if (not_sym[0] || not_sym[1]) {
             int32_t *scratch = nullptr;
             const size_t nsc = (2 * (size_t)n + 1) + scan_tmp_ints((int64_t)n + 1);
             g->d_ro_in = nullptr;

@@ -222,7 +222,9 @@ hipError_t launch_validate(int32_t n, int32_t m, const int32_t *ro, const int32_
 size_t scan_tmp_ints(int64_t len);
 hipError_t launch_csc_build(int32_t n, int32_t m, const int32_t *ro, const uint2 *adj, int32_t *ro_in,
                             uint2 *adj_in, int32_t *scratch, hipStream_t st);
-hipError_t launch_symmetry_check(int32_t n, const int32_t *ro, const uint2 *adj, unsigned int *not_sym,
+// Adds to out[0] and out[1] (cleared by the caller): both stay 0 iff the rows
+// are strictly ascending and the arcs symmetric.
+hipError_t launch_symmetry_check(int32_t n, const int32_t *ro, const uint2 *adj, unsigned long long *out,
                                  hipStream_t st);
 // Partitioned push layout: pro needs (n+1)*np ints; cnt and pm np*(n+1)+1
 // ints each, tmp scan_tmp_ints(np*(n+1)+1).
