@@ -28,6 +28,7 @@
 #include "gr_multi.h"
 #include "gr_noalloc.h"
 #include "gr_order.h"
+#include "gr_report.h"
 #include "gr_sched.h"
 #include "gr_tile.h"
 
@@ -505,8 +506,7 @@ static gr_status graph_build(gr_graph *g, int32_t n, int32_t m, const int32_t *r
     if (!(flags & GR_NO_PULL)) {
         unsigned long long not_sym[2] = {0ull, 0ull};
         BUILD_TRY(hipMemsetAsync(flag, 0, 64, st), "memset");
-        BUILD_TRY(launch_symmetry_check(n, g->d_ro, g->d_adj, reinterpret_cast<unsigned long long *>(flag), st),
-                  "symmetry check");
+        BUILD_TRY(launch_symmetry_check(n, g->d_ro, g->d_adj, flag, st), "symmetry check");
         BUILD_TRY(hipMemcpyAsync(not_sym, flag, sizeof not_sym, hipMemcpyDeviceToHost, st), "symmetry check");
         BUILD_TRY(hipStreamSynchronize(st), "symmetry check");
         if (not_sym[0] || not_sym[1]) {

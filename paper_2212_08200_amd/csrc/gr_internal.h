@@ -183,9 +183,6 @@ hipError_t launch_filter(const DevGraph &g, const Frontier &f, int64_t iter, uin
                          const uint32_t *dist, bool use_far, uint32_t threshold, hipStream_t st);
 // Device address of the counter slot filled by the filter of iteration `iter`.
 unsigned long long *counters_after(const Frontier &f, int64_t iter);
-// Copies a counter slot to `to` (pinned host memory, the slot's layout), then
-// stores tag in to[kSlotWords].
-hipError_t launch_report(const unsigned long long *slot, unsigned long long *to, unsigned long long tag, hipStream_t st);
 
 // Device-driven loop (cooperative launch).
 struct PersistentCfg {
@@ -222,9 +219,7 @@ hipError_t launch_validate(int32_t n, int32_t m, const int32_t *ro, const int32_
 size_t scan_tmp_ints(int64_t len);
 hipError_t launch_csc_build(int32_t n, int32_t m, const int32_t *ro, const uint2 *adj, int32_t *ro_in,
                             uint2 *adj_in, int32_t *scratch, hipStream_t st);
-// Adds to out[0] and out[1] (cleared by the caller): both stay 0 iff the rows
-// are strictly ascending and the arcs symmetric.
-hipError_t launch_symmetry_check(int32_t n, const int32_t *ro, const uint2 *adj, unsigned long long *out,
+hipError_t launch_symmetry_check(int32_t n, const int32_t *ro, const uint2 *adj, unsigned int *not_sym,
                                  hipStream_t st);
 // Partitioned push layout: pro needs (n+1)*np ints; cnt and pm np*(n+1)+1
 // ints each, tmp scan_tmp_ints(np*(n+1)+1).

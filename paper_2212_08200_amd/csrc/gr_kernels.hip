@@ -28,6 +28,7 @@
 // bit patterns order like the values and one uint32 atomic min serves both
 // weight types.
 #include "gr_device.h"
+#include "gr_report.h"
 
 #include <hip/hip_runtime.h>
 
@@ -2278,9 +2279,12 @@ hipError_t launch_csc_build(int32_t n, int32_t m, const int32_t *ro, const uint2
 // (four rows per wave; few enough blocks that their sums don't queue)
 static inline int rows_grid(int32_t n) { return grid_for(((int64_t)n + 3) / 4, kBlk / 64, 4096); }
 
-hipError_t launch_symmetry_check(int32_t n, const int32_t *ro, const uint2 *adj, unsigned long long *out,
+// not_sym: 16 cleared bytes; they stay 0 iff the rows are strictly ascending
+// and the arcs symmetric.
+hipError_t launch_symmetry_check(int32_t n, const int32_t *ro, const uint2 *adj, unsigned int *not_sym,
                                  hipStream_t st) {
-    hipLaunchKernelGGL(k_symmetry, dim3(rows_grid(n)), dim3(kBlk), 0, st, n, ro, adj, out);
+    hipLaunchKernelGGL(k_symmetry, dim3(rows_grid(n)), dim3(kBlk), 0, st, n, ro, adj,
+                       reinterpret_cast<unsigned long long *>(not_sym));
     return hipGetLastError();
 }
 
