@@ -214,9 +214,18 @@ __device__ __forceinline__ void push_entry(const OrderJob &J, gptr<uint32_t> dis
             for (uint32_t r = 0; r * kPushRun < deg[k]; ++r) next_queue[at++] = u32x2{a[k].x, r};
 }
 
+// AHEAD: the third weight and the row's bounds are loaded with the tails'
+// distances, for every vertex whose second arc may help, instead of one after
+// the other for those that go on.  Two trips less per round where they go to
+// memory (R-MAT 20 binary32 613 -> 586 us, 22 1058 -> 1020, uniform of a million
+// vertices 1350 -> 1307); where the tables stay in the L2s the loads for nothing
+// cost more (R-MAT 13 185 -> 191, 15 195 -> 199, 18 220 -> 225, 19 264 -> 266;
+// uniform of half a million, between: 950 -> 885).
+constexpr int32_t kOrderAhead = 3 << 18;  // vertices from which on
+
 // WT: 0 uint32, 1 binary32, 2 unit steps.  Blocks [0, vblocks) of a pull take
 // kOrderVerts vertices each, the others the long rows' chunks.
-template <int WT>
+template <int WT, bool AHEAD>
 __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
     const OrderJob &J = g.job[blockIdx.y];
     const int t = threadIdx.x, lane = t & 63;
@@ -298,13 +307,15 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
         const uint32_t mu = T.mu;
         const auto step = [](uint32_t d, uint32_t w) { return plus<WT>(d, w); };
         __shared__ uint32_t sList[kOrderVerts], sWas[kOrderVerts], sBest[kOrderVerts];
+        __shared__ int2 sRow[AHEAD ? kOrderVerts : 1];
         for (int32_t vb = blockIdx.x; vb < vblocks; vb += gridDim.x) {
             if (t == 0) sCnt = 0u;
             __syncthreads();
             // the two lightest arcs: every load of a vertex is issued at once,
             // then the tails' distances
             constexpr int V = kOrderVerts / 256;
-            uint32_t b[V], best[V], d0[V], d1[V];
+            uint32_t b[V], best[V], d0[V], d1[V], w2[V];
+            int32_t r0[V], r1[V];
             u32x2 a0[V], a1[V];
             bool in0[V], in1[V];
 #pragma unroll
@@ -322,6 +333,14 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
                 in1[k] = in0[k] && a1[k].x != kOrderNone && step(mu, a1[k].y) < b[k];
                 if (in0[k]) d0[k] = dist[a0[k].x];
                 if (in1[k]) d1[k] = dist[a1[k].x];
+                if constexpr (AHEAD) {
+                    const int32_t v = vb * kOrderVerts + k * 256 + t;
+                    if (in1[k]) {
+                        w2[k] = to_global(J.w2)[v];
+                        r0[k] = to_global(J.ro_in)[v];
+                        r1[k] = to_global(J.ro_in)[v + 1];
+                    }
+                }
             }
 #pragma unroll
             for (int k = 0; k < V; ++k) {
@@ -333,7 +352,8 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
                 bool row = in1[k] && step(mu, a1[k].y) < best[k];
                 const int i = k * 256 + t;
                 const int32_t v = vb * kOrderVerts + i;
-                if (row) row = step(mu, to_global(J.w2)[v]) < best[k];
+                if constexpr (AHEAD) row = row && step(mu, w2[k]) < best[k];
+                else if (row) row = step(mu, to_global(J.w2)[v]) < best[k];
                 const unsigned long long m = __ballot(row);
                 if (m != 0ull) {
                     uint32_t at = 0;
@@ -343,6 +363,7 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
                         sList[at] = (uint32_t)i;
                         sWas[at] = b[k];
                         sBest[at] = best[k];
+                        if constexpr (AHEAD) sRow[at] = make_int2(r0[k], r1[k]);
                     }
                 }
                 if (!row && best[k] < b[k]) {
@@ -358,7 +379,14 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
             for (uint32_t k = (uint32_t)t >> 3; k < cnt; k += 32u) {
                 const int32_t v = vb * kOrderVerts + (int32_t)sList[k];
                 uint32_t low = sBest[k];
-                const int32_t e0 = ro[v] + 2, e1 = ro[v + 1];
+                int32_t e0, e1;
+                if constexpr (AHEAD) {
+                    e0 = sRow[k].x + 2;
+                    e1 = sRow[k].y;
+                } else {
+                    e0 = ro[v] + 2;
+                    e1 = ro[v + 1];
+                }
                 for (int32_t e = e0; e < e1; e += 8) {
                     const int32_t my = e + (t & 7);
                     const u32x2 a = arc[min(my, e1 - 1)];
@@ -981,21 +1009,30 @@ hipError_t order_begin(const OrderJob *jobs, int32_t k, int wt, OrderJob *table,
     return hipSuccess;
 }
 
+template <bool AHEAD>
+static void launch_order(int wt, dim3 grid, hipStream_t st, const OrderArgs &a) {
+    if (wt == 0) hipLaunchKernelGGL((k_order<0, AHEAD>), grid, dim3(256), 0, st, a);
+    else if (wt == 1) hipLaunchKernelGGL((k_order<1, AHEAD>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_order<2, AHEAD>), grid, dim3(256), 0, st, a);
+}
+
 hipError_t order_rounds(const OrderJob *jobs, int32_t k, int wt, const OrderJob *table, int64_t first, int32_t rounds,
                         unsigned long long *stat, hipStream_t st) {
     // blocks for the vertices, and for the long rows (16 chunks each)
-    int64_t blocks = 64;
-    for (int32_t i = 0; i < k; ++i)
+    int64_t blocks = 64, big = 0;
+    for (int32_t i = 0; i < k; ++i) {
+        big = std::max<int64_t>(big, jobs[i].n);
         blocks = std::max<int64_t>(blocks, std::min<int64_t>(((int64_t)jobs[i].n + kOrderVerts - 1) / kOrderVerts, 8192) +
                                                std::min<int64_t>(((int64_t)jobs[i].nchunks + 15) / 16, 1024));
-    const dim3 grid((unsigned)blocks, (unsigned)k), blk(256);
+    }
+    const dim3 grid((unsigned)blocks, (unsigned)k);
+    const bool ahead = big >= kOrderAhead;
     OrderArgs a{table, 0, stat, 0};
     for (int32_t r = 0; r < rounds; ++r) {
         a.round = first + r;
         a.tag = r + 1 == rounds ? 2ull * (unsigned long long)(first + rounds) : 0ull;
-        if (wt == 0) hipLaunchKernelGGL((k_order<0>), grid, blk, 0, st, a);
-        else if (wt == 1) hipLaunchKernelGGL((k_order<1>), grid, blk, 0, st, a);
-        else hipLaunchKernelGGL((k_order<2>), grid, blk, 0, st, a);
+        if (ahead) launch_order<true>(wt, grid, st, a);
+        else launch_order<false>(wt, grid, st, a);
     }
     return hipGetLastError();
 }

@@ -72,6 +72,21 @@ def test_ordered_matches_oracle(name):
                 assert st["loop"] == gr.GR_LOOP_QUEUED and st["launches"] >= st["iterations"] + 1
 
 
+@pytest.mark.parametrize("n", [(3 << 18) - 1, 3 << 18, (3 << 18) + 1])
+def test_ordered_large(n):
+    # from 786,432 vertices on, what a row needs is loaded ahead
+    for wtype in (gg.W_U32, gg.W_F32):
+        g = stars(EDGE * 200, n, 41, wtype=wtype)
+        s = int(gg.pick_sources(g, 3, 1)[0])
+        print("ordered n=%d m=%d src=%d" % (g.n, g.m, s), file=sys.stderr, flush=True)
+        want = oracle.dijkstra(g, s)
+        with gr.Graph.from_csr(g) as G:
+            for rep in range(2):
+                got, st = query(G, g.n, s)
+                np.testing.assert_array_equal(got, want)
+                assert st["loop"] == gr.GR_LOOP_QUEUED and 0 < st["arcs_pulled"]
+
+
 def test_ordered_not_taken():
     g = gg.rmat(13, 16, gseed=21, pseed=22, wseed=23)
     s = int(gg.pick_sources(g, 3, 1)[0])
