@@ -789,9 +789,9 @@ static gr_status run_host_loop(const gr_graph *g, int32_t src, uint32_t *dist, h
         c.F[0] = d > 0 ? 1 : 0;
         c.E[0] = d;
     } else {
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(hp, f.ctl, sizeof(unsigned long long) * kSlotWords, hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        const unsigned long long tag = ~0ull;  // (the rounds' tags count from 1)
+        if (e == hipSuccess) e = launch_report(f.ctl, hp, tag, st);
+        if (e == hipSuccess) e = wait_pinned(st, [&] { return pinned_load(hp + kSlotWords) == tag; });
         read_counts(hp, &c);
     }
     int64_t iter = 0;
