@@ -274,6 +274,7 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
         sLow = 0xFFFFFFFFu;
         sCnt = sArcs = sRead = 0u;
     }
+    __syncthreads();  // (a block of chunks alone meets no other barrier before it adds to them)
     uint32_t lowest = 0xFFFFFFFFu, nread = 0, nnew = 0;
     const int32_t vblocks = (n + kOrderVerts - 1) / kOrderVerts;
     if (!pull) {
