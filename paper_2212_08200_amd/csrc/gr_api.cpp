@@ -556,9 +556,8 @@ static gr_status graph_build(gr_graph *g, int32_t n, int32_t m, const int32_t *r
     // degree ones keep the asynchronous loop: uniform graphs of 5,000 and
     // 30,000 vertices 0.28 and 0.35 ms against 0.33 and 0.40; 300,000: 1.5
     // queued against 0.97).
-    // (The loop's 32-bit arc indices step past a row's end.)
-    if (g->auto_loop != GR_LOOP_LDS && g->auto_loop != GR_LOOP_ASYNC && !g->auto_tiled && g->pull && m > 0 &&
-        m < INT32_MAX - 64) {
+    if (g->auto_loop != GR_LOOP_LDS && g->auto_loop != GR_LOOP_ASYNC && !g->auto_tiled && g->pull &&
+        order_indexes(m)) {
         std::vector<int32_t> in;
         if (g->csc_separate) {
             in.resize((size_t)n + 1);

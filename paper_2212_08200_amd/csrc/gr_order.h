@@ -16,6 +16,10 @@ namespace gr {
 // (weight INF, tail kOrderNone) and are listed chunk by chunk instead.
 constexpr int32_t kOrderChunk = 1024;
 constexpr uint32_t kOrderNone = 0xFFFFFFFFu;
+// Arcs per queue entry of a push.  The loop's arc indices are 32-bit and step
+// past the end of a row by up to that many.
+constexpr int32_t kOrderRun = 256;
+constexpr bool order_indexes(int32_t m) { return m > 0 && m <= INT32_MAX - kOrderRun; }
 struct OrderSet {
     void *base = nullptr;
     size_t bytes = 0;

@@ -55,7 +55,7 @@ namespace {
 // 1050 with this rule; a bias of 1 or 16 measures the same on other queries.)
 constexpr double kOrderBias = 4.0;
 constexpr int kOrderVerts = 512;     // vertices per block of a pull, two per thread
-constexpr int kPushRun = 256;        // arcs per queue entry
+constexpr int kPushRun = kOrderRun;  // arcs per queue entry
 
 // Counters of a region, as words: frontier vertices, their arcs, the complement
 // of mu (a maximum: a cleared word is neutral), queue entries, flags, and the
@@ -482,6 +482,7 @@ constexpr int kStPairs = 6;   // state: their total
 constexpr int kBatchVerts = 4;   // vertices in flight per wave
 constexpr int kBatchArcs = 4;   // arcs of a row in flight (2000 us for the 64 queries below, 2066 with 8)
 constexpr int kBatchRun = 64;   // arcs per queue entry
+static_assert(kBatchRun <= kOrderRun && kBatchArcs <= kOrderRun, "steps past a row's end");
 
 struct BatchBeginArgs {
     OrderBatch b;

@@ -1,0 +1,25 @@
+"""CPU unit test of the arc indices of the weight-ordered loop (``csrc/gr_order.h``)."""
+import os
+import re
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2212_08200_amd", "csrc")
+
+
+def test_largest_graph_stays_in_int32(tmp_path):
+    exe = tmp_path / "order_index_test"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", CSRC,
+                    os.path.join(ROOT, "tests", "order_index_test.cpp"), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
+
+
+def test_every_step_is_within_the_run():
+    # the loops' steps past a row's end (e += step, and entries of a queue)
+    with open(os.path.join(CSRC, "gr_order.hip")) as f:
+        text = f.read()
+    run = int(re.search(r"kOrderRun = (\d+);", open(os.path.join(CSRC, "gr_order.h")).read()).group(1))
+    steps = [int(x) for x in re.findall(r"\be \+= (\d+)\)", text)]
+    assert len(steps) >= 2 and max(steps) <= run
+    assert "order_indexes(m)" in open(os.path.join(CSRC, "gr_api.cpp")).read()
