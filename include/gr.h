@@ -180,7 +180,10 @@ typedef enum {
                                a small frontier, else pulls, reading a vertex's arcs in
                                order of weight while they can still improve it.  Extra
                                workspace: about 5 bytes per vertex.  stats: arcs_pulled
-                               counts the arcs read. */
+                               counts the arcs read.  A graph whose copy finds no memory
+                               is created without it (the environment variable
+                               GR_LAYOUT_LIMIT bounds the bytes of this copy and of the
+                               tiles below, to test that). */
     GR_LOOP_ASYNC = 4,      /* asynchronous (Section III-A without the per-advance barrier,
                                III-B frontier as a message queue): one persistent kernel
                                drains a device worklist of improved vertices; no rounds.

@@ -396,6 +396,61 @@ static gr_status build_partition(gr_graph *g, int32_t n, int32_t m, hipStream_t 
     return build_members(g, d, 1, st, sc);
 }
 
+// The layouts that AUTO can do without, last: tiles, or in-arcs by weight.  Where
+// memory does not hold one, the graph is left without it, on the loops that
+// need none.  GR_LAYOUT_LIMIT (bytes) is what such a layout may take at most: a
+// test hook for that path.
+static gr_status build_extra(gr_graph *g, int wt, int64_t over4, int64_t over8, hipStream_t st) {
+    const int32_t n = g->plain.n, m = g->plain.m;
+    size_t limit = SIZE_MAX;
+    if (const char *ev = getenv("GR_LAYOUT_LIMIT")) limit = (size_t)strtoull(ev, nullptr, 10);
+    // *fits: whether memory held it (else nothing is left of it)
+    const auto extra = [&](const char *what, bool *fits, auto build) {
+        hipError_t e;
+        try {
+            e = build();
+        } catch (const std::bad_alloc &) {
+            e = hipErrorOutOfMemory;
+        }
+        *fits = e != hipErrorOutOfMemory;
+        if (!*fits) (void)hipGetLastError();  // (the next launch's check would find it)
+        return e == hipSuccess || !*fits ? GR_OK : hip_fail(e, what);
+    };
+    // Tiles: for bounded degrees, unless the single-workgroup loop runs the
+    // whole graph (it needs no inboxes and starts faster).
+    if (g->auto_loop == GR_LOOP_LDS) return GR_OK;
+    if (g->max_degree <= kTileMaxDegree) {
+        bool fits = true;
+        const gr_status s = extra("tiles", &fits, [&] {
+            return tile_build(&g->tiles, n, m, g->d_ro, g->d_adj, wt, over4, over8, limit, st);
+        });
+        if (s != GR_OK || !fits) return s;
+        g->auto_tiled = g->tiles.ntiles > 0;
+        g->dev_bytes += g->tiles.bytes;
+    }
+    // In-arcs by weight: the graphs that have no better loop (small bounded-
+    // degree ones keep the asynchronous loop: uniform graphs of 5,000 and
+    // 30,000 vertices 0.28 and 0.35 ms against 0.33 and 0.40; 300,000: 1.5
+    // queued against 0.97).
+    if (g->auto_loop == GR_LOOP_ASYNC || g->auto_tiled || !g->pull || !order_indexes(m)) return GR_OK;
+    bool fits = true;
+    const gr_status s = extra("in-arcs by weight", &fits, [&] {
+        std::vector<int32_t> in;
+        if (g->csc_separate) {
+            in.resize((size_t)n + 1);
+            const hipError_t e = hipMemcpyAsync(in.data(), g->d_ro_in, sizeof(int32_t) * in.size(),
+                                                hipMemcpyDeviceToHost, st);
+            if (e != hipSuccess) return e;
+            if (const hipError_t e2 = hipStreamSynchronize(st); e2 != hipSuccess) return e2;
+        }
+        return order_build(&g->order, n, m, g->d_ro_in, g->d_adj_in, g->csc_separate ? in.data() : g->h_ro.data(), wt,
+                           limit, st);
+    });
+    g->auto_order = g->order.base != nullptr;
+    g->dev_bytes += g->order.bytes;
+    return s;
+}
+
 static gr_status graph_build(gr_graph *g, int32_t n, int32_t m, const int32_t *ro, const int32_t *col,
                              const void *weights, gr_weight_type wt, uint32_t flags, hipStream_t st) {
     const bool dev_in = flags & GR_INPUT_DEVICE;
@@ -545,32 +600,6 @@ static gr_status graph_build(gr_graph *g, int32_t n, int32_t m, const int32_t *r
         if (s != GR_OK) return s;
     }
 
-    // Tiles: for bounded degrees, unless the single-workgroup loop runs the
-    // whole graph (it needs no inboxes and starts faster).
-    if (g->max_degree <= kTileMaxDegree && g->auto_loop != GR_LOOP_LDS) {
-        BUILD_TRY(tile_build(&g->tiles, n, m, g->d_ro, g->d_adj, (int)wt, over4, over8, st), "tiles");
-        g->auto_tiled = g->tiles.ntiles > 0;
-        g->dev_bytes += g->tiles.bytes;
-    }
-    // In-arcs by weight: the graphs that have no better loop (small bounded-
-    // degree ones keep the asynchronous loop: uniform graphs of 5,000 and
-    // 30,000 vertices 0.28 and 0.35 ms against 0.33 and 0.40; 300,000: 1.5
-    // queued against 0.97).
-    if (g->auto_loop != GR_LOOP_LDS && g->auto_loop != GR_LOOP_ASYNC && !g->auto_tiled && g->pull &&
-        order_indexes(m)) {
-        std::vector<int32_t> in;
-        if (g->csc_separate) {
-            in.resize((size_t)n + 1);
-            BUILD_TRY(hipMemcpyAsync(in.data(), g->d_ro_in, sizeof(int32_t) * in.size(), hipMemcpyDeviceToHost, st),
-                      "copy in-offsets");
-            BUILD_TRY(hipStreamSynchronize(st), "copy in-offsets");
-        }
-        BUILD_TRY(order_build(&g->order, n, m, g->d_ro_in, g->d_adj_in, g->csc_separate ? in.data() : g->h_ro.data(),
-                              (int)wt, st), "in-arcs by weight");
-        g->auto_order = true;
-        g->dev_bytes += g->order.bytes;
-    }
-
     const bool want_part = !(flags & GR_NO_PARTITION) &&
                            ((flags & GR_FORCE_PARTITION) || (n >= kPartitionMinN && g->locality < 0.5));
     if (want_part) {
@@ -578,7 +607,7 @@ static gr_status graph_build(gr_graph *g, int32_t n, int32_t m, const int32_t *r
         if (s != GR_OK) return s;
         g->auto_layout = GR_LAYOUT_PARTITIONED;
     }
-    return GR_OK;
+    return build_extra(g, (int)wt, over4, over8, st);
 }
 
 extern "C" gr_status gr_graph_create_csr(gr_graph **out, int32_t n, int32_t m, const int32_t *row_offsets,

@@ -29,9 +29,10 @@ struct OrderSet {
     uint4 *chunk = nullptr;    // the long rows' chunks: (vertex, first arc, end, lightest weight)
     int32_t nchunks = 0;
 };
-// ro_in / adj_in: the graph's in-arcs; h_ro_in: the offsets on the host.
+// ro_in / adj_in: the graph's in-arcs; h_ro_in: the offsets on the host; limit:
+// bytes that the layout may take (past them hipErrorOutOfMemory).
 hipError_t order_build(OrderSet *out, int32_t n, int32_t m, const int32_t *ro_in, const uint2 *adj_in,
-                       const int32_t *h_ro_in, int wt, hipStream_t st);
+                       const int32_t *h_ro_in, int wt, size_t limit, hipStream_t st);
 
 // One query of a launch.
 struct OrderJob {

@@ -921,7 +921,7 @@ inline int32_t queue_cap(int32_t n) { return std::clamp(n / 64, 1024, 65536); }
 }  // namespace
 
 hipError_t order_build(OrderSet *out, int32_t n, int32_t m, const int32_t *ro_in, const uint2 *adj_in,
-                       const int32_t *h_ro_in, int wt, hipStream_t st) {
+                       const int32_t *h_ro_in, int wt, size_t limit, hipStream_t st) {
     *out = OrderSet{};
     std::vector<uint4> runs;
     uint32_t nchunks = 0;
@@ -937,6 +937,7 @@ hipError_t order_build(OrderSet *out, int32_t n, int32_t m, const int32_t *ro_in
                  bc = al256(sizeof(uint4) * std::max<size_t>(nchunks, 1)), b2 = al256(sizeof(uint2) * (size_t)n);
     OrderSet s;
     s.bytes = bm + bn + 2 * b2 + bc;
+    if (s.bytes > limit) return hipErrorOutOfMemory;
     hipError_t e = hipMalloc(&s.base, s.bytes);
     if (e != hipSuccess) return e;
     char *p = static_cast<char *>(s.base);

@@ -53,11 +53,12 @@ constexpr uint32_t kTileInner = 0x80000000u;
 
 // Builds the layout of a CSR (device arrays, arcs (head, weight bits)) whose
 // maximum degree is at most kTileMaxDegree.  *out stays empty (ntiles = 0) when
-// the graph does not cut into tiles (see gr_tile_build.cpp); over4 / over8:
-// arcs beyond the fourth / eighth of their vertex.
+// the graph does not cut into tiles (see gr_tile_build.hip); over4 / over8:
+// arcs beyond the fourth / eighth of their vertex; limit: bytes that the layout
+// may take (past them hipErrorOutOfMemory).
 constexpr int32_t kTileMaxDegree = 64;
 hipError_t tile_build(TileSet *out, int32_t n, int32_t m, const int32_t *ro, const uint2 *adj, int wt, int64_t over4,
-                      int64_t over8, hipStream_t st);
+                      int64_t over8, size_t limit, hipStream_t st);
 
 // One query of a launch.
 struct TileJob {

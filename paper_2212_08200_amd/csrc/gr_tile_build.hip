@@ -405,7 +405,7 @@ struct Temp {
 }  // namespace
 
 hipError_t tile_build(TileSet *out, int32_t n, int32_t m, const int32_t *ro, const uint2 *adj, int wt, int64_t over4,
-                      int64_t over8, hipStream_t st) {
+                      int64_t over8, size_t limit, hipStream_t st) {
     *out = TileSet{};
     // four columns where nearly every vertex has at most four arcs, else eight
     // (an arc without a column is walked by the send pass)
@@ -478,7 +478,9 @@ hipError_t tile_build(TileSet *out, int32_t n, int32_t m, const int32_t *ro, con
                  b_off = al256(sizeof(int32_t) * ((size_t)nt + 1));
     const size_t b_ext = sizeof(uint4) * ((size_t)m / 5 + 1), b_in = sizeof(uint2) * ((size_t)m / 5 + 1);
     void *base = nullptr;
-    TRY(hipMalloc(&base, b_pos + b_vid + b_w + b_h + 2 * b_off + b_ext + b_in));
+    const size_t bytes = b_pos + b_vid + b_w + b_h + 2 * b_off + b_ext + b_in;
+    if (bytes > limit) return hipErrorOutOfMemory;
+    TRY(hipMalloc(&base, bytes));
     struct Guard {
         void *p;
         ~Guard() {
@@ -488,7 +490,7 @@ hipError_t tile_build(TileSet *out, int32_t n, int32_t m, const int32_t *ro, con
     TileSet ts;
     char *p = static_cast<char *>(base);
     ts.base = base;
-    ts.bytes = b_pos + b_vid + b_w + b_h + 2 * b_off + b_ext + b_in;
+    ts.bytes = bytes;
     ts.n = n;
     ts.ntiles = nt;
     ts.slots = slots;
