@@ -86,21 +86,22 @@ __device__ __forceinline__ uint32_t ld_dev(gptr<uint32_t> p) {
 
 // Totals of a slot (every lane of every wave gets them).
 struct Totals {
-    unsigned long long F, E, flags;
+    unsigned long long F, E, flags, read;
     uint32_t mu;
 };
 __device__ __forceinline__ Totals read_slot(gptr<const unsigned long long> s) {
     gptr<const unsigned long long> r = s + (threadIdx.x % kOrderRegions) * kOrderRegionWords;
-    unsigned long long F = r[kRgF], E = r[kRgE], o = r[kRgFlags];
+    unsigned long long F = r[kRgF], E = r[kRgE], o = r[kRgFlags], d = r[kRgRead];
     uint32_t mu = ~(uint32_t)r[kRgMu];
 #pragma unroll
     for (int k = kOrderRegions / 2; k > 0; k >>= 1) {
         F += __shfl_xor(F, k, 64);
         E += __shfl_xor(E, k, 64);
         o |= __shfl_xor(o, k, 64);
+        d += __shfl_xor(d, k, 64);
         mu = min(mu, (uint32_t)__shfl_xor((int)mu, k, 64));
     }
-    return Totals{F, E, o, mu};
+    return Totals{F, E, o, d, mu};
 }
 
 constexpr int kBeginJobs = 16;
@@ -130,53 +131,22 @@ __global__ __launch_bounds__(256) void k_order_begin(BeginArgs a) {
     if (t == 0) a.table[blockIdx.y] = j;
 }
 
-// One push pass of a wave over entries [first, ...) of the round's queue.
-template <int WT>
-__device__ __forceinline__ void push_entry(const OrderJob &J, gptr<uint32_t> dist, gptr<unsigned long long> next_bits,
-                                           gptr<u32x2> next_queue, gptr<unsigned long long> region, u32x2 ent,
-                                           uint32_t &lowest) {
+// Puts up to K vertices per lane on the next frontier: their runs go to the
+// region's list, in one atomic per wave.  count: whether the vertices are
+// counted too.
+template <int K>
+__device__ __forceinline__ void enqueue(gptr<const int32_t> ro, int32_t cap, gptr<unsigned long long> region,
+                                        gptr<u32x2> next_queue, const uint32_t (&v)[K], const bool (&on)[K],
+                                        bool count) {
     const int lane = threadIdx.x & 63;
-    gptr<const int32_t> ro = to_global(J.ro);
-    gptr<const u32x2> adj = reinterpret_cast<gptr<const u32x2>>(to_global(J.adj));
-    const int32_t e0 = ro[ent.x] + (int32_t)ent.y * kPushRun, e1 = min(ro[ent.x + 1], e0 + kPushRun);
-    const uint32_t du = ld_dev(dist + ent.x);
-    u32x2 a[kPushRun / 64];
-    uint32_t cur[kPushRun / 64], nd[kPushRun / 64];
-#pragma unroll
-    for (int k = 0; k < kPushRun / 64; ++k) a[k] = adj[min(e0 + k * 64 + lane, e1 - 1)];
-#pragma unroll
-    for (int k = 0; k < kPushRun / 64; ++k) {
-        nd[k] = plus<WT>(du, a[k].y);
-        cur[k] = dist[a[k].x];
-    }
-    uint32_t old[kPushRun / 64];
-    bool win[kPushRun / 64];
-#pragma unroll
-    for (int k = 0; k < kPushRun / 64; ++k) {
-        win[k] = e0 + k * 64 + lane < e1 && nd[k] < cur[k];
-        if (win[k])
-            old[k] = __hip_atomic_fetch_min(dist + a[k].x, nd[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    unsigned long long was[kPushRun / 64];
-#pragma unroll
-    for (int k = 0; k < kPushRun / 64; ++k) {
-        win[k] = win[k] && nd[k] < old[k];
-        if (win[k]) {
-            lowest = min(lowest, nd[k]);
-            was[k] = __hip_atomic_fetch_or(next_bits + (a[k].x >> 6), 1ull << (a[k].x & 63), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-    // vertices new on the next frontier: their runs go to the queue
     uint32_t news = 0, runs = 0;
     unsigned long long arcs = 0;
-    uint32_t deg[kPushRun / 64];
+    uint32_t deg[K];
 #pragma unroll
-    for (int k = 0; k < kPushRun / 64; ++k) {
-        win[k] = win[k] && !(was[k] >> (a[k].x & 63) & 1ull);
+    for (int k = 0; k < K; ++k) {
         deg[k] = 0;
-        if (win[k]) {
-            deg[k] = (uint32_t)(ro[a[k].x + 1] - ro[a[k].x]);
+        if (on[k]) {
+            deg[k] = (uint32_t)(ro[v[k] + 1] - ro[v[k]]);
             news += deg[k] > 0u ? 1u : 0u;  // a vertex without out-arcs is on no frontier
             runs += (deg[k] + kPushRun - 1) / kPushRun;
             arcs += deg[k];
@@ -197,21 +167,133 @@ __device__ __forceinline__ void push_entry(const OrderJob &J, gptr<uint32_t> dis
     if (lane == 0) {
         base = __hip_atomic_fetch_add(region + kRgCnt, (unsigned long long)all, __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT);
-        (void)__hip_atomic_fetch_add(region + kRgF, (unsigned long long)total, __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT);
+        if (count)
+            (void)__hip_atomic_fetch_add(region + kRgF, (unsigned long long)total, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
         (void)__hip_atomic_fetch_add(region + kRgE, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     base = (unsigned long long)__shfl((long long)base, 0, 64);
-    if (base + all > (unsigned long long)J.cap) {  // the next round pulls
+    if (base + all > (unsigned long long)cap) {  // the next round pulls
         if (lane == 0)
             (void)__hip_atomic_fetch_or(region + kRgFlags, kFlagOver, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
     uint32_t at = (uint32_t)base + before - runs;
 #pragma unroll
-    for (int k = 0; k < kPushRun / 64; ++k)
+    for (int k = 0; k < K; ++k)
+        for (uint32_t r = 0; r * kPushRun < deg[k]; ++r) next_queue[at++] = u32x2{v[k], r};
+}
+
+constexpr int kPushArcs = kPushRun / 64;  // arcs per lane of an entry
+constexpr int kPackArcs = 2;              // of a pass over several entries
+
+// One push pass of a wave: K arcs per lane, each (if ok) offering its
+// tail's distance du (+) its weight.
+template <int WT, int K>
+__device__ __forceinline__ void push_pass(const OrderJob &J, gptr<uint32_t> dist, gptr<unsigned long long> next_bits,
+                                          gptr<u32x2> next_queue, gptr<unsigned long long> region,
+                                          const u32x2 (&a)[K], const uint32_t (&du)[K],
+                                          const bool (&ok)[K], uint32_t &lowest) {
+    uint32_t cur[K], nd[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        nd[k] = plus<WT>(du[k], a[k].y);
+        cur[k] = dist[a[k].x];
+    }
+    uint32_t old[K], v[K];
+    bool win[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        win[k] = ok[k] && nd[k] < cur[k];
         if (win[k])
-            for (uint32_t r = 0; r * kPushRun < deg[k]; ++r) next_queue[at++] = u32x2{a[k].x, r};
+            old[k] = __hip_atomic_fetch_min(dist + a[k].x, nd[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    unsigned long long was[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        win[k] = win[k] && nd[k] < old[k];
+        if (win[k]) {
+            lowest = min(lowest, nd[k]);
+            was[k] = __hip_atomic_fetch_or(next_bits + (a[k].x >> 6), 1ull << (a[k].x & 63), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    // vertices new on the next frontier
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        v[k] = a[k].x;
+        win[k] = win[k] && !(was[k] >> (a[k].x & 63) & 1ull);
+    }
+    enqueue<K>(to_global(J.ro), J.cap, region, next_queue, v, win, true);
+}
+
+// An entry of the queue: a wave takes its arcs in one pass.
+template <int WT>
+__device__ __forceinline__ void push_entry(const OrderJob &J, gptr<uint32_t> dist, gptr<unsigned long long> next_bits,
+                                           gptr<u32x2> next_queue, gptr<unsigned long long> region, u32x2 ent,
+                                           uint32_t &lowest) {
+    const int lane = threadIdx.x & 63;
+    gptr<const int32_t> ro = to_global(J.ro);
+    gptr<const u32x2> adj = reinterpret_cast<gptr<const u32x2>>(to_global(J.adj));
+    const int32_t e0 = ro[ent.x] + (int32_t)ent.y * kPushRun, e1 = min(ro[ent.x + 1], e0 + kPushRun);
+    const uint32_t d = ld_dev(dist + ent.x);
+    u32x2 a[kPushArcs];
+    uint32_t du[kPushArcs];
+    bool ok[kPushArcs];
+#pragma unroll
+    for (int k = 0; k < kPushArcs; ++k) {
+        a[k] = adj[min(e0 + k * 64 + lane, e1 - 1)];
+        du[k] = d;
+        ok[k] = e0 + k * 64 + lane < e1;
+    }
+    push_pass<WT, kPushArcs>(J, dist, next_bits, next_queue, region, a, du, ok, lowest);
+}
+
+// Several entries at once (one per lane, has: this lane's): their arcs end to
+// end, 128 to a pass, each lane finding its arcs' entries among the running
+// sums.  For rounds of more entries than waves, whose entries are mostly short:
+// bound by the chain of dependent loads per entry, a wave taking them one by
+// one ran 60 of 64 lanes idle (mesh 1024^2 with a hub of 80 arcs: 31.4 -> 10.1
+// ms, the session's rounds 13.1; a random tree of a million vertices 1.68 ->
+// 0.81, 1.26).  Two arcs per lane: four take the registers of two waves.
+template <int WT>
+__device__ __forceinline__ void push_entries(const OrderJob &J, gptr<uint32_t> dist,
+                                             gptr<unsigned long long> next_bits, gptr<u32x2> next_queue,
+                                             gptr<unsigned long long> region, u32x2 ent, bool has, uint32_t &lowest) {
+    const int lane = threadIdx.x & 63;
+    gptr<const int32_t> ro = to_global(J.ro);
+    gptr<const u32x2> adj = reinterpret_cast<gptr<const u32x2>>(to_global(J.adj));
+    int32_t e0 = 0, len = 0;
+    uint32_t d = 0;
+    if (has) {
+        e0 = ro[ent.x] + (int32_t)ent.y * kPushRun;
+        len = min(ro[ent.x + 1] - e0, kPushRun);
+        d = ld_dev(dist + ent.x);
+    }
+    int32_t upto = len;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t x = __shfl_up(upto, o, 64);
+        if (lane >= o) upto += x;
+    }
+    const int32_t all = __builtin_amdgcn_readlane(upto, 63);
+    const int32_t first = e0 - (upto - len);  // its arc x of all is first + x
+    for (int32_t x0 = 0; x0 < all; x0 += 64 * kPackArcs) {
+        u32x2 a[kPackArcs];
+        uint32_t du[kPackArcs];
+        bool ok[kPackArcs];
+#pragma unroll
+        for (int k = 0; k < kPackArcs; ++k) {
+            const int32_t x = min(x0 + k * 64 + lane, all - 1);
+            int p = 0;  // entries that end at or before arc x
+#pragma unroll
+            for (int b = 32; b > 0; b >>= 1) p += __shfl(upto, p + b - 1, 64) <= x ? b : 0;
+            a[k] = adj[__shfl(first, p, 64) + x];
+            du[k] = (uint32_t)__shfl((int)d, p, 64);
+            ok[k] = x0 + k * 64 + lane < all;
+        }
+        push_pass<WT, kPackArcs>(J, dist, next_bits, next_queue, region, a, du, ok, lowest);
+    }
 }
 
 // AHEAD: the third weight and the row's bounds are loaded with the tails'
@@ -226,7 +308,7 @@ constexpr int32_t kOrderAhead = 3 << 18;  // vertices from which on
 // WT: 0 uint32, 1 binary32, 2 unit steps.  Blocks [0, vblocks) of a pull take
 // kOrderVerts vertices each, the others the long rows' chunks.
 template <int WT, bool AHEAD>
-__global__ __launch_bounds__(256) void k_order(OrderArgs g) {
+__global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
     const OrderJob &J = g.job[blockIdx.y];
     const int t = threadIdx.x, lane = t & 63;
     gptr<unsigned long long> ctl = to_global(J.ctl);
@@ -294,13 +376,32 @@ __global__ __launch_bounds__(256) void k_order(OrderArgs g) {
             if (lane >= o) upto += x;
         }
         const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
-        const uint32_t waves = gridDim.x * 4u;
-        for (uint32_t i = blockIdx.x * 4u + (uint32_t)(t >> 6); i < all; i += waves) {
-            const int rg = (int)__popcll(__ballot(upto <= i));
-            const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)upto, rg);
-            const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)mine, rg);
-            const u32x2 ent = from[(size_t)rg * J.cap + (i - (end - cnt))];
-            push_entry<WT>(J, dist, next_bits, to, region, ent, lowest);
+        const uint32_t waves = gridDim.x * 4u, wave = blockIdx.x * 4u + (uint32_t)(t >> 6);
+        if (all <= waves) {
+            if (wave < all) {
+                const int rg = (int)__popcll(__ballot(upto <= wave));
+                const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)upto, rg);
+                const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)mine, rg);
+                const u32x2 ent = from[(size_t)rg * J.cap + (wave - (end - cnt))];
+                push_entry<WT>(J, dist, next_bits, to, region, ent, lowest);
+            }
+        } else {
+            const uint32_t per = min((all + waves - 1) / waves, 64u);  // entries that a wave takes at once
+            for (uint32_t i0 = wave * per; i0 < all; i0 += waves * per) {
+                const uint32_t i = min(i0 + (uint32_t)lane, all - 1);
+                uint32_t rg = 0, start = 0;
+#pragma unroll
+                for (int r = 0; r < kOrderRegions; ++r) {
+                    const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)upto, r);
+                    if (end <= i) {
+                        rg = (uint32_t)r + 1u;
+                        start = end;
+                    }
+                }
+                const bool has = (uint32_t)lane < per && i0 + (uint32_t)lane < all;
+                const u32x2 ent = from[(size_t)rg * J.cap + (i - start)];
+                push_entries<WT>(J, dist, next_bits, to, region, ent, has, lowest);
+            }
         }
         __syncthreads();
     } else {
