@@ -27,8 +27,9 @@
 // A pull round reads every vertex's distance and lightest weight (streamed),
 // so small frontiers are pushed instead, from a queue of (vertex, run of 256
 // arcs) entries: a round pushes while its frontier is small (kOrderBias) and
-// the queue held it, and once a round has pulled all later ones do (a pull
-// writes no queue).
+// the queue held it.  A pull writes no queue, so pulls follow, until their
+// frontier is small again: then they keep one, and a push may follow
+// (kBackArcs).
 //
 // One launch is one round of every query in it; the launches of a query are
 // enqueued ahead, each reads the state that the round before left, and those
@@ -54,6 +55,20 @@ namespace {
 // 9 M-arc frontier pulled under E >= m / 24 read 31 M arcs and took 1570 us,
 // 1050 with this rule; a bias of 1 or 16 measures the same on other queries.)
 constexpr double kOrderBias = 4.0;
+// After pulls.  A pull streams every vertex (n) and reads the arcs of the
+// vertices not reached yet in vain (R, as many as the pull before read), so a
+// query with a second wave of growth, or a long tail, pushes again: when the
+// frontier's arcs E satisfy kBackArcs E + kBackFixed <= n + kBackRead R.  That
+// needs a queue from the pull before, which it keeps where a push could follow
+// (n + kBackRead R >= kBackFixed) and its own frontier was at most n /
+// kBackShare vertices.  Two R-MAT 17 graphs joined by a path of 300: 58.5 ms
+// when all rounds after the first pull pulled, 4.5 so (7.2 in pushes alone);
+// R-MAT 14 and a path of 1,000: 168 -> 8.6 (13.8); uniform of 300,000 vertices
+// with unreachable parts 0.73 -> 0.64.  kBackFixed is what keeping a queue and
+// a push's longer chain cost (with half of it R-MAT 18 with two arcs per
+// vertex took 0.25 ms against 0.235; with kBackArcs 4 instead of 16 against
+// kBackRead 1 the same); kBackShare 4 and 64 measure within 5%.
+constexpr unsigned long long kBackArcs = 16, kBackFixed = 1ull << 20, kBackRead = 4, kBackShare = 16;
 constexpr int kOrderVerts = 512;     // vertices per block of a pull, two per thread
 constexpr int kPushRun = kOrderRun;  // arcs per queue entry
 
@@ -61,7 +76,8 @@ constexpr int kPushRun = kOrderRun;  // arcs per queue entry
 // of mu (a maximum: a cleared word is neutral), queue entries, flags, and the
 // arcs that the round before read.
 constexpr int kRgF = 0, kRgE = 1, kRgMu = 2, kRgCnt = 3, kRgFlags = 4, kRgRead = 5;
-constexpr unsigned long long kFlagOver = 1ull, kFlagPulled = 2ull;  // the queue overflowed; the round before pulled
+// Over: the queue does not hold the frontier; Pulled: the round before pulled.
+constexpr unsigned long long kFlagOver = 1ull, kFlagPulled = 2ull;
 // State words after the slots (block 0 of each launch keeps them).
 constexpr int kStDone = 0, kStPulls = 2, kStF = 3, kStPushed = 4, kStPulledArcs = 5;
 
@@ -84,6 +100,37 @@ __device__ __forceinline__ uint32_t ld_dev(gptr<uint32_t> p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Across a wave with DPP moves (a permute keeps a register per distance for the
+// whole kernel, 15 spills in k_order).
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, 0xF, 0xF, false);
+}
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp(unsigned long long x) {
+    return (unsigned long long)dpp<CTRL>((uint32_t)(x >> 32)) << 32 | dpp<CTRL>((uint32_t)x);
+}
+// f over every run of 16 lanes, in each of them.
+template <typename T, typename F>
+__device__ __forceinline__ T over_row(T x, F f) {
+    x = f(x, dpp<0xB1>(x));   // quad_perm 1,0,3,2
+    x = f(x, dpp<0x4E>(x));   // quad_perm 2,3,0,1
+    x = f(x, dpp<0x141>(x));  // row_half_mirror
+    return f(x, dpp<0x140>(x));  // row_mirror
+}
+// Inclusive running sum.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
+#define DPPADD(ctrl, rows) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xF, false)
+    DPPADD(0x111, 0xF);  // row_shr 1, 2, 4, 8
+    DPPADD(0x112, 0xF);
+    DPPADD(0x114, 0xF);
+    DPPADD(0x118, 0xF);
+    DPPADD(0x142, 0xA);  // row_bcast 15 into the odd rows
+    DPPADD(0x143, 0xC);  // row_bcast 31 into the upper half
+#undef DPPADD
+    return x;
+}
+
 // Totals of a slot (every lane of every wave gets them).
 struct Totals {
     unsigned long long F, E, flags, read;
@@ -91,17 +138,13 @@ struct Totals {
 };
 __device__ __forceinline__ Totals read_slot(gptr<const unsigned long long> s) {
     gptr<const unsigned long long> r = s + (threadIdx.x % kOrderRegions) * kOrderRegionWords;
-    unsigned long long F = r[kRgF], E = r[kRgE], o = r[kRgFlags], d = r[kRgRead];
-    uint32_t mu = ~(uint32_t)r[kRgMu];
-#pragma unroll
-    for (int k = kOrderRegions / 2; k > 0; k >>= 1) {
-        F += __shfl_xor(F, k, 64);
-        E += __shfl_xor(E, k, 64);
-        o |= __shfl_xor(o, k, 64);
-        d += __shfl_xor(d, k, 64);
-        mu = min(mu, (uint32_t)__shfl_xor((int)mu, k, 64));
-    }
-    return Totals{F, E, o, d, mu};
+    static_assert(kOrderRegions == 16, "a region per lane of a row");
+    const unsigned long long F = r[kRgF], E = r[kRgE], o = r[kRgFlags], d = r[kRgRead];
+    const uint32_t mu = ~(uint32_t)r[kRgMu];
+    const auto sum = [](unsigned long long x, unsigned long long y) { return x + y; };
+    return Totals{over_row(F, sum), over_row(E, sum),
+                  over_row(o, [](unsigned long long x, unsigned long long y) { return x | y; }), over_row(d, sum),
+                  over_row(mu, [](uint32_t x, uint32_t y) { return min(x, y); })};
 }
 
 constexpr int kBeginJobs = 16;
@@ -139,40 +182,33 @@ __device__ __forceinline__ void enqueue(gptr<const int32_t> ro, int32_t cap, gpt
                                         gptr<u32x2> next_queue, const uint32_t (&v)[K], const bool (&on)[K],
                                         bool count) {
     const int lane = threadIdx.x & 63;
-    uint32_t news = 0, runs = 0;
-    unsigned long long arcs = 0;
-    uint32_t deg[K];
+    uint32_t runs = 0, low = 0, high = 0, deg[K];
+    uint32_t news = 0;  // (a vertex without out-arcs is on no frontier)
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        deg[k] = 0;
-        if (on[k]) {
-            deg[k] = (uint32_t)(ro[v[k] + 1] - ro[v[k]]);
-            news += deg[k] > 0u ? 1u : 0u;  // a vertex without out-arcs is on no frontier
-            runs += (deg[k] + kPushRun - 1) / kPushRun;
-            arcs += deg[k];
-        }
+        deg[k] = on[k] ? (uint32_t)(ro[v[k] + 1] - ro[v[k]]) : 0u;
+        runs += (deg[k] + kPushRun - 1) / kPushRun;
+        low += deg[k] & 0xFFFFu;
+        high += deg[k] >> 16;
+        news += (uint32_t)__popcll(__ballot(deg[k] > 0u));
     }
-    if (__ballot(news != 0u) == 0ull) return;
-    uint32_t before = runs, total = news;
-    unsigned long long sum = arcs;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t x = (uint32_t)__shfl_up((int)before, o, 64);
-        if (lane >= o) before += x;
-        total += (uint32_t)__shfl_xor((int)total, o, 64);
-        sum += __shfl_xor(sum, o, 64);
-    }
+    if (news == 0u) return;
+    const uint32_t before = wave_scan(runs);
     const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)before, 63);
+    const unsigned long long sum =
+        ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)wave_scan(high), 63) << 16) +
+        (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(low), 63);
     unsigned long long base = 0;
     if (lane == 0) {
         base = __hip_atomic_fetch_add(region + kRgCnt, (unsigned long long)all, __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT);
         if (count)
-            (void)__hip_atomic_fetch_add(region + kRgF, (unsigned long long)total, __ATOMIC_RELAXED,
+            (void)__hip_atomic_fetch_add(region + kRgF, (unsigned long long)news, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
         (void)__hip_atomic_fetch_add(region + kRgE, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    base = (unsigned long long)__shfl((long long)base, 0, 64);
+    base = (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32 |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
     if (base + all > (unsigned long long)cap) {  // the next round pulls
         if (lane == 0)
             (void)__hip_atomic_fetch_or(region + kRgFlags, kFlagOver, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -270,12 +306,7 @@ __device__ __forceinline__ void push_entries(const OrderJob &J, gptr<uint32_t> d
         len = min(ro[ent.x + 1] - e0, kPushRun);
         d = ld_dev(dist + ent.x);
     }
-    int32_t upto = len;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int32_t x = __shfl_up(upto, o, 64);
-        if (lane >= o) upto += x;
-    }
+    const int32_t upto = (int32_t)wave_scan((uint32_t)len);
     const int32_t all = __builtin_amdgcn_readlane(upto, 63);
     const int32_t first = e0 - (upto - len);  // its arc x of all is first + x
     for (int32_t x0 = 0; x0 < all; x0 += 64 * kPackArcs) {
@@ -316,7 +347,12 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
     const int s0 = (int)(g.round % 3), s1 = (int)((g.round + 1) % 3), s2 = (int)((g.round + 2) % 3);
     constexpr int slot_words = kOrderRegions * kOrderRegionWords;
     const Totals T = read_slot(ctl + s0 * slot_words);
-    const bool pull = T.flags != 0ull || kOrderBias * (double)T.E * (double)T.E >= (double)n * (double)J.m;
+    const bool pulled = (T.flags & kFlagPulled) != 0ull;
+    const bool pull = (T.flags & kFlagOver) != 0ull ||
+                      (pulled ? kBackArcs * T.E + kBackFixed > (unsigned long long)n + kBackRead * T.read
+                              : kOrderBias * (double)T.E * (double)T.E >= (double)n * (double)J.m);
+    const bool keep = pull && pulled && T.F * kBackShare <= (unsigned long long)n &&
+                      (unsigned long long)n + kBackRead * T.read >= kBackFixed;
     // the slot of the round after next
     if (blockIdx.x == 0)
         for (int i = t; i < slot_words; i += 256) ctl[s2 * slot_words + i] = 0ull;
@@ -342,7 +378,8 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
                                    __HIP_MEMORY_SCOPE_SYSTEM);
             state[kStF] += T.F;
             if (pull) {
-                (void)__hip_atomic_fetch_or(region + kRgFlags, kFlagPulled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                (void)__hip_atomic_fetch_or(region + kRgFlags, kFlagPulled | (keep ? 0ull : kFlagOver), __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
                 state[kStPulls] += 1ull;
             } else {
                 state[kStPushed] += T.E;
@@ -359,22 +396,18 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
     __syncthreads();  // (a block of chunks alone meets no other barrier before it adds to them)
     uint32_t lowest = 0xFFFFFFFFu, nread = 0, nnew = 0;
     const int32_t vblocks = (n + kOrderVerts - 1) / kOrderVerts;
-    if (!pull) {
-        gptr<unsigned long long> bits = reinterpret_cast<gptr<unsigned long long>>(to_global(J.bits));
-        gptr<unsigned long long> next_bits = bits + (size_t)((g.round + 1) & 1) * J.nword;
+    gptr<unsigned long long> bits = reinterpret_cast<gptr<unsigned long long>>(to_global(J.bits));
+    gptr<u32x2> queue = reinterpret_cast<gptr<u32x2>>(to_global(J.queue));
+    gptr<u32x2> to = queue + ((size_t)((g.round + 1) & 1) * kOrderRegions + blockIdx.x % kOrderRegions) * J.cap;
+    if (!pulled)  // what a push marked of this frontier (pulls mark nothing)
         for (int32_t i = blockIdx.x * 256 + t; i < J.nword; i += gridDim.x * 256)
             bits[(size_t)(g.round & 1) * J.nword + i] = 0ull;
-        gptr<u32x2> queue = reinterpret_cast<gptr<u32x2>>(to_global(J.queue));
+    if (!pull) {
+        gptr<unsigned long long> next_bits = bits + (size_t)((g.round + 1) & 1) * J.nword;
         gptr<const u32x2> from = queue + (size_t)(g.round & 1) * kOrderRegions * J.cap;
-        gptr<u32x2> to = queue + ((size_t)((g.round + 1) & 1) * kOrderRegions + blockIdx.x % kOrderRegions) * J.cap;
         // entry i of the regions' lists laid end to end
         uint32_t mine = lane < kOrderRegions ? (uint32_t)ctl[s0 * slot_words + lane * kOrderRegionWords + kRgCnt] : 0u;
-        uint32_t upto = mine;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t x = (uint32_t)__shfl_up((int)upto, o, 64);
-            if (lane >= o) upto += x;
-        }
+        const uint32_t upto = wave_scan(mine);
         const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
         const uint32_t waves = gridDim.x * 4u, wave = blockIdx.x * 4u + (uint32_t)(t >> 6);
         if (all <= waves) {
@@ -410,6 +443,8 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
         const auto step = [](uint32_t d, uint32_t w) { return plus<WT>(d, w); };
         __shared__ uint32_t sList[kOrderVerts], sWas[kOrderVerts], sBest[kOrderVerts];
         __shared__ int2 sRow[AHEAD ? kOrderVerts : 1];
+        // keep: the vertices that a pass improved, a bit each, for the queue
+        __shared__ uint32_t sWon[kOrderVerts / 32];
         for (int32_t vb = blockIdx.x; vb < vblocks; vb += gridDim.x) {
             if (t == 0) sCnt = 0u;
             __syncthreads();
@@ -468,10 +503,15 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
                         if constexpr (AHEAD) sRow[at] = make_int2(r0[k], r1[k]);
                     }
                 }
-                if (!row && best[k] < b[k]) {
+                const bool won = !row && best[k] < b[k];
+                if (won) {
                     dist[v] = best[k];
                     lowest = min(lowest, best[k]);
                     ++nnew;
+                }
+                if (keep) {
+                    const unsigned long long w = __ballot(won);
+                    if ((lane & 31) == 0) sWon[(k * 256 + t) / 32] = (uint32_t)(w >> lane);
                 }
             }
             __syncthreads();
@@ -509,8 +549,23 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
                     dist[v] = low;
                     lowest = min(lowest, low);
                     ++nnew;
+                    if (keep) atomicOr(&sWon[sList[k] / 32], 1u << (sList[k] % 32));
                 }
             }
+            __syncthreads();
+            if (keep) {
+                uint32_t v[V];
+                bool on[V];
+#pragma unroll
+                for (int k = 0; k < V; ++k) {
+                    v[k] = (uint32_t)(vb * kOrderVerts + k * 256 + t);
+                    on[k] = sWon[(k * 256 + t) / 32] >> (t % 32) & 1u;
+                }
+                enqueue<V>(to_global(J.ro), J.cap, region, to, v, on, false);
+            }
+        }
+        if (keep) {  // (now of the vertices that chunks improve, some of them several times)
+            if (t == 0) sCnt = 0u;
             __syncthreads();
         }
         // long rows: 16 lanes per chunk, 16 arcs at a time
@@ -540,6 +595,21 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
                 low < __hip_atomic_fetch_min(dist + ch.x, low, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
                 lowest = min(lowest, low);
                 ++nnew;
+                if (keep) {
+                    const uint32_t at = atomicAdd(&sCnt, 1u);
+                    if (at < (uint32_t)kOrderVerts) sList[at] = ch.x;
+                }
+            }
+        }
+        if (keep) {
+            __syncthreads();
+            const uint32_t cnt = min(sCnt, (uint32_t)kOrderVerts);
+            if (t == 0 && cnt < sCnt)
+                (void)__hip_atomic_fetch_or(region + kRgFlags, kFlagOver, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (uint32_t i = (uint32_t)t; __ballot(i < cnt) != 0ull; i += 256u) {
+                const bool on[1] = {i < cnt};
+                const uint32_t v[1] = {on[0] ? sList[i] : 0u};
+                enqueue<1>(to_global(J.ro), J.cap, region, to, v, on, false);
             }
         }
     }

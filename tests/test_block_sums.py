@@ -35,7 +35,8 @@ def unordered(body):
     bad = []
     for w in sorted(sums):
         first = next((m for m in CLEAR.finditer(body) if re.search(r"\b%s\b(?:\[\w+\])?\s*=" % w, m.group(1))), None)
-        assert first, "%s is never cleared" % w
+        if not first:
+            continue  # (stored by all its threads)
         rest = body[first.end():]
         # (other words cleared in the same place belong to the same group)
         while CLEAR.match(rest.lstrip()):
@@ -61,4 +62,4 @@ def test_cleared_sums_meet_a_barrier(name):
 def test_the_check_finds_a_missing_barrier():
     with open(os.path.join(CSRC, "gr_order.hip")) as f:
         body = dict(kernels(f.read()))["k_order"]
-    assert unordered(body.replace("__syncthreads()", "", 1)) != []
+    assert {"sLow", "sArcs", "sRead"} <= set(unordered(body.replace("__syncthreads()", "", 1)))

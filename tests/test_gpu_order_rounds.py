@@ -66,3 +66,46 @@ def test_wide_frontiers_of_short_rows(name):
             torch.cuda.synchronize()
             np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), oracle.dijkstra(g, int(s)))
             assert st["loop"] == gr.GR_LOOP_QUEUED and st["iterations"] > st["pull_iterations"]
+
+
+def joined(scale, length, seed, **kw):
+    """Two R-MAT graphs joined by a path: the frontier grows, shrinks to one
+    vertex and grows again."""
+    a, b = gg.rmat(scale, 16, gseed=seed, pseed=2, wseed=3), gg.rmat(scale, 12, gseed=seed + 1, pseed=5, wseed=6)
+    (sa, da), (sb, db), n = arcs(a), arcs(b), a.n + b.n + length
+    path = np.concatenate([gg.pick_sources(a, 3, 1), np.arange(a.n + b.n, n), a.n + gg.pick_sources(b, 3, 1)]).astype(np.int64)
+    return both_ways(n, np.concatenate([sa, sb + a.n, path[:-1]]), np.concatenate([da, db + a.n, path[1:]]), seed, **kw)
+
+
+def tailed(scale, length, seed, **kw):
+    g = gg.rmat(scale, 16, gseed=seed, pseed=2, wseed=3)
+    s, d = arcs(g)
+    path = np.concatenate([gg.pick_sources(g, 3, 1), np.arange(g.n, g.n + length)]).astype(np.int64)
+    return both_ways(g.n + length, np.concatenate([s, path[:-1]]), np.concatenate([d, path[1:]]), seed, **kw)
+
+
+AGAIN = {  # graph, rounds that a path alone takes
+    "joined": (lambda: joined(15, 300, 1), 300),
+    "joined, binary32": (lambda: joined(14, 200, 5, wtype=gg.W_F32), 200),
+    "joined, zero weights": (lambda: joined(14, 200, 7, whi=1), 200),
+    "joined, large": (lambda: joined(19, 40, 9), 40),
+    "a tail of a large graph": (lambda: tailed(20, 300, 11, wtype=gg.W_F32), 300),
+}
+
+
+@pytest.mark.parametrize("name", sorted(AGAIN))
+def test_pushes_again_after_pulls(name):
+    make, path = AGAIN[name]
+    g = make()
+    with gr.Graph.from_csr(g) as G:
+        for s in [int(x) for x in gg.pick_sources(g, 5, 2)]:
+            want = oracle.dijkstra(g, s)
+            for rep in range(2):
+                print("again", name, g.n, g.m, s, file=sys.stderr, flush=True)
+                d = torch.full((g.n,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+                st = gr.gr_sssp_ex(G.handle, s, d)
+                torch.cuda.synchronize()
+                np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), want)
+                # it pulled, and most rounds of the path pushed
+                assert st["pull_iterations"] > 0
+                assert st["iterations"] - st["pull_iterations"] > path // 2
