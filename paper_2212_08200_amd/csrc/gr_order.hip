@@ -78,6 +78,8 @@ constexpr int kPushRun = kOrderRun;  // arcs per queue entry
 constexpr int kRgF = 0, kRgE = 1, kRgMu = 2, kRgCnt = 3, kRgFlags = 4, kRgRead = 5;
 // Over: the queue does not hold the frontier; Pulled: the round before pulled.
 constexpr unsigned long long kFlagOver = 1ull, kFlagPulled = 2ull;
+// Batches: the frontier's masks are set; those of the frontier before were.
+constexpr unsigned long long kFlagMarked = 4ull, kFlagWasMarked = 8ull;
 // State words after the slots (block 0 of each launch keeps them).
 constexpr int kStDone = 0, kStPulls = 2, kStF = 3, kStPushed = 4, kStPulledArcs = 5;
 
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(256) void k_order_begin(BeginArgs a) {
 // Puts up to K vertices per lane on the next frontier: their runs go to the
 // region's list, in one atomic per wave.  count: whether the vertices are
 // counted too.
-template <int K>
+template <int K, int RUN>
 __device__ __forceinline__ void enqueue(gptr<const int32_t> ro, int32_t cap, gptr<unsigned long long> region,
                                         gptr<u32x2> next_queue, const uint32_t (&v)[K], const bool (&on)[K],
                                         bool count) {
@@ -187,7 +189,7 @@ __device__ __forceinline__ void enqueue(gptr<const int32_t> ro, int32_t cap, gpt
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         deg[k] = on[k] ? (uint32_t)(ro[v[k] + 1] - ro[v[k]]) : 0u;
-        runs += (deg[k] + kPushRun - 1) / kPushRun;
+        runs += (deg[k] + RUN - 1) / RUN;
         low += deg[k] & 0xFFFFu;
         high += deg[k] >> 16;
         news += (uint32_t)__popcll(__ballot(deg[k] > 0u));
@@ -217,7 +219,7 @@ __device__ __forceinline__ void enqueue(gptr<const int32_t> ro, int32_t cap, gpt
     uint32_t at = (uint32_t)base + before - runs;
 #pragma unroll
     for (int k = 0; k < K; ++k)
-        for (uint32_t r = 0; r * kPushRun < deg[k]; ++r) next_queue[at++] = u32x2{v[k], r};
+        for (uint32_t r = 0; r * RUN < deg[k]; ++r) next_queue[at++] = u32x2{v[k], r};
 }
 
 constexpr int kPushArcs = kPushRun / 64;  // arcs per lane of an entry
@@ -260,7 +262,7 @@ __device__ __forceinline__ void push_pass(const OrderJob &J, gptr<uint32_t> dist
         v[k] = a[k].x;
         win[k] = win[k] && !(was[k] >> (a[k].x & 63) & 1ull);
     }
-    enqueue<K>(to_global(J.ro), J.cap, region, next_queue, v, win, true);
+    enqueue<K, kPushRun>(to_global(J.ro), J.cap, region, next_queue, v, win, true);
 }
 
 // An entry of the queue: a wave takes its arcs in one pass.
@@ -561,7 +563,7 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
                     v[k] = (uint32_t)(vb * kOrderVerts + k * 256 + t);
                     on[k] = sWon[(k * 256 + t) / 32] >> (t % 32) & 1u;
                 }
-                enqueue<V>(to_global(J.ro), J.cap, region, to, v, on, false);
+                enqueue<V, kPushRun>(to_global(J.ro), J.cap, region, to, v, on, false);
             }
         }
         if (keep) {  // (now of the vertices that chunks improve, some of them several times)
@@ -609,7 +611,7 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
             for (uint32_t i = (uint32_t)t; __ballot(i < cnt) != 0ull; i += 256u) {
                 const bool on[1] = {i < cnt};
                 const uint32_t v[1] = {on[0] ? sList[i] : 0u};
-                enqueue<1>(to_global(J.ro), J.cap, region, to, v, on, false);
+                enqueue<1, kPushRun>(to_global(J.ro), J.cap, region, to, v, on, false);
             }
         }
     }
@@ -653,6 +655,13 @@ constexpr int kStPairs = 6;   // state: their total
 constexpr int kBatchVerts = 4;   // vertices in flight per wave
 constexpr int kBatchArcs = 4;   // arcs of a row in flight (2000 us for the 64 queries below, 2066 with 8)
 constexpr int kBatchRun = 64;   // arcs per queue entry
+constexpr int kBatchKeep = 512;  // vertices that a block of a pull can put on the queue
+// Pushes again as above, where a pull costs a row per vertex: when kBatchBack E
+// <= n + R (1, 4 and 16 measure the same).  16 sources: two R-MAT 17 graphs
+// joined by a path of 300 135 -> 10.5 ms (the session kernels 11.7), R-MAT 14
+// and a path of 1,000 202 -> 13.0 (23.4), R-MAT 20 with a tail of 3,000 200 ->
+// 47 (74); R-MAT 20 1.60 -> 1.52.
+constexpr unsigned long long kBatchBack = 4;
 static_assert(kBatchRun <= kOrderRun && kBatchArcs <= kOrderRun, "steps past a row's end");
 
 struct BatchBeginArgs {
@@ -712,7 +721,7 @@ __global__ __launch_bounds__(64) void k_order_batch_begin(BatchBeginArgs a) {
         ctl[kRgF] = (unsigned long long)F;
         ctl[kRgE] = E;
         ctl[kRgCnt] = fits ? all : 0ull;
-        ctl[kRgFlags] = fits ? 0ull : kFlagOver;
+        ctl[kRgFlags] = kFlagMarked | (fits ? 0ull : kFlagOver);
         ctl[kRgPairs] = pairs;
     }
 }
@@ -754,7 +763,11 @@ __global__ __launch_bounds__(256, 8) void k_order_batch(OrderBatchArgs g) {
     const int s0 = (int)(g.round % 3), s1 = (int)((g.round + 1) % 3), s2 = (int)((g.round + 2) % 3);
     constexpr int slot_words = kOrderRegions * kOrderRegionWords;
     const Totals T = read_slot(ctl + s0 * slot_words);
-    const bool pull = T.flags != 0ull || kOrderBias * (double)T.E * (double)T.E >= (double)n * (double)J.m;
+    const bool pulled = (T.flags & kFlagPulled) != 0ull;
+    const bool pull = (T.flags & kFlagOver) != 0ull ||
+                      (pulled ? kBatchBack * T.E > (unsigned long long)n + T.read
+                              : kOrderBias * (double)T.E * (double)T.E >= (double)n * (double)J.m);
+    const bool keep = pull && pulled && T.F * kBackShare <= (unsigned long long)n;
     gptr<uint32_t> mus = to_global(g.b.mu);
     if (blockIdx.x == 0) {
         for (int i = t; i < slot_words; i += 256) ctl[s2 * slot_words + i] = 0ull;
@@ -783,11 +796,14 @@ __global__ __launch_bounds__(256, 8) void k_order_batch(OrderBatchArgs g) {
             if (g.tag != 0ull) __hip_atomic_store(g.stat, g.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             state[kStF] += T.F;
             if (pull) {
-                (void)__hip_atomic_fetch_or(region + kRgFlags, kFlagPulled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 state[kStPulls] += 1ull;
             } else {
                 state[kStPushed] += T.E;
             }
+            (void)__hip_atomic_fetch_or(region + kRgFlags,
+                                        (pull ? kFlagPulled : 0ull) | (pull && !keep ? kFlagOver : kFlagMarked) |
+                                            (T.flags & kFlagMarked ? kFlagWasMarked : 0ull),
+                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     if (T.F == 0ull) return;
@@ -797,11 +813,12 @@ __global__ __launch_bounds__(256, 8) void k_order_batch(OrderBatchArgs g) {
     gptr<uint32_t> D = to_global(g.b.D);
     gptr<const int32_t> ro = to_global(J.ro);
     __shared__ uint32_t sLow[kBatchLanes];
-    __shared__ uint32_t sNew, sRead;
+    __shared__ uint32_t sNew, sRead, sKept;
+    __shared__ uint32_t sKeep[kBatchKeep];  // keep: the vertices that the block improved
     __shared__ unsigned long long sPairs;
     if (t < kBatchLanes) sLow[t] = 0u;
     if (t == 0) {
-        sNew = sRead = 0u;
+        sNew = sRead = sKept = 0u;
         sPairs = 0ull;
     }
     __syncthreads();
@@ -811,12 +828,14 @@ __global__ __launch_bounds__(256, 8) void k_order_batch(OrderBatchArgs g) {
     const auto row = [&](uint32_t v) { return D + (size_t)v * kBatchLanes + lane; };
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4u + (uint32_t)(t >> 6)));
     const uint32_t waves = gridDim.x * 4u;
-    if (!pull) {
+    // the next round's next masks: what marked the frontier before
+    if (T.flags & kFlagWasMarked)
         for (int64_t i = (int64_t)blockIdx.x * 256 + t; i < n; i += (int64_t)gridDim.x * 256)
             mask[(size_t)s2 * n + i] = 0ull;
-        gptr<u32x2> queue = reinterpret_cast<gptr<u32x2>>(to_global(J.queue));
+    gptr<u32x2> queue = reinterpret_cast<gptr<u32x2>>(to_global(J.queue));
+    gptr<u32x2> to = queue + ((size_t)((g.round + 1) & 1) * kOrderRegions + rg) * J.cap;
+    if (!pull) {
         gptr<const u32x2> from = queue + (size_t)(g.round & 1) * kOrderRegions * J.cap;
-        gptr<u32x2> to = queue + ((size_t)((g.round + 1) & 1) * kOrderRegions + rg) * J.cap;
         gptr<const u32x2> adj = reinterpret_cast<gptr<const u32x2>>(to_global(J.adj));
         uint32_t mine = lane < kOrderRegions ? (uint32_t)ctl[s0 * slot_words + lane * kOrderRegionWords + kRgCnt] : 0u;
         uint32_t upto = mine;
@@ -908,6 +927,14 @@ __global__ __launch_bounds__(256, 8) void k_order_batch(OrderBatchArgs g) {
         for (int i = 0; i < kOrderRegions; ++i) mu = max(mu, mus[(s0 * kOrderRegions + i) * 64 + lane]);
         // (INF for a lane whose frontier is empty: its arcs are all ruled out)
         mu = min(~mu, WT == 1 ? kInfF32 : kInfU32);
+        // a vertex that the lanes w improved (one: by this wave alone) and that goes to the queue
+        const auto kept = [&](uint32_t v, unsigned long long w, bool one) {
+            if (lane != 0) return;
+            if (one) next[v] = w;
+            else if (__hip_atomic_fetch_or(next + v, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0ull) return;
+            const uint32_t at = atomicAdd(&sKept, 1u);
+            if (at < (uint32_t)kBatchKeep) sKeep[at] = v;
+        };
         // the arcs [e, e1) of a row, in order of weight, against the lanes' best
         const auto walk = [&](int32_t e, int32_t e1, uint32_t &best) {
             for (; e < e1; e += kBatchArcs) {
@@ -971,6 +998,7 @@ __global__ __launch_bounds__(256, 8) void k_order_batch(OrderBatchArgs g) {
                 const unsigned long long x = (unsigned long long)__popcll(w) * (uint32_t)(rc[v0 + k + 1] - rc[v0 + k]);
                 pairs += lane == 0 ? x : 0ull;
                 ++nnew;
+                if (keep) kept(v0 + k, w, true);
             }
         }
         // long rows: a wave per chunk
@@ -988,6 +1016,18 @@ __global__ __launch_bounds__(256, 8) void k_order_batch(OrderBatchArgs g) {
             const unsigned long long x = (unsigned long long)__popcll(w) * (uint32_t)(rc[ch.x + 1] - rc[ch.x]);
             pairs += lane == 0 ? x : 0ull;
             ++nnew;
+            if (keep) kept(ch.x, w, false);
+        }
+        if (keep) {
+            __syncthreads();
+            const uint32_t cnt = min(sKept, (uint32_t)kBatchKeep);
+            if (t == 0 && cnt < sKept)
+                (void)__hip_atomic_fetch_or(region + kRgFlags, kFlagOver, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (uint32_t i = (uint32_t)t; __ballot(i < cnt) != 0ull; i += 256u) {
+                const bool on[1] = {i < cnt};
+                const uint32_t v[1] = {on[0] ? sKeep[i] : 0u};
+                enqueue<1, kBatchRun>(ro, J.cap, region, to, v, on, false);
+            }
         }
     }
     if (low != 0u) atomicMax(&sLow[lane], low);

@@ -109,3 +109,22 @@ def test_pushes_again_after_pulls(name):
                 # it pulled, and most rounds of the path pushed
                 assert st["pull_iterations"] > 0
                 assert st["iterations"] - st["pull_iterations"] > path // 2
+
+
+@pytest.mark.parametrize("name", sorted(AGAIN))
+def test_batch_pushes_again_after_pulls(name):
+    g = AGAIN[name][0]()
+    srcs = np.asarray(list(gg.pick_sources(g, 5, 9)) + [g.n - 1, 0], np.int32)  # (one on the path)
+    with gr.Graph.from_csr(g) as G:
+        rows = torch.empty(len(srcs), g.n, dtype=torch.int32, device="cuda")
+        for rep in range(2):
+            print("batch again", name, g.n, g.m, file=sys.stderr, flush=True)
+            rows.fill_(0x5A5A5A5A)
+            st = gr.gr_sssp_batch_ex(G.handle, srcs, rows)
+            torch.cuda.synchronize()
+            got = rows.cpu().numpy().view(np.uint32)
+            for i in (0, 4, 9, 10):
+                np.testing.assert_array_equal(got[i], oracle.dijkstra(g, int(srcs[i])), err_msg=str(srcs[i]))
+            # the arcs read: at most all of them in each of the fifteen or so
+            # rounds that either end's growth takes, not in those of the path
+            assert st["rounds"] > AGAIN[name][1] and st["edges_pushed"] < 30 * g.m
