@@ -250,7 +250,9 @@ typedef struct {
                            hands the next round a list of them instead of a filter pass
                            (graphs of degree <= 64, push only, no near-far split) */
     int32_t barrier_timeout_us; /* device-driven loop: bound on one grid-barrier wait;
-                                   0 = 20 s.  Exceeding it ends the query with GR_ERR_HIP. */
+                                   0 = 20 s.  Exceeding it ends the query with GR_ERR_HIP.
+                                   Loop over tiles: bound on a wait during which no tile
+                                   of the query ran (10 ms at least, 21 s at most). */
     uint32_t delta;     /* near-far split width, in the weight type (a uint32 value, or the
                            bits of a positive finite binary32): improved vertices whose
                            distance is not below the threshold are held back until the

@@ -45,10 +45,17 @@
 //              one of its own tokens on, and returns what it holds when it
 //              has nothing to do, after its writes were performed.  active =
 //              0 thus means that no offer is left anywhere: the query ends.
+//   status     bits 0 / 1: the query ended / a wait did not.  A workgroup may
+//              wait for as long as others run tiles (on a path all but one or
+//              two do), so what a wait is held against is their progress: the
+//              rest of the word counts it, every few hundred microseconds
+//              while any tile runs.
 // Any single resident workgroup makes progress alone, so the launch needs no
 // co-residency.  dist is both the output and what survives of a tile between
 // runs: the holder writes the words it lowered before it lets the tile go.
 #include "gr_tile.h"
+
+#include <algorithm>
 
 #include "gr_device.h"
 
@@ -63,10 +70,15 @@ constexpr int kRegs = 5;  // arcs out, and mail words, that the two courier wave
 // Tokens a workgroup takes at once; it does so below what one pass over the arcs
 // out can pass on.
 constexpr int kTileTokens = 4 * kTileMaxExt;
-constexpr uint64_t kTileIdleTicks = 100;  // wall clock ticks (10 ns) a workgroup keeps its tokens while it waits
+// The receiving wave counts progress every so many passes (0.2 to 0.5 ms; by the
+// clock, looked at every 16 passes, the meshes below took 1-2% longer), and a
+// wait is bounded by no less than kTileMinSpin.
+constexpr uint32_t kTileLooks = 256, kTileMinSpin = 1000000;
+constexpr uint32_t kTileIdleTicks = 100;  // wall clock ticks (10 ns) a workgroup keeps its tokens while it waits
 
 // Control words (8 bytes each, hot ones on 256-byte lines of their own).
 constexpr int kTcStatus = 0;
+constexpr uint32_t kTcDone = 1, kTcLate = 2, kTcBeat = 4;
 constexpr int kTcHead = 32;
 constexpr int kTcTail = 64;
 constexpr int kTcActive = 96;
@@ -95,7 +107,7 @@ struct TileArgs {
     uint32_t *ring;
     uint32_t mask;  // ring entries - 1
     unsigned long long *ctl;
-    uint64_t spin_ticks;
+    uint32_t spin;  // bound on a wait without progress, wall clock ticks
     unsigned long long *stat;
 };
 
@@ -139,6 +151,10 @@ __device__ __forceinline__ uint32_t tile_plus(uint32_t d, uint32_t w) {
     else return __builtin_elementwise_add_sat(d, WT == 2 ? 1u : w);
 }
 
+__device__ __forceinline__ uint32_t tile_status(gptr<unsigned long long> ctl) {
+    return ld_dev(reinterpret_cast<gptr<uint32_t>>(ctl + kTcStatus));
+}
+
 // A lane raises flag[q] and queues q if no workgroup holds it.  True when it
 // passed a token on.
 __device__ __forceinline__ bool tile_wake(const TileArgs &a, gptr<uint32_t> flags, uint32_t job, uint32_t q) {
@@ -149,7 +165,7 @@ __device__ __forceinline__ bool tile_wake(const TileArgs &a, gptr<uint32_t> flag
         const unsigned long long p =
             __hip_atomic_fetch_add(ctl + kTcTail, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         gptr<uint32_t> slot = to_global(a.ring) + ((uint32_t)p & a.mask);
-        while (ld_dev(slot) != 0u && ld_dev(ctl + kTcStatus) == 0ull) __builtin_amdgcn_s_sleep(1);
+        while (ld_dev(slot) != 0u && (tile_status(ctl) & (kTcDone | kTcLate)) == 0u) __builtin_amdgcn_s_sleep(1);
         __hip_atomic_store(slot, (job << 24 | q) + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     return !(old & 1u);
@@ -228,7 +244,21 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
         sTok = 0;
         const unsigned long long old =
             __hip_atomic_fetch_add(ctl + kTcActive, 0ull - x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (old == x) __hip_atomic_store(ctl + kTcStatus, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (old == x) (void)__hip_atomic_fetch_or(ctl + kTcStatus, (unsigned long long)kTcDone, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+    };
+    uint32_t looks = 0;  // the receiving wave's passes
+    // one lane, waiting since t0; seen: the status word that t0 belongs to
+    const auto waiting = [&](uint32_t &t0, uint32_t s, uint32_t &seen) {
+        const uint32_t now = (uint32_t)wall_clock64();
+        if (s != seen) {
+            seen = s;
+            t0 = now;
+        }
+        if (now - t0 > kTileIdleTicks) give_tokens();
+        if (now - t0 > a.spin)
+            (void)__hip_atomic_fetch_or(ctl + kTcStatus, (unsigned long long)kTcLate, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
     };
     for (;;) {
         // 1. the next tile
@@ -238,20 +268,17 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
                 const unsigned long long p =
                     __hip_atomic_fetch_add(ctl + kTcHead, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 gptr<uint32_t> slot = ring + ((uint32_t)p & a.mask);
-                const uint64_t t0 = wall_clock64();
+                uint32_t since = (uint32_t)wall_clock64(), seen = 0u;
                 for (;;) {
                     const uint32_t x = ld_dev(slot);
-                    const unsigned long long s = ld_dev(ctl + kTcStatus);
+                    const uint32_t s = tile_status(ctl);
                     if (x != 0u) {
                         __hip_atomic_store(slot, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         cmd = (int)(x - 1u);
                         break;
                     }
-                    if (s != 0ull) break;
-                    const uint64_t dt = wall_clock64() - t0;
-                    if (dt > kTileIdleTicks) give_tokens();
-                    if (dt > a.spin_ticks)
-                        __hip_atomic_store(ctl + kTcStatus, 3ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if ((s & (kTcDone | kTcLate)) != 0u) break;
+                    waiting(since, s, seen);
                     __builtin_amdgcn_s_sleep(2);
                 }
                 sCmd = cmd;
@@ -521,6 +548,9 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
                 if (!quiet) {
                     snap = (uint32_t)ran();
                     moved = false;
+                    if ((++looks % kTileLooks) == 0u && lane == 0)
+                        (void)__hip_atomic_fetch_add(ctl + kTcStatus, (unsigned long long)kTcBeat, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
                     continue;
                 }
                 // its distances go to memory; it waits for mail, or is let go
@@ -528,7 +558,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
                 __syncthreads();
                 int next = 0;  // 0: let go, 1: again
                 if (lane == 0) {
-                    const uint64_t t0 = wall_clock64();
+                    uint32_t since = (uint32_t)wall_clock64(), seen = 0u;
                     for (;;) {
                         if (ld_dev(flag) & 1u) {
                             (void)__hip_atomic_exchange(flag, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -537,8 +567,8 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
                             next = 1;
                             break;
                         }
-                        const uint64_t dt = wall_clock64() - t0;
-                        const bool over = ld_dev(ctl + kTcStatus) != 0ull;
+                        const uint32_t s = tile_status(ctl);
+                        const bool over = (s & (kTcDone | kTcLate)) != 0u;
                         if (over || ld_dev(ctl + kTcTail) > ld_dev(ctl + kTcHead)) {
                             uint32_t held = 2u;
                             if (__hip_atomic_compare_exchange_strong(flag, &held, 0u, __ATOMIC_RELAXED,
@@ -547,9 +577,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
                                 break;
                             continue;
                         }
-                        if (dt > kTileIdleTicks) give_tokens();
-                        if (dt > a.spin_ticks)
-                            __hip_atomic_store(ctl + kTcStatus, 3ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        waiting(since, s, seen);
                         __builtin_amdgcn_s_sleep(1);
                     }
                     sCmd = next;
@@ -576,7 +604,9 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
         if (x + 1ull == gridDim.x) {  // the last one: statistics to the host
             __hip_atomic_store(a.stat + 1, ld_dev(ctl + kTcArcs), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             __hip_atomic_store(a.stat + 2, ld_dev(ctl + kTcItems), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            __hip_atomic_store(a.stat + 0, ld_dev(ctl + kTcStatus), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            const uint32_t w = tile_status(ctl);
+            __hip_atomic_store(a.stat + 0, w & kTcDone ? 1ull : w & kTcLate ? 3ull : 0ull, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
 }
@@ -623,7 +653,7 @@ hipError_t launch_tiles(const TileSet *const *sets, const int32_t *srcs, uint32_
     const uint32_t rl = ring_entries(tiles);
     a.mask = rl - 1;
     p += al256((size_t)rl * 4);
-    a.spin_ticks = spin_ticks;
+    a.spin = (uint32_t)std::clamp<uint64_t>(spin_ticks, kTileMinSpin, INT32_MAX);
     a.stat = stat;
     for (int32_t b = 0; b < k; b += kInitJobs) {
         TileInitArgs ia{};
