@@ -1200,13 +1200,14 @@ static gr_status run_lds_batch(const gr_graph *const *graphs, const int32_t *src
 
 // Tiled asynchronous loop: k queries on graphs with tiles (of one slot count),
 // rows[i] receiving query i's distances; one initialisation and one persistent
-// launch for all of them, and one wait.  us (optional): the launches' time.
+// launch for all of them, and one wait.  count: whether the totals are wanted;
+// us (optional): the launches' time.
 struct TileTotals {
     int64_t arcs = 0, items = 0, launches = 0;
 };
 // Enqueues them; hp: kTileStatWords pinned words.
 static gr_status tiles_enqueue(const gr_graph *const *graphs, const int32_t *srcs, int32_t k, uint32_t *const *rows,
-                               int wt, hipStream_t st, int64_t timeout_us, unsigned long long *hp, hipEvent_t *ev) {
+                               int wt, hipStream_t st, int64_t timeout_us, bool count, unsigned long long *hp, hipEvent_t *ev) {
     DeviceInfo di;
     gr_status s = device_info(graphs[0]->device, &di);
     if (s != GR_OK) return s;
@@ -1217,7 +1218,7 @@ static gr_status tiles_enqueue(const gr_graph *const *graphs, const int32_t *src
     const uint64_t spin = (uint64_t)timeout_us * (uint64_t)di.wall_khz / 1000ull;
     for (int i = 0; i < kTileStatWords; ++i) hp[i] = 0ull;
     if (ev) (void)hipEventRecord(ev[0], st);
-    hipError_t e = launch_tiles(sets, srcs, rows, k, wt, ws, di.num_cu, spin, hp, st);
+    hipError_t e = launch_tiles(sets, srcs, rows, k, wt, ws, di.num_cu, spin, count, hp, st);
     if (ev) (void)hipEventRecord(ev[1], st);
     const hipError_t e2 = hipFreeAsync(ws, st);
     if (e == hipSuccess) e = e2;
@@ -1235,12 +1236,12 @@ static gr_status tiles_result(const unsigned long long *hp, int64_t timeout_us, 
 }
 
 static gr_status run_tiles(const gr_graph *const *graphs, const int32_t *srcs, int32_t k, uint32_t *const *rows,
-                           int wt, hipStream_t st, int64_t timeout_us, TileTotals *tot, double *us) {
+                           int wt, hipStream_t st, int64_t timeout_us, bool count, TileTotals *tot, double *us) {
     unsigned long long *hp = pinned_slot();
     if (!hp) return fail(GR_ERR_OUT_OF_MEMORY, "pinned host buffer");
     hipEvent_t ev[2] = {nullptr, nullptr};
     const bool timed = us && hipEventCreate(&ev[0]) == hipSuccess && hipEventCreate(&ev[1]) == hipSuccess;
-    gr_status s = tiles_enqueue(graphs, srcs, k, rows, wt, st, timeout_us, hp, timed ? ev : nullptr);
+    gr_status s = tiles_enqueue(graphs, srcs, k, rows, wt, st, timeout_us, count, hp, timed ? ev : nullptr);
     const hipError_t e = s == GR_OK ? hipStreamSynchronize(st) : hipSuccess;
     if (timed && s == GR_OK && e == hipSuccess) {
         float ms = 0.f;
@@ -1259,7 +1260,8 @@ static gr_status run_tiled(const gr_graph *g, int32_t src, uint32_t *dist, hipSt
     TileTotals tot;
     double us = 0;
     const int wt = rc.dg->wt == 2 ? 2 : g->plain.wt;
-    gr_status s = run_tiles(&g, &src, 1, &dist, wt, st, rc.barrier_timeout_us, &tot, rc.timing ? &us : nullptr);
+    gr_status s = run_tiles(&g, &src, 1, &dist, wt, st, rc.barrier_timeout_us, stats != nullptr, &tot,
+                            rc.timing ? &us : nullptr);
     if (s != GR_OK) return s;
     if (stats) {
         gr_sssp_stats local{};
@@ -1420,7 +1422,8 @@ static std::vector<std::vector<int32_t>> own_groups(const gr_graph *const *graph
 }
 
 static gr_status tiles_group_enqueue(const gr_graph *const *graphs, const int32_t *srcs, uint32_t *const *rows,
-                                     const std::vector<int32_t> &idx, hipStream_t st, unsigned long long *hp) {
+                                     const std::vector<int32_t> &idx, hipStream_t st, bool count,
+                                     unsigned long long *hp) {
     const gr_graph *gs[kTileMaxJobs];
     int32_t ss[kTileMaxJobs];
     uint32_t *rs[kTileMaxJobs];
@@ -1429,12 +1432,12 @@ static gr_status tiles_group_enqueue(const gr_graph *const *graphs, const int32_
         ss[j] = srcs[idx[j]];
         rs[j] = rows[idx[j]];
     }
-    return tiles_enqueue(gs, ss, (int32_t)idx.size(), rs, gs[0]->plain.wt, st, kBarrierTimeoutUs, hp, nullptr);
+    return tiles_enqueue(gs, ss, (int32_t)idx.size(), rs, gs[0]->plain.wt, st, kBarrierTimeoutUs, count, hp, nullptr);
 }
 
 // Such a group (weighted queries); rounds receives each query's.
 static gr_status run_own_group(const gr_graph *const *graphs, const int32_t *srcs, uint32_t *const *rows,
-                               const std::vector<int32_t> &idx, hipStream_t st, TileTotals *tot,
+                               const std::vector<int32_t> &idx, hipStream_t st, bool count, TileTotals *tot,
                                std::vector<int32_t> *rounds) {
     const gr_graph *gs[kTileMaxJobs];
     int32_t ss[kTileMaxJobs];
@@ -1448,7 +1451,7 @@ static gr_status run_own_group(const gr_graph *const *graphs, const int32_t *src
     }
     if (gs[0]->tiles.ntiles > 0) {
         for (int32_t j = 0; j < k; ++j) (*rounds)[j] = source_rounds(gs[j], ss[j]);
-        return run_tiles(gs, ss, k, rs, gs[0]->plain.wt, st, kBarrierTimeoutUs, tot, nullptr);
+        return run_tiles(gs, ss, k, rs, gs[0]->plain.wt, st, kBarrierTimeoutUs, count, tot, nullptr);
     }
     const unsigned long long *x = nullptr;
     int64_t launches = 0;
@@ -1679,7 +1682,7 @@ static gr_status run_own_fixed(const gr_graph *g, int32_t src, uint32_t *dist, h
         gr_status s = device_info(g->device, &di);
         if (s != GR_OK) return s;
         const uint64_t spin = (uint64_t)rc.barrier_timeout_us * (uint64_t)di.wall_khz / 1000ull;
-        HIP_TRY(launch_tiles(&set, &src, &dist, 1, dg.wt, ws, di.num_cu, spin, stat, st));
+        HIP_TRY(launch_tiles(&set, &src, &dist, 1, dg.wt, ws, di.num_cu, spin, false, stat, st));
         HIP_TRY(read(stat, 1));
         if (h[0] == 3ull)
             return fail(GR_ERR_HIP, "tiled loop: a wait exceeded %lld us", (long long)rc.barrier_timeout_us);
@@ -1809,7 +1812,7 @@ static gr_status run_single_auto(const gr_graph *g, int32_t src, uint32_t *dist,
     if (s != GR_OK) return s;
     const int loop = g->auto_loop;
     gr_sssp_stats one{};
-    if (wants_tiles(g, nullptr)) s = run_tiled(g, src, dist, st, rc, &one);
+    if (wants_tiles(g, nullptr)) s = run_tiled(g, src, dist, st, rc, stats ? &one : nullptr);
     else if (wants_order(g, nullptr)) s = run_ordered(g, src, dist, st, rc, &one);
     else if (loop == GR_LOOP_ASYNC) s = run_async(g, src, dist, st, rc, &one);
     else if (loop == GR_LOOP_LDS) s = run_lds(g, src, dist, st, rc, &one);
@@ -2122,7 +2125,8 @@ extern "C" gr_status gr_sssp_multi(const gr_graph *const *graphs, const int32_t 
         size_t run = 0;
         if (beside)
             for (const auto &idx : groups)
-                if (s == GR_OK && tiled(idx)) s = tiles_group_enqueue(graphs, srcs, rows.data(), idx, side.st, hp + run++ * 4);
+                if (s == GR_OK && tiled(idx)) 
+                    s = tiles_group_enqueue(graphs, srcs, rows.data(), idx, side.st, stats != nullptr, hp + run++ * 4);
         gr_multi_stats sum{};
         const auto add = [&](const TileTotals &tot, const std::vector<int32_t> &idx, const std::vector<int32_t> &rounds) {
             sum.edges_pushed += tot.arcs;
@@ -2137,7 +2141,7 @@ extern "C" gr_status gr_sssp_multi(const gr_graph *const *graphs, const int32_t 
             if (s != GR_OK || (beside && tiled(idx))) continue;
             TileTotals tot;
             std::vector<int32_t> rounds;
-            s = run_own_group(graphs, srcs, rows.data(), idx, st, &tot, &rounds);
+            s = run_own_group(graphs, srcs, rows.data(), idx, st, stats != nullptr, &tot, &rounds);
             if (s == GR_OK) add(tot, idx, rounds);
         }
         gr_multi_stats rest{};
@@ -2390,7 +2394,7 @@ extern "C" gr_status gr_sssp_batch_ex(const gr_graph *g, const int32_t *srcs, in
     if (wants_tiles(g, nullptr)) {
         std::vector<const gr_graph *> gs((size_t)k, g);
         TileTotals tot;
-        s = run_tiles(gs.data(), srcs, k, rows.data(), g->plain.wt, st, kBarrierTimeoutUs, &tot, nullptr);
+        s = run_tiles(gs.data(), srcs, k, rows.data(), g->plain.wt, st, kBarrierTimeoutUs, stats != nullptr, &tot, nullptr);
         if (s == GR_OK && stats) {
             *stats = gr_multi_stats{};
             for (int32_t i = 0; i < k; ++i) stats->rounds = std::max(stats->rounds, source_rounds(g, srcs[i]));
@@ -2753,7 +2757,7 @@ static void server_own_worker(gr_server *s, int kind) {
         for (const auto &idx : own_groups(gs.data(), (int32_t)gs.size(), true)) {
             TileTotals tot;
             std::vector<int32_t> rounds;
-            const gr_status ds = run_own_group(gs.data(), ss.data(), rows.data(), idx, st, &tot, &rounds);
+            const gr_status ds = run_own_group(gs.data(), ss.data(), rows.data(), idx, st, false, &tot, &rounds);
             const int64_t t_done = now_ns();
             lk.lock();
             for (size_t j = 0; j < idx.size(); ++j) {

@@ -79,7 +79,7 @@ constexpr int kTileFlagStride = 16;
 constexpr int kTileMaxJobs = 64;
 constexpr int kTileMaxTiles = 1 << 24;  // a queue entry packs (query, tile) in 30 bits
 // Statistics words the kernel writes to stat (pinned host memory): status (1
-// done, 3 a wait timed out), arcs relaxed, vertex expansions.
+// done, 3 a wait timed out), arcs relaxed (with count), vertex expansions.
 constexpr int kTileStatWords = 3;
 
 // Workspace bytes of a launch over these queries' layouts, and the launch:
@@ -87,6 +87,6 @@ constexpr int kTileStatWords = 3;
 // wt: 0 uint32, 1 binary32, 2 unit steps; all layouts have `slots` slots.
 size_t tile_ws_bytes(const TileSet *const *sets, int32_t k);
 hipError_t launch_tiles(const TileSet *const *sets, const int32_t *srcs, uint32_t *const *dist, int32_t k, int wt,
-                        void *ws, int num_cu, uint64_t spin_ticks, unsigned long long *stat, hipStream_t st);
+                        void *ws, int num_cu, uint64_t spin_ticks, bool count, unsigned long long *stat, hipStream_t st);
 
 }  // namespace gr

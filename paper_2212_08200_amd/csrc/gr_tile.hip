@@ -45,11 +45,10 @@
 //              one of its own tokens on, and returns what it holds when it
 //              has nothing to do, after its writes were performed.  active =
 //              0 thus means that no offer is left anywhere: the query ends.
-//   status     bits 0 / 1: the query ended / a wait did not.  A workgroup may
-//              wait for as long as others run tiles (on a path all but one or
-//              two do), so what a wait is held against is their progress: the
-//              rest of the word counts it, every few hundred microseconds
-//              while any tile runs.
+//   beat       progress, counted every few hundred microseconds while any tile
+//              runs.  A workgroup may wait for as long as others do (on a path
+//              all but one or two wait), so a wait has outlasted its bound only
+//              if this did not change meanwhile.
 // Any single resident workgroup makes progress alone, so the launch needs no
 // co-residency.  dist is both the output and what survives of a tile between
 // runs: the holder writes the words it lowered before it lets the tile go.
@@ -65,7 +64,7 @@ namespace {
 
 // Sweeps of a wave between two looks at the tile's state.
 constexpr int kTileSweeps = 4;
-constexpr int kTileNap = 1;  // s_sleep (64 cycles) of a wave whose block of sweeps found nothing
+constexpr int kTileNap = 8;  // s_sleep (64 cycles) of a wave whose block of sweeps found nothing (1: meshes 1% longer)
 constexpr int kRegs = 5;  // arcs out, and mail words, that the two courier waves keep in registers, per lane
 // Tokens a workgroup takes at once; it does so below what one pass over the arcs
 // out can pass on.
@@ -78,14 +77,14 @@ constexpr uint32_t kTileIdleTicks = 100;  // wall clock ticks (10 ns) a workgrou
 
 // Control words (8 bytes each, hot ones on 256-byte lines of their own).
 constexpr int kTcStatus = 0;
-constexpr uint32_t kTcDone = 1, kTcLate = 2, kTcBeat = 4;
 constexpr int kTcHead = 32;
 constexpr int kTcTail = 64;
 constexpr int kTcActive = 96;
 constexpr int kTcArcs = 128;
 constexpr int kTcItems = 129;
 constexpr int kTcExits = 130;
-constexpr int kTcWords = 160;
+constexpr int kTcBeat = 160;
+constexpr int kTcWords = 192;
 
 template <typename T>
 using gptr = T __attribute__((address_space(1))) *;
@@ -151,10 +150,6 @@ __device__ __forceinline__ uint32_t tile_plus(uint32_t d, uint32_t w) {
     else return __builtin_elementwise_add_sat(d, WT == 2 ? 1u : w);
 }
 
-__device__ __forceinline__ uint32_t tile_status(gptr<unsigned long long> ctl) {
-    return ld_dev(reinterpret_cast<gptr<uint32_t>>(ctl + kTcStatus));
-}
-
 // A lane raises flag[q] and queues q if no workgroup holds it.  True when it
 // passed a token on.
 __device__ __forceinline__ bool tile_wake(const TileArgs &a, gptr<uint32_t> flags, uint32_t job, uint32_t q) {
@@ -165,7 +160,7 @@ __device__ __forceinline__ bool tile_wake(const TileArgs &a, gptr<uint32_t> flag
         const unsigned long long p =
             __hip_atomic_fetch_add(ctl + kTcTail, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         gptr<uint32_t> slot = to_global(a.ring) + ((uint32_t)p & a.mask);
-        while (ld_dev(slot) != 0u && (tile_status(ctl) & (kTcDone | kTcLate)) == 0u) __builtin_amdgcn_s_sleep(1);
+        while (ld_dev(slot) != 0u && ld_dev(ctl + kTcStatus) == 0ull) __builtin_amdgcn_s_sleep(1);
         __hip_atomic_store(slot, (job << 24 | q) + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     return !(old & 1u);
@@ -205,11 +200,12 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t x) {
 // Everything this wave sent to memory has been performed.
 __device__ __forceinline__ void wait_mem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// WT: 0 uint32, 1 binary32, 2 unit steps; D: arc slots per vertex.  One workgroup
+// WT: 0 uint32, 1 binary32, 2 unit steps; D: arc slots per vertex; COUNT:
+// whether arcs are counted for the statistics (1% of the time of a mesh).  One workgroup
 // fills a compute unit; with four slots its registers leave room for a wave
 // per SIMD of other launches (a server's sessions: 48 mixed queries 5.6 ms
 // against 6.3).
-template <int WT, int D>
+template <int WT, int D, bool COUNT>
 __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D == 4 ? 5 : 4))) void k_tile(
     TileArgs a) {
     __shared__ __attribute__((aligned(16))) uint32_t sD[kTileVerts];
@@ -244,21 +240,18 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
         sTok = 0;
         const unsigned long long old =
             __hip_atomic_fetch_add(ctl + kTcActive, 0ull - x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (old == x) (void)__hip_atomic_fetch_or(ctl + kTcStatus, (unsigned long long)kTcDone, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
+        if (old == x) __hip_atomic_store(ctl + kTcStatus, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     uint32_t looks = 0;  // the receiving wave's passes
-    // one lane, waiting since t0; seen: the status word that t0 belongs to
-    const auto waiting = [&](uint32_t &t0, uint32_t s, uint32_t &seen) {
+    // one lane, waiting since t0; seen: beat when t0 was last set
+    const auto waiting = [&](uint32_t &t0, uint32_t &seen) {
         const uint32_t now = (uint32_t)wall_clock64();
-        if (s != seen) {
-            seen = s;
-            t0 = now;
-        }
         if (now - t0 > kTileIdleTicks) give_tokens();
-        if (now - t0 > a.spin)
-            (void)__hip_atomic_fetch_or(ctl + kTcStatus, (unsigned long long)kTcLate, __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT);
+        if (now - t0 <= a.spin) return;
+        const uint32_t b = (uint32_t)ld_dev(ctl + kTcBeat);
+        if (b == seen) __hip_atomic_store(ctl + kTcStatus, 3ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        seen = b;
+        t0 = now;
     };
     for (;;) {
         // 1. the next tile
@@ -268,17 +261,17 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
                 const unsigned long long p =
                     __hip_atomic_fetch_add(ctl + kTcHead, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 gptr<uint32_t> slot = ring + ((uint32_t)p & a.mask);
-                uint32_t since = (uint32_t)wall_clock64(), seen = 0u;
+                uint32_t since = (uint32_t)wall_clock64(), seen = ~0u;
                 for (;;) {
                     const uint32_t x = ld_dev(slot);
-                    const uint32_t s = tile_status(ctl);
+                    const unsigned long long s = ld_dev(ctl + kTcStatus);
                     if (x != 0u) {
                         __hip_atomic_store(slot, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         cmd = (int)(x - 1u);
                         break;
                     }
-                    if ((s & (kTcDone | kTcLate)) != 0u) break;
-                    waiting(since, s, seen);
+                    if (s != 0ull) break;
+                    waiting(since, seen);
                     __builtin_amdgcn_s_sleep(2);
                 }
                 sCmd = cmd;
@@ -306,7 +299,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
         gptr<const int32_t> vid = to_global(J.vid) + base;
         gptr<uint32_t> dist = to_global(J.dist);
         uint32_t last[kTileVpt], w[kTileVpt][D], hd[kTileVpt][D / 2];
-        uint32_t dirty = 0;
+        uint32_t dirty = 0, deg = 0;  // deg: arcs in the columns (empty slots lead back), a byte per vertex
         {
             const u32x4 v = reinterpret_cast<gptr<const u32x4>>(vid)[t];
             gptr<const u32x4> pw = reinterpret_cast<gptr<const u32x4>>(to_global(J.w) + base * D) + t;
@@ -321,7 +314,12 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
             for (int s = 0; s < D / 2; ++s) {
                 const u32x4 x = ph[s * kTileThreads];
 #pragma unroll
-                for (int i = 0; i < kTileVpt; ++i) hd[i][s] = x[i];
+                for (int i = 0; i < kTileVpt; ++i) {
+                    const uint32_t own = 4u * (uint32_t)tile_place(t, i);
+                    hd[i][s] = x[i];
+                    deg += ((x[i] & 0xFFFFu) != own ? 1u : 0u) << (8 * i);
+                    deg += (x[i] >> 16 != own ? 1u : 0u) << (8 * i);
+                }
             }
             // (places past the end read vertex 0)
 #pragma unroll
@@ -375,6 +373,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
                             if (cur[i] < last[i]) {
                                 last[i] = cur[i];
                                 dirty |= 1u << i;
+                                if constexpr (COUNT) arcs = __builtin_amdgcn_udot4(deg, 1u << (8 * i), arcs, false);
 #pragma unroll
                                 for (int s = 0; s < D; ++s) {
                                     uint32_t h2 = hd[i][s / 2];
@@ -441,7 +440,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
                         moved = true;
                         uint32_t q = kTileInner;
                         if (fell) {
-                            ++arcs;
+                            if constexpr (COUNT) ++arcs;
                             const uint32_t nd = tile_plus<WT>(du, sExtW[j]);
                             q = sExtQ[j];
                             if (q & kTileInner) min_lds(&sD[q & 0xFFFFu], nd);
@@ -549,8 +548,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
                     snap = (uint32_t)ran();
                     moved = false;
                     if ((++looks % kTileLooks) == 0u && lane == 0)
-                        (void)__hip_atomic_fetch_add(ctl + kTcStatus, (unsigned long long)kTcBeat, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT);
+                        (void)__hip_atomic_fetch_add(ctl + kTcBeat, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     continue;
                 }
                 // its distances go to memory; it waits for mail, or is let go
@@ -558,7 +556,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
                 __syncthreads();
                 int next = 0;  // 0: let go, 1: again
                 if (lane == 0) {
-                    uint32_t since = (uint32_t)wall_clock64(), seen = 0u;
+                    uint32_t since = (uint32_t)wall_clock64(), seen = ~0u;
                     for (;;) {
                         if (ld_dev(flag) & 1u) {
                             (void)__hip_atomic_exchange(flag, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -567,8 +565,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
                             next = 1;
                             break;
                         }
-                        const uint32_t s = tile_status(ctl);
-                        const bool over = (s & (kTcDone | kTcLate)) != 0u;
+                        const bool over = ld_dev(ctl + kTcStatus) != 0ull;
                         if (over || ld_dev(ctl + kTcTail) > ld_dev(ctl + kTcHead)) {
                             uint32_t held = 2u;
                             if (__hip_atomic_compare_exchange_strong(flag, &held, 0u, __ATOMIC_RELAXED,
@@ -577,7 +574,7 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
                                 break;
                             continue;
                         }
-                        waiting(since, s, seen);
+                        waiting(since, seen);
                         __builtin_amdgcn_s_sleep(1);
                     }
                     sCmd = next;
@@ -593,20 +590,20 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(D 
     }
     // (items is the wave's, arcs the lane's)
     if (lane == 0) atomicAdd(&sItems, (unsigned long long)items);
-    atomicAdd(&sArcs, (unsigned long long)arcs + (lane == 0 ? (unsigned long long)items * D : 0ull));
+    if constexpr (COUNT) atomicAdd(&sArcs, (unsigned long long)arcs);
     __syncthreads();
     if (t == 0) {
         (void)__hip_atomic_fetch_add(ctl + kTcItems, sItems, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        (void)__hip_atomic_fetch_add(ctl + kTcArcs, sArcs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if constexpr (COUNT) {
+            (void)__hip_atomic_fetch_add(ctl + kTcArcs, sArcs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         wait_mem();
         const unsigned long long x =
             __hip_atomic_fetch_add(ctl + kTcExits, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (x + 1ull == gridDim.x) {  // the last one: statistics to the host
             __hip_atomic_store(a.stat + 1, ld_dev(ctl + kTcArcs), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             __hip_atomic_store(a.stat + 2, ld_dev(ctl + kTcItems), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            const uint32_t w = tile_status(ctl);
-            __hip_atomic_store(a.stat + 0, w & kTcDone ? 1ull : w & kTcLate ? 3ull : 0ull, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(a.stat + 0, ld_dev(ctl + kTcStatus), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
 }
@@ -632,7 +629,7 @@ size_t tile_ws_bytes(const TileSet *const *sets, int32_t k) {
 }
 
 hipError_t launch_tiles(const TileSet *const *sets, const int32_t *srcs, uint32_t *const *dist, int32_t k, int wt,
-                        void *ws, int num_cu, uint64_t spin_ticks, unsigned long long *stat, hipStream_t st) {
+                        void *ws, int num_cu, uint64_t spin_ticks, bool count, unsigned long long *stat, hipStream_t st) {
     if (k < 1 || k > kTileMaxJobs || wt < 0 || wt > 2 || !ws || !stat) return hipErrorInvalidValue;
     int64_t tiles = 0;
     for (int32_t i = 0; i < k; ++i) {
@@ -698,7 +695,11 @@ hipError_t launch_tiles(const TileSet *const *sets, const int32_t *srcs, uint32_
     const int64_t room = (int64_t)num_cu;
     const unsigned grid = (unsigned)(tiles < room ? tiles : room);
     const dim3 g(grid), blk(kTileThreads);
-#define TILE_LAUNCH(WT, D) hipLaunchKernelGGL((k_tile<WT, D>), g, blk, 0, st, a)
+#define TILE_LAUNCH(WT, D)                                                            \
+    do {                                                                              \
+        if (count) hipLaunchKernelGGL((k_tile<WT, D, true>), g, blk, 0, st, a);       \
+        else hipLaunchKernelGGL((k_tile<WT, D, false>), g, blk, 0, st, a);            \
+    } while (0)
     if (sets[0]->slots == 4) {
         if (wt == 0) TILE_LAUNCH(0, 4);
         else if (wt == 1) TILE_LAUNCH(1, 4);

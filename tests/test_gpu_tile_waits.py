@@ -32,3 +32,20 @@ def test_a_path_longer_than_the_bound(wtype):
             torch.cuda.synchronize()
             np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), want)
             assert st["loop"] == gr.GR_LOOP_ASYNC and st["launches"] == 2 and st["push_us"] > 2 * us
+
+
+@pytest.mark.parametrize("back", [0, 1])
+def test_arcs_and_expansions_of_a_path(back):
+    # every vertex is improved once, so it is expanded once, over its own arcs
+    # alone: the next one's, and with back the one it came from
+    n = 9001
+    i = np.arange(n - 1)
+    g = gg.from_arcs(n, sorted([(int(a), int(a) + 1, 1.5) for a in i] + [(int(a) + 1, int(a), 2.5) for a in i] * back),
+                     wtype=gg.W_F32)
+    with gr.Graph.from_csr(g) as G:
+        d = torch.full((n,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+        st = gr.gr_sssp_ex(G.handle, 0, d)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), oracle.dijkstra(g, 0))
+        assert st["loop"] == gr.GR_LOOP_ASYNC and st["launches"] == 2
+        assert st["frontier_sum"] == n and st["edges_pushed"] == g.m
