@@ -196,9 +196,10 @@ typedef enum {
                                environment variable GR_ASYNC_LIST_CAP (entries, >= 1)
                                lowers the list capacity, to test the overflow path.
                                Over tiles (only AUTO picks it; stats report this mode):
-                               graphs of maximum out-degree <= 64 whose vertices cut into
-                               tiles of up to 3,584 with most arcs inside (meshes, road
-                               networks, whatever their vertex order) hold a second copy
+                               graphs whose vertices cut into tiles of up to 3,584 with
+                               most arcs inside (meshes, road networks, whatever their
+                               vertex order; at most 3,072 arcs per vertex, and few of
+                               more than eight) hold a second copy
                                of their arcs by tile; one persistent kernel runs a tile
                                per workgroup in LDS, improvements cross tiles through
                                one word per arc.  Extra workspace: about 64 bytes per

@@ -32,6 +32,7 @@ constexpr int kSweepBatch = 8;
 constexpr int kMaxSweeps = 96;
 constexpr int32_t kMaxPairs = 1 << 20;
 
+// (the finalizer "lowbias32" of C. Wellons' hash-prospector)
 __device__ __forceinline__ uint32_t hash32(uint32_t x) {
     x ^= x >> 16;
     x *= 0x7FEB352Du;
@@ -40,12 +41,19 @@ __device__ __forceinline__ uint32_t hash32(uint32_t x) {
     return x ^ (x >> 16);
 }
 
-__global__ __launch_bounds__(256) void k_cell_seed(int32_t n, int32_t s, int32_t *label) {
+// A label: of a cell, -1 for none yet, and -2 - cell for a vertex of more than
+// kCellHub arcs, which is in the cell but hands it on to nobody: its arcs lead
+// anywhere, and a cell that grows from all of their ends fits no tile.
+constexpr int32_t kCellHub = 16;
+__device__ __forceinline__ int32_t hub_label(int32_t l, int32_t deg) { return l >= 0 && deg > kCellHub ? -2 - l : l; }
+
+__global__ __launch_bounds__(256) void k_cell_seed(int32_t n, int32_t s, const int32_t *ro, int32_t *label) {
     const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (v >= n) return;
     const int32_t b = (int32_t)(v / s), off = (int32_t)(v - (int64_t)b * s);
     const int32_t len = (int32_t)min((int64_t)s, n - (int64_t)b * s);
-    label[v] = off == (int32_t)(hash32((uint32_t)b) % (uint32_t)len) ? b : -1;
+    const bool seed = off == (int32_t)(hash32((uint32_t)b) % (uint32_t)len);
+    label[v] = seed ? hub_label(b, ro[v + 1] - ro[v]) : -1;
 }
 
 // One level: an unlabelled vertex takes a neighbour's label of the level before.
@@ -57,18 +65,19 @@ __global__ __launch_bounds__(256) void k_cell_sweep(int32_t n, const int32_t *ro
     int32_t l = 0;
     if (v < n) {
         l = was[v];
-        if (l < 0) {
+        if (l == -1) {
             const int32_t e0 = ro[v], d = ro[v + 1] - e0;
             int32_t at = d > 0 ? (int32_t)(hash32((uint32_t)v ^ salt) % (uint32_t)d) : 0;
             for (int32_t k = 0; k < d && l < 0; ++k) {
                 l = was[adj[e0 + at].x];
                 if (++at == d) at = 0;
             }
+            l = l < 0 ? -1 : hub_label(l, d);
         }
         now[v] = l;
     }
     if (left) {
-        const unsigned long long m = __ballot(v < n && l < 0);
+        const unsigned long long m = __ballot(v < n && l == -1);
         if ((threadIdx.x & 63) == 0 && m) atomicAdd(left, (unsigned int)__popcll(m));
     }
 }
@@ -79,7 +88,7 @@ __global__ __launch_bounds__(256) void k_cell_size(int32_t n, int32_t s, int32_t
     const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (v >= n) return;
     int32_t l = label[v];
-    if (l < 0) label[v] = l = cells + (int32_t)(v / s);
+    if (l < 0) label[v] = l = l == -1 ? cells + (int32_t)(v / s) : -2 - l;
     atomicAdd(size + l, 1u);
 }
 
@@ -429,7 +438,7 @@ hipError_t tile_build(TileSet *out, int32_t n, int32_t m, const int32_t *ro, con
         hsize[0] = (unsigned)n;
     } else {
         TRY(tmp.get(&pairs, kMaxPairs));
-        hipLaunchKernelGGL(k_cell_seed, grid, blk, 0, st, n, s, la);
+        hipLaunchKernelGGL(k_cell_seed, grid, blk, 0, st, n, s, ro, la);
         unsigned int left = (unsigned)n, before = 0;
         for (int k = 0; k < kMaxSweeps && left > 0 && left != before; k += kSweepBatch) {
             before = left;
