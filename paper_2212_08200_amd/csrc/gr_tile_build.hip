@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kTileThreads) void k_tile_in_sort(const int32_t *in
 // Joins the cells into tiles of at most kTileFill vertices: a tile grows by
 // the neighbouring cell it shares most sampled border arcs with, among those
 // that fit; the next tile starts beside the tiles made so far.  Returns the
-// number of tiles, or -1 when a cell is too large.
+// number of tiles, or -1 when a cell is too large or the graph has no locality.
 int32_t merge_cells(const std::vector<unsigned int> &size, const std::vector<uint2> &pairs,
                     std::vector<int32_t> *tile_of) {
     const int32_t c = (int32_t)size.size();
@@ -296,6 +296,23 @@ int32_t merge_cells(const std::vector<unsigned int> &size, const std::vector<uin
             nb[at[p.x]++] = (int32_t)p.y;
             nb[at[p.y]++] = (int32_t)p.x;
         }
+    }
+    // Cells of a mesh meet a few others along many arcs (6 to 20 along 64 and
+    // more, each counted four times here), those of a random graph another one
+    // with nearly every arc: where the sample has enough arcs per cell to tell,
+    // the latter end here (uniform of 500,000 vertices and degree 3, whose cells
+    // are trees with a third of their arcs on the border: created in 11.9 ms,
+    // 8.2 so, 3.1 without trying).
+    if ((int64_t)nb.size() >= 64 * (int64_t)c) {
+        std::vector<int32_t> seen((size_t)c, -1);
+        int64_t distinct = 0;
+        for (int32_t i = 0; i < c; ++i)
+            for (int32_t k = off[i]; k < off[i + 1]; ++k)
+                if (seen[nb[k]] != i) {
+                    seen[nb[k]] = i;
+                    ++distinct;
+                }
+        if (5 * distinct > (int64_t)nb.size()) return -1;
     }
     tile_of->assign((size_t)c, -1);
     std::vector<int32_t> gain((size_t)c, 0), front, todo;

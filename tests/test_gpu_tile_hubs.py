@@ -74,3 +74,30 @@ def test_meshes_with_hubs(name):
         torch.cuda.synchronize()
         for s, row in zip(srcs * 3, rows.cpu().numpy().view(np.uint32)):
             np.testing.assert_array_equal(row, oracle.dijkstra(g, s))
+
+
+@pytest.mark.parametrize("n,deg", [(20000, 3), (60001, 3), (150000, 2), (300000, 4)])
+def test_random_graphs_of_low_degree_have_no_tiles(n, deg, monkeypatch):
+    # their cells are trees, with few arcs on the borders; only the worklist of
+    # the asynchronous loop without tiles has a capacity to overflow
+    monkeypatch.setenv("GR_ASYNC_LIST_CAP", "64")
+    g = gg.uniform(n, n * deg // 2, 3, 4, symmetric=True)
+    s = int(gg.pick_sources(g, 3, 1)[0])
+    with gr.Graph.from_csr(g) as G:
+        d = torch.full((g.n,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+        st = gr.gr_sssp_ex(G.handle, s, d)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), oracle.dijkstra(g, s))
+        assert st["loop"] == gr.GR_LOOP_QUEUED if n > 65536 else st["iterations"] > 1
+
+
+@pytest.mark.parametrize("side", [150, 700])
+def test_meshes_have_tiles(side, monkeypatch):
+    monkeypatch.setenv("GR_ASYNC_LIST_CAP", "64")
+    g = gg.grid(side, wseed=4)
+    with gr.Graph.from_csr(g) as G:
+        d = torch.full((g.n,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+        st = gr.gr_sssp_ex(G.handle, 9, d)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), oracle.dijkstra(g, 9))
+        assert st["loop"] == gr.GR_LOOP_ASYNC and st["iterations"] == 1
