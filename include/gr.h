@@ -482,11 +482,12 @@ typedef struct {
  * runs them as one launch, one workgroup per query, on a stream of its own;
  * batch_size is then that launch's query count.  Queries on graphs whose AUTO
  * runs over tiles or weight-ordered arcs take no slot either: a thread of the
- * server runs all that wait (up to 64) together, beside the executors; their
- * workspace is outside the budget (over tiles about 64 bytes per tile and 4
- * per arc between tiles, over weight-ordered arcs about 5 per vertex; the
- * budget counts 28 bytes per vertex for a query).  cfg may be
- * NULL. */
+ * server for each of the two runs those that wait (up to 64) and fit the budget
+ * together, beside the executors.  Their footprint is their workspace (over
+ * tiles 80 bytes per tile, 4 per arc between tiles and 20 KB; over
+ * weight-ordered arcs about 5 per vertex and 300 KB); where that alone exceeds
+ * the budget they join an executor.  A query that waits for memory is let in
+ * before any that arrived later.  cfg may be NULL. */
 gr_status gr_server_create(gr_server **out, size_t hbm_budget_bytes, const gr_server_config *cfg);
 /* Registers a graph (not copied; it must outlive the server). */
 gr_status gr_server_add_graph(gr_server *s, const gr_graph *g, int32_t *graph_id);

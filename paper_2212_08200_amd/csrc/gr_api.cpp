@@ -2457,13 +2457,29 @@ struct gr_server {
     size_t in_flight = 0;
     bool stopping = false;
     std::vector<std::thread> workers;
-    std::deque<SchedQuery> own[2];  // queries on graphs that run over tiles (0) or weight-ordered arcs (1)
+    std::unique_ptr<LaunchQueue> own[2];  // queries on graphs that run over tiles (0) or weight-ordered arcs (1)
     std::vector<std::thread> own_workers;
+
+    // The heads of the queues other than `self` (an own queue, or -1: the
+    // executors' FIFO), and whether any has one.
+    OlderHeads heads(int self) const {
+        OlderHeads h;
+        if (self != -1) policy->head_into(&h);
+        for (int i = 0; i < 2; ++i)
+            if (i != self) own[i]->head_into(&h);
+        return h;
+    }
 };
 
 static QuerySize query_size(const gr_graph *g) {
     // its marks and dirty bytes, and its share of the session's two queues
     return QuerySize{mq_slot_bytes(g->plain.n) + (size_t)g->plain.n * 26, g->plain.n, g->plain.m};
+}
+
+// Workspace of a query in a launch of its own (a launch's is at most the sum).
+static size_t own_bytes(const gr_graph *g) {
+    if (g->tiles.ntiles > 0) return tile_query_bytes(g->tiles);
+    return g->order.base ? al256(sizeof(OrderJob) * kOrderMaxJobs) + order_ws_bytes(g->plain.n) : 0;
 }
 
 // One executor: a session of up to max_batch slots on its own stream.  Each
@@ -2583,7 +2599,8 @@ static void server_worker(gr_server *s, int exec_id) {
             }
             if (have_ses)
                 adm = s->policy->admit(SessionRoom{nslots - nused, qcap - used_n, (int64_t)INT32_MAX - used_m},
-                                       &s->in_flight);
+                                       &s->in_flight, s->heads(-1));
+            if (!adm.empty() && s->heads(-1).n > 0) s->cv.notify_all();  // (less is kept for this queue's head)
         }
         if (broken != GR_OK) {
             // fail everything this executor holds and every query still queued
@@ -2722,30 +2739,29 @@ static void server_worker(gr_server *s, int exec_id) {
 }
 
 // Queries on graphs that run over tiles or weight-ordered arcs: one thread takes
-// all that wait (up to kTileMaxJobs) and runs them together, while the
-// executors' sessions go on.  Those that arrive meanwhile are the next ones.
+// those that wait (up to kTileMaxJobs) and fit the budget and runs them together,
+// while the executors' sessions go on.  Those that arrive meanwhile are the next
+// ones.
 static void server_own_worker(gr_server *s, int kind) {
-    std::deque<SchedQuery> &own = s->own[kind];
+    LaunchQueue &own = *s->own[kind];
     (void)hipSetDevice(s->device);
     hipStream_t st = nullptr;  // created with the first query
     std::unique_lock<std::mutex> lk(s->mu);
     for (;;) {
-        s->cv.wait(lk, [&] { return s->stopping || !own.empty(); });
-        if (own.empty()) break;
-        if (!st) {  // (without a stream of their own the queries run on the null stream)
-            lk.unlock();
-            if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) st = nullptr;
-            lk.lock();
+        const size_t before = s->in_flight;
+        const std::vector<SchedQuery> qs = own.take(kTileMaxJobs, &s->in_flight, s->heads(kind));
+        const size_t bytes = s->in_flight - before;
+        if (qs.empty()) {
+            if (s->stopping && own.pending() == 0) break;
+            s->cv.wait(lk);  // (for a query, or for memory)
+            continue;
         }
-        std::vector<SchedQuery> qs;
+        if (s->heads(kind).n > 0) s->cv.notify_all();  // (less is kept for this queue's head)
         std::vector<const gr_graph *> gs;
         std::vector<int32_t> ss;
         std::vector<uint32_t *> rows;
         const int64_t t_start = now_ns();
-        while (!own.empty() && (int)qs.size() < kTileMaxJobs) {
-            const SchedQuery q = own.front();
-            own.pop_front();
-            qs.push_back(q);
+        for (const SchedQuery &q : qs) {
             gs.push_back(s->graphs[q.graph]);
             ss.push_back(q.src);
             rows.push_back(static_cast<uint32_t *>(q.dst));
@@ -2754,6 +2770,8 @@ static void server_own_worker(gr_server *s, int kind) {
             t.res.t_start_ns = t_start;
         }
         lk.unlock();
+        // (without a stream of their own the queries run on the null stream)
+        if (!st && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) st = nullptr;
         for (const auto &idx : own_groups(gs.data(), (int32_t)gs.size(), true)) {
             TileTotals tot;
             std::vector<int32_t> rounds;
@@ -2771,6 +2789,7 @@ static void server_own_worker(gr_server *s, int kind) {
             lk.unlock();
         }
         lk.lock();
+        s->in_flight -= bytes;
         s->cv.notify_all();
     }
     lk.unlock();
@@ -2803,6 +2822,8 @@ extern "C" gr_status gr_server_create(gr_server **out, size_t hbm_budget_bytes, 
     s->cfg = c;
     gr_server *raw = s.get();
     s->policy.reset(new SlotPolicy(hbm_budget_bytes, [raw](int32_t gid) { return query_size(raw->graphs[gid]); }));
+    for (auto &q : s->own)
+        q.reset(new LaunchQueue(hbm_budget_bytes, [raw](int32_t gid) { return own_bytes(raw->graphs[gid]); }));
     for (int i = 0; i < c.num_streams; ++i) s->workers.emplace_back(server_worker, raw, i);
     // a thread for each kind (serving 48 queries of twelve graphs: 4.05 ms with
     // one for both, 3.42 so, 3.34 with two for the tiles)
@@ -2844,9 +2865,10 @@ extern "C" gr_status gr_serve_submit(gr_server *s, int32_t graph_id, int32_t src
     // run outside the executors' sessions
     // (those whose graph fits the row-offset layout, which any mix of them shares);
     // those on graphs that run over tiles or weight-ordered arcs have queues
-    // and threads of their own
+    // and threads of their own (unless the budget holds only the session's
+    // workspace, which is less on the smallest graphs)
     const SchedQuery q{id, graph_id, src, dist_out, t, g->auto_loop == GR_LOOP_LDS && g->lds_fit};
-    if (g->auto_tiled || g->auto_order) s->own[g->auto_tiled ? 0 : 1].push_back(q);
+    if ((g->auto_tiled || g->auto_order) && own_bytes(g) <= s->budget) s->own[g->auto_tiled ? 0 : 1]->push(q);
     else s->policy->push(q);
     s->cv.notify_all();
     *ticket = id;

@@ -88,6 +88,8 @@ constexpr int kTileStatWords = 3;
 // every dist row, in at most `groups` co-resident workgroups per compute unit.
 // wt: 0 uint32, 1 binary32, 2 unit steps; all layouts have `slots` slots.
 size_t tile_ws_bytes(const TileSet *const *sets, int32_t k);
+// A query's share: the sum over a launch's is at least its tile_ws_bytes.
+size_t tile_query_bytes(const TileSet &set);
 hipError_t launch_tiles(const TileSet *const *sets, const int32_t *srcs, uint32_t *const *dist, int32_t k, int wt,
                         void *ws, int num_cu, uint64_t spin_ticks, bool count, unsigned long long *stat, hipStream_t st);
 

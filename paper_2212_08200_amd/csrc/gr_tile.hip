@@ -628,6 +628,13 @@ size_t tile_ws_bytes(const TileSet *const *sets, int32_t k) {
     return b + al256((size_t)ring_entries(tiles) * 4);
 }
 
+size_t tile_query_bytes(const TileSet &set) {
+    // its flags and mail, its entry in the table, and its share of the queue:
+    // ring_entries(t1 + t2 + ...) < 4 (t1 + t2 + ...) + 4096
+    return al256((size_t)set.ntiles * kTileFlagStride * 4) + al256((size_t)set.mail * 4) +
+           4 * (4 * (size_t)set.ntiles + 4096) + al256(kTcWords * 8) + al256(sizeof(TileJob)) + 256;
+}
+
 hipError_t launch_tiles(const TileSet *const *sets, const int32_t *srcs, uint32_t *const *dist, int32_t k, int wt,
                         void *ws, int num_cu, uint64_t spin_ticks, bool count, unsigned long long *stat, hipStream_t st) {
     if (k < 1 || k > kTileMaxJobs || wt < 0 || wt > 2 || !ws || !stat) return hipErrorInvalidValue;
