@@ -368,10 +368,9 @@ gr_status gr_bfs_ex(const gr_graph *g, int32_t src, void *depth_out, void *strea
 /* Statistics of gr_sssp_batch_ex and gr_sssp_multi. */
 typedef struct {
     int32_t rounds;             /* rounds in which some query's frontier was not empty */
-    int32_t replays;            /* replays of the captured chunk of rounds (one host wait each); 0 when
-                                   none runs (k = 1, or the single-workgroup loop); the weight-ordered
-                                   loop and calls whose queries take several loops count chunks of 8
-                                   rounds */
+    int32_t replays;            /* replays of the captured chunk of rounds (one host wait each), and the
+                                   weight-ordered loop's launches in chunks of 8; 0 when neither runs
+                                   (k = 1, the single-workgroup loop, tiles) */
     int64_t edges_pushed;       /* arcs expanded (a batched arc serves every source active at its tail) */
     int64_t frontier_sum;       /* frontier entries expanded */
     int64_t source_relaxations; /* (arc, query) relaxations: for gr_sssp_batch_ex the (arc, active source)
@@ -437,7 +436,8 @@ gr_status gr_sssp_batch_ex(const gr_graph *g, const int32_t *srcs, int32_t k, vo
  * query runs that loop in a workgroup of its own, all in one launch, with no
  * workspace (stats->replays = 0).  Queries on graphs whose AUTO runs over tiles
  * (rounds 1, or 0 for a source without arcs) or weight-ordered arcs run in
- * launches of their own, each kind together, before the others.
+ * launches of their own, each kind together, and the others as above: in
+ * rounds together, also those whose AUTO loop is the single-workgroup loop.
  */
 gr_status gr_sssp_multi(const gr_graph *const *graphs, const int32_t *srcs, int32_t k, void *const *dist_out,
                         void *stream, gr_multi_stats *stats, int32_t *iterations);

@@ -2056,12 +2056,85 @@ static gr_status check_same_device(const gr_graph *g) {
 
 static constexpr int kMqRoundsPerReplay = 8;
 
+// k queries on several graphs through a session of their own.
+static gr_status multi_session(const gr_graph *const *graphs, const int32_t *srcs, int32_t k, void *const *dist_out,
+                               hipStream_t st, gr_multi_stats *stats, int32_t *iterations) {
+    int64_t sum_n = 0;
+    for (int32_t i = 0; i < k; ++i) sum_n += graphs[i]->plain.n;
+    MqSession ses;
+    MqMode mode;
+    for (int32_t i = 0; i < k; ++i) mode.local_hops = std::max(mode.local_hops, graphs[i]->auto_local_hops);
+    gr_status gs = mq_create(&ses, sum_n, kMqRoundsPerReplay, st, mode, false);
+    if (gs != GR_OK) return gs;
+    std::vector<size_t> off((size_t)k + 1, 0);
+    for (int32_t i = 0; i < k; ++i) off[i + 1] = off[i] + mq_slot_bytes(graphs[i]->plain.n);
+    void *ws = nullptr;
+    hipError_t e = hipMallocAsync(&ws, off[k], st);
+    if (e != hipSuccess) {
+        mq_destroy(&ses);
+        return hip_fail(e, "hipMallocAsync");
+    }
+    std::vector<int> live;
+    std::vector<int32_t> ngr(kMqSlots, 0);
+    for (int32_t i = 0; i < k; ++i) {
+        live.push_back(i);
+        ngr[i] = (int32_t)groups_for(graphs[i]->plain.n);
+    }
+    for (int32_t i0 = 0; i0 < k && e == hipSuccess; i0 += 16) {
+        MqUpdate u{};
+        u.nadmit = std::min<int32_t>(16, k - i0);
+        for (int32_t j = 0; j < u.nadmit; ++j) {
+            const int32_t i = i0 + j;
+            u.admit_slot[j] = i;
+            u.admit_src[j] = srcs[i];
+            u.admit[j] = mq_slot(graphs[i], static_cast<uint32_t *>(dist_out[i]), static_cast<char *>(ws) + off[i],
+                                 graphs[i]->plain.wt);
+        }
+        if (i0 + 16 >= k) mq_live(u, live, ngr);
+        else u.nlive = -1;
+        e = mq_update(ses.b, u, st);
+    }
+    gr_status status = GR_OK;
+    MqRead rd{};
+    int64_t last_E = -1;
+    while (e == hipSuccess) {
+        e = mq_replay(&ses, 0, st, last_E);
+        if (e == hipSuccess) e = hipEventSynchronize(ses.ev[0]);
+        if (e != hipSuccess) break;
+        rd = mq_parse(ses.h);
+        last_E = rd.E;
+        if (rd.F == 0) break;
+        bool over = false;
+        for (int32_t i = 0; i < k; ++i)
+            over = over || rd.slot_rounds[i] > (unsigned long long)graphs[i]->plain.n + 1;
+        if (over) {
+            status = fail(GR_ERR_ITER_LIMIT, "a query ran past n + 1 rounds");
+            break;
+        }
+    }
+    if (e == hipSuccess) e = hipFreeAsync(ws, st);
+    else (void)hipFreeAsync(ws, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess && stats) {
+        stats->rounds = (int32_t)rd.rounds;
+        stats->replays = (int32_t)ses.replays;
+        stats->edges_pushed = (int64_t)rd.edges;
+        stats->frontier_sum = (int64_t)rd.frontier;
+        stats->source_relaxations = (int64_t)rd.edges;
+    }
+    if (e == hipSuccess && iterations)
+        for (int32_t i = 0; i < k; ++i) iterations[i] = (int32_t)rd.slot_rounds[i];
+    mq_destroy(&ses);
+    if (e != hipSuccess) return hip_fail(e, "multi-query loop");
+    return status;
+}
+
 extern "C" gr_status gr_sssp_multi(const gr_graph *const *graphs, const int32_t *srcs, int32_t k,
                                    void *const *dist_out, void *stream, gr_multi_stats *stats,
                                    int32_t *iterations) {
     if (!graphs || !srcs || !dist_out) return fail(GR_ERR_INVALID_ARG, "NULL graphs, srcs or dist_out");
     if (k < 1 || k > kMqSlots) return fail(GR_ERR_INVALID_ARG, "k = %d outside [1, %d]", k, kMqSlots);
-    int64_t sum_n = 0, sum_m = 0;
+    int64_t sum_m = 0;
     for (int32_t i = 0; i < k; ++i) {
         const gr_graph *g = graphs[i];
         if (!g) return fail(GR_ERR_INVALID_ARG, "graphs[%d] is NULL", i);
@@ -2070,7 +2143,6 @@ extern "C" gr_status gr_sssp_multi(const gr_graph *const *graphs, const int32_t 
             return fail(GR_ERR_SOURCE_RANGE, "srcs[%d] = %d outside [0, %d)", i, srcs[i], g->plain.n);
         gr_status s = check_same_device(g);
         if (s != GR_OK) return s;
-        sum_n += g->plain.n;
         sum_m += g->plain.m;
     }
     if (sum_m > INT32_MAX)
@@ -2147,7 +2219,7 @@ extern "C" gr_status gr_sssp_multi(const gr_graph *const *graphs, const int32_t 
         gr_multi_stats rest{};
         std::vector<int32_t> it(rg.size(), 0);
         if (s == GR_OK && !rg.empty())
-            s = gr_sssp_multi(rg.data(), rs.data(), (int32_t)rg.size(), rd.data(), stream, &rest, it.data());
+            s = multi_session(rg.data(), rs.data(), (int32_t)rg.size(), rd.data(), st, &rest, it.data());
         if (beside) {
             const hipError_t e = hipStreamSynchronize(side.st);
             side_release(side);
@@ -2174,78 +2246,10 @@ extern "C" gr_status gr_sssp_multi(const gr_graph *const *graphs, const int32_t 
                 for (size_t j = 0; j < at.size(); ++j)  // (a source without arcs has no frontier in any loop)
                     iterations[at[j]] = source_rounds(rg[j], rs[j]) ? it[j] : 0;
         }
-        // several loops in one call: as many chunks of rounds as the longest ran
-        if (groups.size() + (rg.empty() ? 0 : 1) > 1)
-            sum.replays = std::max(sum.replays, (sum.rounds + kMqRoundsPerReplay - 1) / kMqRoundsPerReplay);
         if (stats) *stats = sum;
         return GR_OK;
     }
-    MqSession ses;
-    MqMode mode;
-    for (int32_t i = 0; i < k; ++i) mode.local_hops = std::max(mode.local_hops, graphs[i]->auto_local_hops);
-    gr_status gs = mq_create(&ses, sum_n, kMqRoundsPerReplay, st, mode, false);
-    if (gs != GR_OK) return gs;
-    std::vector<size_t> off((size_t)k + 1, 0);
-    for (int32_t i = 0; i < k; ++i) off[i + 1] = off[i] + mq_slot_bytes(graphs[i]->plain.n);
-    void *ws = nullptr;
-    hipError_t e = hipMallocAsync(&ws, off[k], st);
-    if (e != hipSuccess) {
-        mq_destroy(&ses);
-        return hip_fail(e, "hipMallocAsync");
-    }
-    std::vector<int> live;
-    std::vector<int32_t> ngr(kMqSlots, 0);
-    for (int32_t i = 0; i < k; ++i) {
-        live.push_back(i);
-        ngr[i] = (int32_t)groups_for(graphs[i]->plain.n);
-    }
-    for (int32_t i0 = 0; i0 < k && e == hipSuccess; i0 += 16) {
-        MqUpdate u{};
-        u.nadmit = std::min<int32_t>(16, k - i0);
-        for (int32_t j = 0; j < u.nadmit; ++j) {
-            const int32_t i = i0 + j;
-            u.admit_slot[j] = i;
-            u.admit_src[j] = srcs[i];
-            u.admit[j] = mq_slot(graphs[i], static_cast<uint32_t *>(dist_out[i]), static_cast<char *>(ws) + off[i],
-                                 graphs[i]->plain.wt);
-        }
-        if (i0 + 16 >= k) mq_live(u, live, ngr);
-        else u.nlive = -1;
-        e = mq_update(ses.b, u, st);
-    }
-    gr_status status = GR_OK;
-    MqRead rd{};
-    int64_t last_E = -1;
-    while (e == hipSuccess) {
-        e = mq_replay(&ses, 0, st, last_E);
-        if (e == hipSuccess) e = hipEventSynchronize(ses.ev[0]);
-        if (e != hipSuccess) break;
-        rd = mq_parse(ses.h);
-        last_E = rd.E;
-        if (rd.F == 0) break;
-        bool over = false;
-        for (int32_t i = 0; i < k; ++i)
-            over = over || rd.slot_rounds[i] > (unsigned long long)graphs[i]->plain.n + 1;
-        if (over) {
-            status = fail(GR_ERR_ITER_LIMIT, "a query ran past n + 1 rounds");
-            break;
-        }
-    }
-    if (e == hipSuccess) e = hipFreeAsync(ws, st);
-    else (void)hipFreeAsync(ws, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e == hipSuccess && stats) {
-        stats->rounds = (int32_t)rd.rounds;
-        stats->replays = (int32_t)ses.replays;
-        stats->edges_pushed = (int64_t)rd.edges;
-        stats->frontier_sum = (int64_t)rd.frontier;
-        stats->source_relaxations = (int64_t)rd.edges;
-    }
-    if (e == hipSuccess && iterations)
-        for (int32_t i = 0; i < k; ++i) iterations[i] = (int32_t)rd.slot_rounds[i];
-    mq_destroy(&ses);
-    if (e != hipSuccess) return hip_fail(e, "multi-query loop");
-    return status;
+    return multi_session(graphs, srcs, k, dist_out, st, stats, iterations);
 }
 
 // Batched same-graph queries (gr_sssp_batch, k >= 2): vertex-major distances,
