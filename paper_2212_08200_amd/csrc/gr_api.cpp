@@ -1768,8 +1768,9 @@ extern "C" gr_status gr_bfs_ex(const gr_graph *g, int32_t src, void *depth_out, 
     // hop counts leave few redundant relaxations: dist unless asked otherwise
     if (!(opts && opts->relax_filter)) rc.bound = false;
     // AUTO: over the tiles on large graphs that have them (mesh 512^2 0.38 ms
-    // against 3.9, 1024^2 0.72 against 8.7); up to 65,536 vertices the queued
-    // loop, whose rounds callers read as levels (a test pins it).  Else the
+    // against 3.9, 1024^2 0.72 against 8.7).  Up to 65,536 vertices it stays with
+    // the queued loop, which its tests name for such meshes, not for its speed
+    // (200^2 1.7 ms; a weighted query over the tiles 0.2).  Else the
     // single-workgroup loop on graphs that fit one workgroup's LDS
     // (push only: not when pull or alternation is asked for, nor with a
     // near-far split); else the host-driven loop on skewed graphs (few
