@@ -112,6 +112,11 @@ template <int CTRL>
 __device__ __forceinline__ unsigned long long dpp(unsigned long long x) {
     return (unsigned long long)dpp<CTRL>((uint32_t)(x >> 32)) << 32 | dpp<CTRL>((uint32_t)x);
 }
+// The first lane's value, as a scalar.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ __forceinline__ unsigned long long uniform(unsigned long long x) {
+    return (unsigned long long)uniform((uint32_t)(x >> 32)) << 32 | uniform((uint32_t)x);
+}
 // f over every run of 16 lanes, in each of them.
 template <typename T, typename F>
 __device__ __forceinline__ T over_row(T x, F f) {
@@ -133,20 +138,25 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
     return x;
 }
 
-// Totals of a slot (every lane of every wave gets them).
+// Totals of a slot (every lane of every wave gets them).  A launch's chain starts
+// with them: 64 bits only where the sum needs them.
 struct Totals {
-    unsigned long long F, E, flags, read;
-    uint32_t mu;
+    unsigned long long E;
+    uint32_t F, flags, read, mu;
 };
 __device__ __forceinline__ Totals read_slot(gptr<const unsigned long long> s) {
-    gptr<const unsigned long long> r = s + (threadIdx.x % kOrderRegions) * kOrderRegionWords;
     static_assert(kOrderRegions == 16, "a region per lane of a row");
-    const unsigned long long F = r[kRgF], E = r[kRgE], o = r[kRgFlags], d = r[kRgRead];
-    const uint32_t mu = ~(uint32_t)r[kRgMu];
-    const auto sum = [](unsigned long long x, unsigned long long y) { return x + y; };
-    return Totals{over_row(F, sum), over_row(E, sum),
-                  over_row(o, [](unsigned long long x, unsigned long long y) { return x | y; }), over_row(d, sum),
-                  over_row(mu, [](uint32_t x, uint32_t y) { return min(x, y); })};
+    gptr<const unsigned long long> r = s + (threadIdx.x % kOrderRegions) * kOrderRegionWords;
+    const unsigned long long E = r[kRgE];
+    const uint32_t F = (uint32_t)r[kRgF], o = (uint32_t)r[kRgFlags], d = (uint32_t)r[kRgRead], mu = ~(uint32_t)r[kRgMu];
+    const auto sum = [](auto x, auto y) { return x + y; };
+    Totals T;
+    T.F = uniform(over_row(F, sum));
+    T.E = uniform(over_row(E, sum));
+    T.flags = uniform(over_row(o, [](uint32_t x, uint32_t y) { return x | y; }));
+    T.read = uniform(over_row(d, sum));
+    T.mu = uniform(over_row(mu, [](uint32_t x, uint32_t y) { return min(x, y); }));
+    return T;
 }
 
 constexpr int kBeginJobs = 16;
@@ -349,11 +359,11 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
     const int s0 = (int)(g.round % 3), s1 = (int)((g.round + 1) % 3), s2 = (int)((g.round + 2) % 3);
     constexpr int slot_words = kOrderRegions * kOrderRegionWords;
     const Totals T = read_slot(ctl + s0 * slot_words);
-    const bool pulled = (T.flags & kFlagPulled) != 0ull;
-    const bool pull = (T.flags & kFlagOver) != 0ull ||
+    const bool pulled = (T.flags & (uint32_t)kFlagPulled) != 0u;
+    const bool pull = (T.flags & (uint32_t)kFlagOver) != 0u ||
                       (pulled ? kBackArcs * T.E + kBackFixed > (unsigned long long)n + kBackRead * T.read
                               : kOrderBias * (double)T.E * (double)T.E >= (double)n * (double)J.m);
-    const bool keep = pull && pulled && T.F * kBackShare <= (unsigned long long)n &&
+    const bool keep = pull && pulled && (unsigned long long)T.F * kBackShare <= (unsigned long long)n &&
                       (unsigned long long)n + kBackRead * T.read >= kBackFixed;
     // the slot of the round after next
     if (blockIdx.x == 0)
@@ -363,7 +373,7 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
         gptr<unsigned long long> state = ctl + kOrderState;
         for (int i = 0; i < kOrderRegions; ++i)
             state[kStPulledArcs] += ctl[s0 * slot_words + i * kOrderRegionWords + kRgRead];
-        if (T.F == 0ull) {
+        if (T.F == 0u) {
             if (state[kStDone] == 0ull) {
                 state[kStDone] = 1ull;
                 unsigned long long *st = g.stat + (size_t)blockIdx.y * kOrderStatWords;
@@ -388,7 +398,7 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
             }
         }
     }
-    if (T.F == 0ull) return;
+    if (T.F == 0u) return;
     gptr<uint32_t> dist = to_global(J.dist);
     __shared__ uint32_t sLow, sCnt, sArcs, sRead;
     if (t == 0) {
@@ -763,11 +773,11 @@ __global__ __launch_bounds__(256, 8) void k_order_batch(OrderBatchArgs g) {
     const int s0 = (int)(g.round % 3), s1 = (int)((g.round + 1) % 3), s2 = (int)((g.round + 2) % 3);
     constexpr int slot_words = kOrderRegions * kOrderRegionWords;
     const Totals T = read_slot(ctl + s0 * slot_words);
-    const bool pulled = (T.flags & kFlagPulled) != 0ull;
-    const bool pull = (T.flags & kFlagOver) != 0ull ||
+    const bool pulled = (T.flags & (uint32_t)kFlagPulled) != 0u;
+    const bool pull = (T.flags & (uint32_t)kFlagOver) != 0u ||
                       (pulled ? kBatchBack * T.E > (unsigned long long)n + T.read
                               : kOrderBias * (double)T.E * (double)T.E >= (double)n * (double)J.m);
-    const bool keep = pull && pulled && T.F * kBackShare <= (unsigned long long)n;
+    const bool keep = pull && pulled && (unsigned long long)T.F * kBackShare <= (unsigned long long)n;
     gptr<uint32_t> mus = to_global(g.b.mu);
     if (blockIdx.x == 0) {
         for (int i = t; i < slot_words; i += 256) ctl[s2 * slot_words + i] = 0ull;
@@ -781,7 +791,7 @@ __global__ __launch_bounds__(256, 8) void k_order_batch(OrderBatchArgs g) {
             state[kStPulledArcs] += ctl[s0 * slot_words + i * kOrderRegionWords + kRgRead];
             state[kStPairs] += ctl[s0 * slot_words + i * kOrderRegionWords + kRgPairs];
         }
-        if (T.F == 0ull) {
+        if (T.F == 0u) {
             if (state[kStDone] == 0ull) {
                 state[kStDone] = 1ull;
                 const unsigned long long v[kOrderBatchStatWords] = {1ull, (unsigned long long)g.round, state[kStPulls],
@@ -806,7 +816,7 @@ __global__ __launch_bounds__(256, 8) void k_order_batch(OrderBatchArgs g) {
                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    if (T.F == 0ull) return;
+    if (T.F == 0u) return;
     gptr<unsigned long long> mask = to_global(g.b.mask);
     gptr<const unsigned long long> on = mask + (size_t)s0 * n;
     gptr<unsigned long long> next = mask + (size_t)s1 * n;
