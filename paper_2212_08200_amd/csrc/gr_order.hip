@@ -70,6 +70,11 @@ constexpr double kOrderBias = 4.0;
 // kBackRead 1 the same); kBackShare 4 and 64 measure within 5%.
 constexpr unsigned long long kBackArcs = 16, kBackFixed = 1ull << 20, kBackRead = 4, kBackShare = 16;
 constexpr int kOrderVerts = 512;     // vertices per block of a pull, two per thread
+// Lines of a row's arcs that a pull reads at once after the first: rows are
+// bound by the chain of line, tails' distances and best (a bipartite graph of
+// 2,000 and 200,000 vertices whose rows have 500 arcs 1.52 ms with one, 1.25
+// with two, 1.01 with four, in pushes 0.95; R-MAT 15 3% less with four).
+constexpr int kPullWide = 4;
 constexpr int kPushRun = kOrderRun;  // arcs per queue entry
 
 // Counters of a region, as words: frontier vertices, their arcs, the complement
@@ -339,6 +344,38 @@ __device__ __forceinline__ void push_entries(const OrderJob &J, gptr<uint32_t> d
     }
 }
 
+// A row's arcs [e, e1) in order of weight by G lanes, U x G of them: lowers low
+// (the lanes' common best) and returns whether the arcs after them may lower it
+// further.
+template <int WT, int G, int U>
+__device__ __forceinline__ bool pull_arcs(gptr<const u32x2> arc, gptr<const uint32_t> dist, uint32_t mu, int32_t e,
+                                          int32_t e1, uint32_t &low, uint32_t &nread) {
+    const int lane = threadIdx.x & 63, my = e + (lane & (G - 1));
+    u32x2 a[U];
+    bool in[U];
+    uint32_t d[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) a[u] = arc[min(my + u * G, e1 - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        in[u] = my + u * G < e1 && plus<WT>(mu, a[u].y) < low;
+        if (in[u]) d[u] = dist[a[u].x];
+    }
+    uint32_t c = low;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (in[u]) {
+            ++nread;
+            c = min(c, plus<WT>(d[u], a[u].y));
+        }
+    c = min(c, dpp<0xB1>(c));  // the lanes of the group are active together
+    c = min(c, dpp<0x4E>(c));
+    c = min(c, dpp<0x141>(c));
+    if constexpr (G == 16) c = min(c, dpp<0x140>(c));
+    low = c;
+    return __ballot(in[U - 1] && plus<WT>(mu, a[U - 1].y) < low) >> ((lane & (64 - G)) + G - 1) & 1ull;
+}
+
 // AHEAD: the third weight and the row's bounds are loaded with the tails'
 // distances, for every vertex whose second arc may help, instead of one after
 // the other for those that go on.  Two trips less per round where they go to
@@ -527,7 +564,7 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
                 }
             }
             __syncthreads();
-            // eight lanes per vertex: a line of eight arcs at a time
+            // eight lanes per vertex: a line of eight arcs, then several at a time
             const uint32_t cnt = sCnt;
             gptr<const int32_t> ro = to_global(J.ro_in);
             for (uint32_t k = (uint32_t)t >> 3; k < cnt; k += 32u) {
@@ -541,21 +578,9 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
                     e0 = ro[v] + 2;
                     e1 = ro[v + 1];
                 }
-                for (int32_t e = e0; e < e1; e += 8) {
-                    const int32_t my = e + (t & 7);
-                    const u32x2 a = arc[min(my, e1 - 1)];
-                    const bool in = my < e1 && step(mu, a.y) < low;
-                    uint32_t c = low;
-                    if (in) {
-                        ++nread;
-                        c = min(c, step(dist[a.x], a.y));
-                    }
-#pragma unroll
-                    for (int o = 1; o < 8; o <<= 1) c = min(c, (uint32_t)__shfl_xor((int)c, o, 8));
-                    low = c;
-                    // the last of the eight still counts: the next eight may
-                    if (!(__ballot(in && step(mu, a.y) < low) >> ((lane & 56) + 7) & 1ull)) break;
-                }
+                bool more = e0 < e1 && pull_arcs<WT, 8, 1>(arc, dist, mu, e0, e1, low, nread);
+                for (int32_t e = e0 + 8; more && e < e1; e += 8 * kPullWide)
+                    more = pull_arcs<WT, 8, kPullWide>(arc, dist, mu, e, e1, low, nread);
                 // (only this block writes dist[v])
                 if ((t & 7) == 0 && low < sWas[k]) {
                     dist[v] = low;
@@ -580,7 +605,7 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
             if (t == 0) sCnt = 0u;
             __syncthreads();
         }
-        // long rows: 16 lanes per chunk, 16 arcs at a time
+        // long rows: 16 lanes per chunk
         const int32_t cfirst = ((int32_t)gridDim.x > vblocks ? (int32_t)blockIdx.x - vblocks : (int32_t)blockIdx.x);
         const int32_t cstep = ((int32_t)gridDim.x > vblocks ? (int32_t)gridDim.x - vblocks : (int32_t)gridDim.x) * 16;
         for (int32_t c = cfirst * 16 + (t >> 4); cfirst >= 0 && c < J.nchunks; c += cstep) {
@@ -589,20 +614,10 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
             const uint32_t b0 = ld_dev(dist + ch.x);
             uint32_t low = b0;
             if (!(step(mu, ch.w) < low)) continue;  // its lightest arc
-            for (int32_t e = (int32_t)ch.y; e < (int32_t)ch.z; e += 16) {
-                const int32_t my = e + (t & 15);
-                const u32x2 a = arc[min(my, (int32_t)ch.z - 1)];
-                const bool in = my < (int32_t)ch.z && step(mu, a.y) < low;
-                uint32_t c1 = low;
-                if (in) {
-                    ++nread;
-                    c1 = min(c1, step(dist[a.x], a.y));
-                }
-#pragma unroll
-                for (int o = 1; o < 16; o <<= 1) c1 = min(c1, (uint32_t)__shfl_xor((int)c1, o, 16));
-                low = c1;
-                if (!(__ballot(in && step(mu, a.y) < low) >> ((lane & 48) + 15) & 1ull)) break;
-            }
+            const int32_t e0 = (int32_t)ch.y, e1 = (int32_t)ch.z;
+            bool more = pull_arcs<WT, 16, 1>(arc, dist, mu, e0, e1, low, nread);
+            for (int32_t e = e0 + 16; more && e < e1; e += 16 * kPullWide)
+                more = pull_arcs<WT, 16, kPullWide>(arc, dist, mu, e, e1, low, nread);
             if ((t & 15) == 0 && low < b0 &&
                 low < __hip_atomic_fetch_min(dist + ch.x, low, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
                 lowest = min(lowest, low);
