@@ -20,9 +20,9 @@
 //
 // Bound by the chain of dependent loads in a round (its counters, a vertex, its
 // tails, its row, the tails again: 17-20 us at 200,000 to 1 M vertices, 6 us at
-// 32 K) and, in the first pulls, by their random 64-byte sectors.  Measured
-// against the push-only rounds: R-MAT 15, 432 -> 193 us; 20 (binary32), 1925 ->
-// 620; 22, 3421 -> 890.
+// 32 K) and, in the first pulls, by their random loads.  Measured against the
+// push-only rounds: R-MAT 15, 432 -> 190 us; 20 (binary32), 1925 -> 570; 22,
+// 3421 -> 820.
 //
 // A pull round reads every vertex's distance and lightest weight (streamed),
 // so small frontiers are pushed instead, from a queue of (vertex, run of 256
@@ -378,11 +378,12 @@ __device__ __forceinline__ bool pull_arcs(gptr<const u32x2> arc, gptr<const uint
 
 // AHEAD: the third weight and the row's bounds are loaded with the tails'
 // distances, for every vertex whose second arc may help, instead of one after
-// the other for those that go on.  Two trips less per round where they go to
-// memory (R-MAT 20 binary32 613 -> 586 us, 22 1058 -> 1020, uniform of a million
-// vertices 1350 -> 1307); where the tables stay in the L2s the loads for nothing
-// cost more (R-MAT 13 185 -> 191, 15 195 -> 199, 18 220 -> 225, 19 264 -> 266;
-// uniform of half a million, between: 950 -> 885).
+// the other for those that go on: two trips less per round, against loads for
+// nothing where few vertices go on (R-MAT 13 185 -> 191 us, 15 195 -> 199, 18
+// 220 -> 225, 19 264 -> 266, 20 binary32 613 -> 586, 22 1058 -> 1020; uniform of
+// half a million vertices 950 -> 885, of a million 1350 -> 1307).  How many go
+// on is not known beforehand; the line lies where the R-MAT graphs, of which the
+// fewest do, begin to gain.  Uniform graphs would from half a million on.
 constexpr int32_t kOrderAhead = 3 << 18;  // vertices from which on
 
 // WT: 0 uint32, 1 binary32, 2 unit steps.  Blocks [0, vblocks) of a pull take
@@ -666,9 +667,9 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
 // the graph, a saturating add and one comparison per arc, and rows read through
 // a scalar base.  A pull doesn't ask whether a tail is on the frontier: the
 // row's newer distances help the lanes along, 17 M arcs read instead of 38 M.
-// 64 sources on a scale-20 R-MAT graph of 32 M arcs: 2.00 ms, of which 0.16
+// 64 sources on a scale-20 R-MAT graph of 31 M arcs: 1.90 ms, of which 0.16
 // transposes the output (the queue-driven push rounds of the session kernels
-// took 11.4 ms); 0.55 ms at scale 15 (1.41).
+// took 10.8 ms); 0.65 ms at scale 15 (1.42).
 struct OrderBatchArgs {
     OrderBatch b;
     int64_t round;

@@ -84,9 +84,10 @@ constexpr int kTileMaxTiles = 1 << 24;  // a queue entry packs (query, tile) in 
 // done, 3 a wait timed out), arcs relaxed (with count), vertex expansions.
 constexpr int kTileStatWords = 3;
 
-// Workspace bytes of a launch over these queries' layouts, and the launch:
-// every dist row, in at most `groups` co-resident workgroups per compute unit.
-// wt: 0 uint32, 1 binary32, 2 unit steps; all layouts have `slots` slots.
+// Workspace bytes of a launch over these queries' layouts, and the launch: a
+// workgroup per compute unit, or per tile if there are fewer.  wt: 0 uint32, 1
+// binary32, 2 unit steps; all layouts have the same number of slots; count:
+// whether the arcs are counted.
 size_t tile_ws_bytes(const TileSet *const *sets, int32_t k);
 // A query's share: the sum over a launch's is at least its tile_ws_bytes.
 size_t tile_query_bytes(const TileSet &set);

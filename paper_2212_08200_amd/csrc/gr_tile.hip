@@ -697,8 +697,8 @@ hipError_t launch_tiles(const TileSet *const *sets, const int32_t *srcs, uint32_
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    // one workgroup per tile, up to what the chip holds (2048 threads per compute unit;
-    // eight slots take the registers of one workgroup per compute unit)
+    // one workgroup per tile, up to one per compute unit (its registers leave no
+    // room for another)
     const int64_t room = (int64_t)num_cu;
     const unsigned grid = (unsigned)(tiles < room ? tiles : room);
     const dim3 g(grid), blk(kTileThreads);
