@@ -500,8 +500,9 @@ def counter_traffic(kernel, workload, loop, layout, relax):
         if ":" in line and not line.startswith(("|", "#", "`")):
             k, _, v = line.partition(":")
             fields[k.strip()] = v.strip()
+    own = {"k_order": ("gr_order.hip", "gr_order.h"), "k_tile": ("gr_tile.hip", "gr_tile.h")}
     src = "".join(open(os.path.join(ROOT, "paper_2212_08200_amd", "csrc", f)).read()
-                  for f in ("gr_kernels.hip", "gr_device.h", "gr_internal.h"))
+                  for f in own.get(kernel, ("gr_kernels.hip",)) + ("gr_device.h", "gr_internal.h"))
     if fields.get("kernel_sources_sha256") != hashlib.sha256(src.encode()).hexdigest():
         return None
     if fields.get("loop") != loop or fields.get("layout") != layout or fields.get("relax_filter") != relax:

@@ -20,9 +20,10 @@
 //
 // Bound by the chain of dependent loads in a round (its counters, a vertex, its
 // tails, its row, the tails again: 17-20 us at 200,000 to 1 M vertices, 6 us at
-// 32 K) and, in the first pulls, by their random loads.  Measured against the
-// push-only rounds: R-MAT 15, 432 -> 190 us; 20 (binary32), 1925 -> 570; 22,
-// 3421 -> 820.
+// 32 K) and, on graphs past the caches, by memory: R-MAT 22 moves 247 MB per
+// launch of 60 us on average, 4.1 TB/s where a copy reaches 4.7 (62% of the L2s'
+// requests miss).  Measured against the push-only rounds: R-MAT 15, 432 -> 190
+// us; 20 (binary32), 1925 -> 570; 22, 3421 -> 820.
 //
 // A pull round reads every vertex's distance and lightest weight (streamed),
 // so small frontiers are pushed instead, from a queue of (vertex, run of 256
@@ -62,9 +63,9 @@ constexpr double kOrderBias = 4.0;
 // needs a queue from the pull before, which it keeps where a push could follow
 // (n + kBackRead R >= kBackFixed) and its own frontier was at most n /
 // kBackShare vertices.  Two R-MAT 17 graphs joined by a path of 300: 58.5 ms
-// when all rounds after the first pull pulled, 4.5 so (7.2 in pushes alone);
-// R-MAT 14 and a path of 1,000: 168 -> 8.6 (13.8); uniform of 300,000 vertices
-// with unreachable parts 0.73 -> 0.64.  kBackFixed is what keeping a queue and
+// when all rounds after the first pull pulled, 3.6 so (7.2 in pushes alone);
+// R-MAT 14 and a path of 1,000: 168 -> 8.2 (13.8); uniform of 300,000 vertices
+// with unreachable parts 0.73 -> 0.62.  kBackFixed is what keeping a queue and
 // a push's longer chain cost (with half of it R-MAT 18 with two arcs per
 // vertex took 0.25 ms against 0.235; with kBackArcs 4 instead of 16 against
 // kBackRead 1 the same); kBackShare 4 and 64 measure within 5%.
@@ -663,9 +664,10 @@ __global__ __launch_bounds__(256, 8) void k_order(OrderArgs g) {
 // The same rounds for up to 64 sources of one graph, a source per lane and the
 // distances vertex-major, so that an arc costs one 256-byte row: a pull reads a
 // vertex's arcs while they can still improve any of its lanes.  Bound by those
-// rows (L2 and memory) and by the instructions per arc, hence scalar loads of
-// the graph, a saturating add and one comparison per arc, and rows read through
-// a scalar base.  A pull doesn't ask whether a tail is on the frontier: the
+// rows (64 sources on R-MAT 22: 2.2 GB per launch of 505 us, 4.4 TB/s; 69% of
+// the L2s' requests miss) and where these stay in the caches by the instructions
+// per arc, hence scalar loads of the graph, a saturating add and one comparison
+// per arc, and rows read through a scalar base.  A pull doesn't ask whether a tail is on the frontier: the
 // row's newer distances help the lanes along, 17 M arcs read instead of 38 M.
 // 64 sources on a scale-20 R-MAT graph of 31 M arcs: 1.90 ms, of which 0.16
 // transposes the output (the queue-driven push rounds of the session kernels
@@ -684,7 +686,7 @@ constexpr int kBatchRun = 64;   // arcs per queue entry
 constexpr int kBatchKeep = 512;  // vertices that a block of a pull can put on the queue
 // Pushes again as above, where a pull costs a row per vertex: when kBatchBack E
 // <= n + R (1, 4 and 16 measure the same).  16 sources: two R-MAT 17 graphs
-// joined by a path of 300 135 -> 10.5 ms (the session kernels 11.7), R-MAT 14
+// joined by a path of 300 135 -> 10 ms (the session kernels 11.7), R-MAT 14
 // and a path of 1,000 202 -> 13.0 (23.4), R-MAT 20 with a tail of 3,000 200 ->
 // 47 (74); R-MAT 20 1.60 -> 1.52.
 constexpr unsigned long long kBatchBack = 4;
